@@ -26,6 +26,12 @@ constexpr uint32_t kTagInit = 4u << 24;
 __device__ __forceinline__ float gelu(float z) {
     return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
 }
+// gelu and its derivative from one erf
+__device__ __forceinline__ void gelu_both(float z, float &a, float &d) {
+    const float e = 1.0f + erff(z * 0.70710678118654752f);
+    a = 0.5f * z * e;
+    d = 0.5f * e + z * 0.39894228040143268f * expf(-0.5f * z * z);
+}
 __device__ __forceinline__ float gelu_d(float z) {
     return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) +
            z * 0.39894228040143268f * expf(-0.5f * z * z);
@@ -107,6 +113,404 @@ __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float
     m[i] = mi;
     v[i] = vi;
     p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+}
+
+// ---- fused surrogate network -------------------------------------------------
+// The whole chain of a row (both hidden layers, the output, the squared error
+// and the gradients back to the first layer's pre-activations) depends on that
+// row alone, so one block takes 16 rows through it: activations and their
+// derivatives stay in LDS, the weights are read from L2, and every product is
+// a 16-row strip of v_mfma_f32_16x16x4f32 tiles (FP32 operands and sums, as
+// the thread-per-output loops had).  A second launch forms the weight
+// gradients (sums over rows).  One launch per layer and direction, a thread
+// per output running its sum alone (a serial chain of up to 512 loads), took
+// 510 us for a gradient at batch 512, hidden 256; the two launches take 24 +
+// 5.5 us.  The rows kernel is bound by its chain (two products of 64 matrix
+// steps a wave on 32 of the 256 CUs, the error functions, four barriers), not
+// by its weight loads: requesting a group of them ahead or not measured alike.
+// Wider layers than the LDS tiles hold (hidden > 320) keep a launch per layer.
+// Operand lane layout as in the dense steps: lane l holds A[l % 16][l / 16]
+// and B[l / 16][l % 16]; accumulator i is row 4 (l / 16) + i, column l % 16.
+// Where a sum runs over a whole layer, lane group kr takes the terms 4 kr + t
+// of a 16-term chunk in step t, so that its four values are consecutive.
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int kMlpRows = 16;
+constexpr int kMlpThreads = 1024;
+constexpr int kMlpWaves = kMlpThreads / 64;
+constexpr int kMlpTiles = 2;                            // output tiles per wave, at most
+constexpr int kMlpU = 4;                                // 16-term chunks loaded together
+constexpr int kMlpMaxH = 320;   // widest hidden layer: three 16-row tiles in 64 KB of LDS
+
+// Hidden width padded to whole groups of chunks (zero columns).
+__host__ __device__ constexpr int mlp_pad(int h) { return (h + 16 * kMlpU - 1) / (16 * kMlpU) * (16 * kMlpU); }
+__host__ __device__ constexpr int mlp_stride(int HP) { return HP + 4; }
+// A1, gelu'(Z1), dZ2 (16 x hidden each, padded)
+inline size_t mlp_lds(int HP) { return sizeof(float) * 3 * kMlpRows * (size_t)mlp_stride(HP); }
+inline bool mlp_fits(int h) { return h <= kMlpMaxH; }
+static_assert(kMlpMaxH <= 16 * kMlpWaves * kMlpTiles, "accumulators of the widest layer");
+
+// Bounds-checked loads (zero outside the buffer's `bytes` bytes): a guard as a
+// condition became a branch and a wait per load.  out_if: bits that move an
+// offset outside any buffer when k >= K (by arithmetic, for the same reason).
+// Columns past the layer's width read other weights: they only reach output
+// columns past the width, which are dropped.
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int out_if(int k, int K) { return ((K - 1 - k) >> 31) & 0x7ffffff0; }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float *p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float buf_f(__amdgpu_buffer_rsrc_t r, int off) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
+__device__ __forceinline__ v4f buf_f4(__amdgpu_buffer_rsrc_t r, int off) {
+    const v4u v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    return (v4f){__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]),
+                 __uint_as_float(v[3])};
+}
+
+// Sum over the 16 lanes that share a row of the accumulator layout.
+__device__ __forceinline__ float row16_sum(float x) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+
+// GRAD: y's error against tgt and everything the weight gradients need: A1,
+// dZ2, dZ1 (B x h), per block the column sums pcol[blk][3][h] (dZ1, dZ2 and dy
+// A2) and pl[blk][2] (dy, squared error).  Otherwise only y.  MJ: output tiles
+// per wave; VEC: W2's rows are 16-byte aligned (h % 4 == 0).
+template <int MJ, bool GRAD, bool VEC>
+__global__ void __launch_bounds__(kMlpThreads)
+k_mlp_rows(const float *__restrict__ W1, const float *__restrict__ b1,
+           const float *__restrict__ W2, const float *__restrict__ b2,
+           const float *__restrict__ W3, const float *__restrict__ b3, int I, int H,
+           const float *__restrict__ X, const float *__restrict__ tgt, int64_t B,
+           float *__restrict__ y, float *__restrict__ A1g, float *__restrict__ dZ2g,
+           float *__restrict__ dZ1g, float *__restrict__ pcol, float *__restrict__ pl) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ float ysum[kMlpWaves][kMlpRows], dys[kMlpRows];
+    const int HP = mlp_pad(H), HS = mlp_stride(HP), nt = HP / 16;
+    float *A1 = lds, *D1 = A1 + kMlpRows * HS, *G2 = D1 + kMlpRows * HS;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kr = lane >> 4, kc = lane & 15;
+    const int64_t r0 = (int64_t)blockIdx.x * kMlpRows;
+    const __amdgpu_buffer_rsrc_t w1 = buffer_of(W1, 4ll * I * H), w2 = buffer_of(W2, 4ll * H * H);
+    const __amdgpu_buffer_rsrc_t xb =
+        buffer_of(X + r0 * I, 4ll * I * min((int64_t)kMlpRows, B - r0));
+    v4f acc[MJ];
+    // first layer: the terms k0 + kr of four at a time
+#pragma unroll
+    for (int s = 0; s < MJ; ++s) {
+        const int c = 16 * (w + kMlpWaves * s) + kc;
+        const float bias = c < H ? b1[c] : 0.0f;
+        acc[s] = (v4f){bias, bias, bias, bias};
+    }
+    for (int k0 = 0; k0 < I; k0 += 4 * kMlpU) {
+        float a[kMlpU], b[kMlpU][MJ];
+#pragma unroll
+        for (int u = 0; u < kMlpU; ++u) {
+            const int k = k0 + 4 * u + kr;
+            a[u] = buf_f(xb, 4 * (kc * I + k) | out_if(k, I));   // rows past the batch: zeros
+#pragma unroll
+            for (int s = 0; s < MJ; ++s) {
+                const int c = 16 * (w + kMlpWaves * s) + kc;
+                b[u][s] = buf_f(w1, 4 * (k * H + c));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kMlpU; ++u)
+#pragma unroll
+            for (int s = 0; s < MJ; ++s)
+                acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u][s], acc[s], 0, 0, 0);
+    }
+#pragma unroll
+    for (int s = 0; s < MJ; ++s) {
+        const int J = w + kMlpWaves * s, c = 16 * J + kc;
+        if (J >= nt) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 4 * kr + i;
+            float a, d;
+            if constexpr (GRAD) gelu_both(acc[s][i], a, d);
+            else a = gelu(acc[s][i]);
+            if (c >= H) a = 0.0f;
+            A1[r * HS + c] = a;
+            if constexpr (GRAD) {
+                D1[r * HS + c] = d;
+                if (c < H && r0 + r < B) A1g[(r0 + r) * H + c] = a;
+            }
+        }
+    }
+    // second layer: chunks of 16 terms
+#pragma unroll
+    for (int s = 0; s < MJ; ++s) {
+        const int c = 16 * (w + kMlpWaves * s) + kc;
+        const float bias = c < H ? b2[c] : 0.0f;
+        acc[s] = (v4f){bias, bias, bias, bias};
+    }
+    {
+        // the next group's weights are requested before the current group's
+        // matrix steps
+        float b[kMlpU][MJ][4], bn[kMlpU][MJ][4];
+        auto wload = [&](int k0, float (&v)[kMlpU][MJ][4]) {
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u)
+#pragma unroll
+                for (int s = 0; s < MJ; ++s) {
+                    const int c = 16 * (w + kMlpWaves * s) + kc;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int k = k0 + 16 * u + 4 * kr + t;
+                        v[u][s][t] = buf_f(w2, 4 * (k * H + c));   // k >= h: zero
+                    }
+                }
+        };
+        wload(0, b);
+        __syncthreads();
+        for (int k0 = 0; k0 < HP; k0 += 16 * kMlpU) {
+            wload(k0 + 16 * kMlpU, bn);   // zeros past the last group
+            __builtin_amdgcn_sched_barrier(0);   // (else the loads sink below the steps)
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u) {
+                const v4f a = *reinterpret_cast<const v4f *>(A1 + kc * HS + k0 + 16 * u + 4 * kr);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int s = 0; s < MJ; ++s)
+                        acc[s] =
+                            __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[u][s][t], acc[s], 0, 0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u)
+#pragma unroll
+                for (int s = 0; s < MJ; ++s)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) b[u][s][t] = bn[u][s][t];
+        }
+    }
+    // output: y_r = b3 + sum_c gelu(z2) w3, summed per wave, then over waves
+    float yp[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    v4f d2[MJ];   // gelu'(z2); acc becomes gelu(z2)
+#pragma unroll
+    for (int s = 0; s < MJ; ++s) {
+        const int c = 16 * (w + kMlpWaves * s) + kc;
+        const float w3 = c < H ? W3[c] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float a, d = 0.0f;
+            if constexpr (GRAD) gelu_both(acc[s][i], a, d);
+            else a = gelu(acc[s][i]);
+            acc[s][i] = a;
+            d2[s][i] = d;
+            yp[i] += c < H ? a * w3 : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        yp[i] = row16_sum(yp[i]);
+        if (kc == 0) ysum[w][4 * kr + i] = yp[i];
+    }
+    __syncthreads();
+    if (tid < kMlpRows) {
+        float v = b3[0];
+        for (int q = 0; q < kMlpWaves; ++q) v += ysum[q][tid];
+        const bool on = r0 + tid < B;
+        if constexpr (GRAD) {
+            const float e = on ? v - tgt[r0 + tid] : 0.0f;
+            dys[tid] = 2.0f * e / (float)B;
+            ysum[0][tid] = e * e;
+        } else if (on) {
+            y[r0 + tid] = v;
+        }
+    }
+    if constexpr (!GRAD) return;
+    __syncthreads();
+    if (tid == 0) {
+        float sd = 0.0f, se = 0.0f;
+        for (int r = 0; r < kMlpRows; ++r) {
+            sd += dys[r];
+            se += ysum[0][r];
+        }
+        pl[2 * (int64_t)blockIdx.x] = sd;
+        pl[2 * (int64_t)blockIdx.x + 1] = se;
+    }
+    // dZ2 = dy w3 gelu'(z2); the column sums over the block's rows
+    float *pc = pcol + (int64_t)blockIdx.x * 3 * H;
+#pragma unroll
+    for (int s = 0; s < MJ; ++s) {
+        const int J = w + kMlpWaves * s, c = 16 * J + kc;
+        if (J >= nt) continue;
+        const float w3 = c < H ? W3[c] : 0.0f;
+        float sb = 0.0f, sw = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 4 * kr + i;
+            const float dy = dys[r];
+            const bool on = c < H && r0 + r < B;
+            const float g = on ? dy * w3 * d2[s][i] : 0.0f;
+            G2[r * HS + c] = g;
+            if (on) dZ2g[(r0 + r) * H + c] = g;
+            sb += g;
+            sw += on ? dy * acc[s][i] : 0.0f;
+        }
+        sb += __shfl_xor(sb, 16, 64);
+        sb += __shfl_xor(sb, 32, 64);
+        sw += __shfl_xor(sw, 16, 64);
+        sw += __shfl_xor(sw, 32, 64);
+        if (kr == 0 && c < H) {
+            pc[H + c] = sb;
+            pc[2 * H + c] = sw;
+        }
+    }
+    // dZ1 = (dZ2 W2^T) gelu'(z1): the operand row c of W2 is contiguous in k
+#pragma unroll
+    for (int s = 0; s < MJ; ++s) acc[s] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    {
+        v4f b[kMlpU][MJ], bn[kMlpU][MJ];
+        auto wload = [&](int k0, v4f (&v)[kMlpU][MJ]) {
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u)
+#pragma unroll
+                for (int s = 0; s < MJ; ++s) {
+                    const int c = 16 * (w + kMlpWaves * s) + kc, k = k0 + 16 * u + 4 * kr;
+                    if constexpr (VEC) {   // h % 4 == 0: k < h holds for all four or none
+                        v[u][s] = buf_f4(w2, 4 * (c * H + k) | out_if(k, H));
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            v[u][s][t] = buf_f(w2, 4 * (c * H + k + t) | out_if(k + t, H));
+                    }
+                }
+        };
+        wload(0, b);
+        __syncthreads();
+        for (int k0 = 0; k0 < HP; k0 += 16 * kMlpU) {
+            wload(k0 + 16 * kMlpU, bn);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u) {
+                const v4f a = *reinterpret_cast<const v4f *>(G2 + kc * HS + k0 + 16 * u + 4 * kr);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int s = 0; s < MJ; ++s)
+                        acc[s] =
+                            __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[u][s][t], acc[s], 0, 0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u)
+#pragma unroll
+                for (int s = 0; s < MJ; ++s) b[u][s] = bn[u][s];
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < MJ; ++s) {
+        const int J = w + kMlpWaves * s, c = 16 * J + kc;
+        if (J >= nt) continue;
+        float sb = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 4 * kr + i;
+            const bool on = c < H && r0 + r < B;
+            const float g = on ? acc[s][i] * D1[r * HS + c] : 0.0f;
+            if (on) dZ1g[(r0 + r) * H + c] = g;
+            sb += g;
+        }
+        sb += __shfl_xor(sb, 16, 64);
+        sb += __shfl_xor(sb, 32, 64);
+        if (kr == 0 && c < H) pc[c] = sb;
+    }
+}
+
+// Weight gradients from the rows' activations and pre-activation gradients:
+// dW2 = A1^T dZ2, dW1 = X^T dZ1 (one block per 16 x 32 tile, its eight waves
+// taking every eighth step of four rows, summed in LDS in wave order), then
+// db1, db2, dW3 from the per-block column sums (64 columns a block), then db3
+// and the loss.  grad: W1, b1, W2, b2, W3, b3.
+constexpr int kWgThreads = 512;
+constexpr int kWgWaves = kWgThreads / 64;
+__global__ void __launch_bounds__(kWgThreads)
+k_mlp_wgrad(const float *__restrict__ X, const float *__restrict__ A1,
+            const float *__restrict__ dZ1, const float *__restrict__ dZ2, int I, int H, int64_t B,
+            const float *__restrict__ pcol, const float *__restrict__ pl, int nblk,
+            float *__restrict__ dW1, float *__restrict__ db1, float *__restrict__ dW2,
+            float *__restrict__ db2, float *__restrict__ dW3, float *__restrict__ db3,
+            float *__restrict__ loss) {
+    __shared__ float red[kWgWaves][16 * 32];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int to = (H + 31) / 32, n2 = (H + 15) / 16 * to, n1 = (I + 15) / 16 * to;
+    const int ncs = (H + 63) / 64;
+    int blk = blockIdx.x;
+    if (blk < n2 + n1) {
+        const bool second = blk < n2;
+        if (!second) blk -= n2;
+        const float *L = second ? A1 : X, *G = second ? dZ2 : dZ1;
+        float *dW = second ? dW2 : dW1;
+        const int K = second ? H : I;
+        const int i0 = 16 * (blk / to), o0 = 32 * (blk % to);
+        const int kr = lane >> 4, kc = lane & 15;
+        const bool ia = i0 + kc < K, oa = o0 + kc < H, ob = o0 + 16 + kc < H;
+        v4f acc0 = (v4f){0.0f, 0.0f, 0.0f, 0.0f}, acc1 = acc0;
+        for (int64_t b0 = 4 * w; b0 < B; b0 += 4 * kWgWaves * kMlpU) {
+            float a[kMlpU], g0[kMlpU], g1[kMlpU];
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u) {
+                const int64_t b = b0 + 4 * kWgWaves * u + kr;
+                const bool on = b < B;
+                a[u] = on && ia ? L[b * K + i0 + kc] : 0.0f;
+                g0[u] = on && oa ? G[b * H + o0 + kc] : 0.0f;
+                g1[u] = on && ob ? G[b * H + o0 + 16 + kc] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u) {
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], g0[u], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], g1[u], acc1, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            red[w][(4 * kr + i) * 32 + kc] = acc0[i];
+            red[w][(4 * kr + i) * 32 + 16 + kc] = acc1[i];
+        }
+        __syncthreads();
+        const int r = tid >> 5, c = tid & 31;   // 512 threads, one entry each
+        float s = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kWgWaves; ++q) s += red[q][tid];
+        if (i0 + r < K && o0 + c < H) dW[(int64_t)(i0 + r) * H + o0 + c] = s;
+        return;
+    }
+    blk -= n2 + n1;
+    if (blk < 3 * ncs) {
+        const int arr = blk / ncs, c = 64 * (blk % ncs) + lane;
+        float s = 0.0f;
+        if (c < H)
+            for (int q = w; q < nblk; q += kWgWaves) s += pcol[((int64_t)q * 3 + arr) * H + c];
+        red[w][lane] = s;
+        __syncthreads();
+        if (w == 0 && c < H) {
+            float t = 0.0f;
+            for (int q = 0; q < kWgWaves; ++q) t += red[q][lane];
+            (arr == 0 ? db1 : arr == 1 ? db2 : dW3)[c] = t;
+        }
+        return;
+    }
+    if (w == 0) {
+        float sd = 0.0f, se = 0.0f;
+        for (int q = lane; q < nblk; q += 64) {
+            sd += pl[2 * (int64_t)q];
+            se += pl[2 * (int64_t)q + 1];
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            sd += __shfl_xor(sd, o, 64);
+            se += __shfl_xor(se, o, 64);
+        }
+        if (lane == 0) {
+            *db3 = sd;
+            if (loss) *loss = se / (float)B;
+        }
+    }
 }
 
 // Glorot-uniform weights from Philox words, zero biases.
@@ -355,6 +759,30 @@ lne_status mlp_validate(lne_ctx *ctx, int in, int h, int64_t B) {
     return LNE_OK;
 }
 
+// The fused rows kernel, hidden width within mlp_fits.
+template <bool GRAD>
+lne_status mlp_rows(lne_ctx *ctx, int in, int h, const float *P, const float *X, const float *tgt,
+                    int64_t B, float *y, float *A1, float *dZ2, float *dZ1, float *pcol,
+                    float *pl) {
+    const MlpLayout L(in, h);
+    const int HP = mlp_pad(h), mj = (HP / 16 + kMlpWaves - 1) / kMlpWaves;
+    const bool vec = h % 4 == 0 && (uintptr_t)(P + L.W2) % 16 == 0;
+    const unsigned grid = grid_of(B, kMlpRows);
+    {
+        Launch Lc(ctx, "mlp_rows");
+#define LNE_MR(MJ, VEC)                                                                      \
+    k_mlp_rows<MJ, GRAD, VEC><<<grid, kMlpThreads, mlp_lds(HP), ctx->stream>>>(              \
+        P + L.W1, P + L.b1, P + L.W2, P + L.b2, P + L.W3, P + L.b3, in, h, X, tgt, B, y, A1, \
+        dZ2, dZ1, pcol, pl)
+        if (mj <= 1 && vec) LNE_MR(1, true);
+        else if (mj <= 1) LNE_MR(1, false);
+        else if (vec) LNE_MR(2, true);
+        else LNE_MR(2, false);
+#undef LNE_MR
+    }
+    return check_launch(ctx, "mlp_rows");
+}
+
 // Forward pass keeping the pre-activations: Z1, A1, Z2, A2 (B x h each), y.
 lne_status mlp_fwd(lne_ctx *ctx, int in, int h, const float *P, const float *X, int64_t B,
                    float *Z1, float *A1, float *Z2, float *A2, float *y) {
@@ -402,6 +830,10 @@ lne_status lne_mlp_forward(lne_ctx *ctx, int32_t in_dim, int32_t hidden, const f
     if (!ctx) return LNE_EINVAL;
     LNE_TRY(mlp_validate(ctx, in_dim, hidden, batch));
     if (!params || !X || !y) return fail(ctx, LNE_EINVAL, "mlp_forward: NULL argument");
+    if (mlp_fits(hidden))
+        return mlp_rows<false>(ctx, in_dim, hidden, params, X, nullptr, batch, y, nullptr, nullptr,
+                               nullptr, nullptr, nullptr);
+    // wider networks than the fused kernel's LDS tile holds: a launch per layer
     Buf act(ctx);
     LNE_TRY(alloc(ctx, act, sizeof(float) * (size_t)(2 * batch * hidden)));
     float *A1 = act.as<float>(), *A2 = A1 + batch * hidden;
@@ -417,6 +849,24 @@ lne_status lne_mlp_grad(lne_ctx *ctx, int32_t in_dim, int32_t hidden, const floa
     const MlpLayout Ly(in_dim, hidden);
     const int64_t Bh = batch * hidden;
     Buf ws(ctx);
+    if (mlp_fits(hidden)) {
+        const int64_t nblk = ceil_div(batch, kMlpRows);
+        LNE_TRY(alloc(ctx, ws, sizeof(float) * (size_t)(3 * Bh + nblk * (3 * hidden + 2))));
+        float *A1 = ws.as<float>(), *dZ2 = A1 + Bh, *dZ1 = dZ2 + Bh;
+        float *pcol = dZ1 + Bh, *pl = pcol + nblk * 3 * hidden;
+        LNE_TRY(mlp_rows<true>(ctx, in_dim, hidden, params, X, target, batch, nullptr, A1, dZ2,
+                               dZ1, pcol, pl));
+        const int64_t to = ceil_div(hidden, 32);
+        const int64_t blocks = (ceil_div(hidden, 16) + ceil_div(in_dim, 16)) * to +
+                               3 * ceil_div(hidden, 64) + 1;
+        {
+            Launch L(ctx, "mlp_wgrad");
+            k_mlp_wgrad<<<(unsigned)blocks, kWgThreads, 0, ctx->stream>>>(
+                X, A1, dZ1, dZ2, in_dim, hidden, batch, pcol, pl, (int)nblk, grad + Ly.W1,
+                grad + Ly.b1, grad + Ly.W2, grad + Ly.b2, grad + Ly.W3, grad + Ly.b3, loss);
+        }
+        return check_launch(ctx, "mlp_wgrad");
+    }
     LNE_TRY(alloc(ctx, ws, sizeof(float) * (size_t)(6 * Bh + 2 * batch)));
     float *Z1 = ws.as<float>(), *A1 = Z1 + Bh, *Z2 = A1 + Bh, *A2 = Z2 + Bh;
     float *dZ2 = A2 + Bh, *dZ1 = dZ2 + Bh, *y = dZ1 + Bh, *dy = y + batch;

@@ -47,6 +47,30 @@ def test_mlp_forward_and_gradient_match_oracle(lne, ctx, B):
     assert np.linalg.norm(g - g0) <= 1e-4 * np.linalg.norm(g0)
 
 
+@pytest.mark.parametrize("n_in,h,B", [(1, 1, 1), (3, 17, 16), (21, 64, 33), (40, 130, 100),
+                                      (21, 300, 17), (5, 320, 48), (21, 321, 20)])
+def test_network_at_the_edges_of_its_tiles(lne, ctx, n_in, h, B):
+    """Odd widths and batches around the 16-row, 16-column and 32-column tiles,
+    the widest fused network (320) and the first that is not (321).  Each sum
+    has at most 1 + max(n_in, h, B) terms of relative rounding u = 2^-24; the
+    three chained layers and the sums over rows stay within 1e-4 in norm."""
+    import torch
+    rng = np.random.default_rng(h)
+    p = lne.mlp_init(ctx, n_in, h, seed=h)
+    p += 0.05 * torch.from_numpy(rng.standard_normal(p.numel()).astype(np.float32)).cuda()
+    X = rng.standard_normal((B, n_in)).astype(np.float32)
+    t = rng.standard_normal(B).astype(np.float32)
+    pn = p.cpu().numpy().astype(np.float64)
+    Xd, td = torch.from_numpy(X).cuda(), torch.from_numpy(t).cuda()
+    y0, _ = S.forward(pn, X.astype(np.float64), n_in, h)
+    y = lne.mlp_forward(ctx, n_in, h, p, Xd).cpu().numpy()
+    np.testing.assert_allclose(y, y0, rtol=1e-4, atol=1e-5)
+    g, loss = lne.mlp_grad(ctx, n_in, h, p, Xd, td)
+    l0, g0 = S.loss_and_grad(pn, X.astype(np.float64), t.astype(np.float64), n_in, h)
+    assert abs(loss.item() - l0) <= 1e-4 * max(l0, 1e-3)
+    assert np.linalg.norm(g.cpu().numpy() - g0) <= 1e-4 * np.linalg.norm(g0)
+
+
 def test_adam_step_matches_oracle(lne, ctx):
     import torch
     p = lne.mlp_init(ctx, IN, H, seed=9)
