@@ -502,56 +502,85 @@ __global__ void k_w_to_bf16t(const double *__restrict__ W, int kin, int kout,
 constexpr int kSolveThreads = 1024;
 constexpr int kEigMaxK = 288;   // widest k of the Cholesky and eigen-solver kernels
 
-// Right-looking upper Cholesky of A (k x k, in place; LDS or global).
-// Returns false on a pivot that is not positive relative to the original
-// diagonal.  The trailing update takes rows by wave and columns by lane.
-__device__ bool chol_upper(double *A, int k, const double *diag0) {
-    __shared__ int bad;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    constexpr int NW = kSolveThreads / 64;
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
-    for (int j = 0; j < k; ++j) {
-        const double piv = A[(int64_t)j * k + j];
-        const bool ok = piv > 1e-14 * diag0[j] && piv > 0.0 && isfinite(piv);
-        if (!ok) {
-            if (threadIdx.x == 0) bad = 1;
-            __syncthreads();
-            return false;
-        }
-        const double r = sqrt(piv);
-        __syncthreads();
-        for (int c = j + 1 + threadIdx.x; c < k; c += kSolveThreads) A[(int64_t)j * k + c] /= r;
-        if (threadIdx.x == 0) A[(int64_t)j * k + j] = r;
-        __syncthreads();
-        for (int i = j + 1 + wv; i < k; i += NW) {
-            const double aji = A[(int64_t)j * k + i];
-            for (int c = i + lane; c < k; c += 64)
-                A[(int64_t)i * k + c] -= aji * A[(int64_t)j * k + c];
-        }
-        __syncthreads();
-    }
-    return bad == 0;
+// A double moved between lanes by a DPP pattern (both halves).
+template <int CTRL>
+__device__ inline double dpp_d(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+__device__ inline double readlane_d(double x, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                            __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
+// Bounds-checked doubles of a k x k matrix: zero outside the rows and columns,
+// stores there dropped (out_if turns an index past k into an offset outside
+// the buffer by arithmetic; a guard written as a condition becomes a branch
+// and a wait per access).
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int out_if(int i, int k) { return ((k - 1 - i) >> 31) & 0x7ffffff0; }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t square_buf(double *p, int k) {
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, 8 * k * k, 0x00020000);
+}
+__device__ __forceinline__ double buf_d(__amdgpu_buffer_rsrc_t r, int off) {
+    const v2u v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    return __hiloint2double((int)v[1], (int)v[0]);
+}
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int off, double x) {
+    const v2u v = (v2u){(unsigned)__double2loint(x), (unsigned)__double2hiint(x)};
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
 }
 
 // Cholesky of the Gram G = R^T R (a shifted retry if a pivot fails) and W =
-// R^-1.  IN_LDS: the k x k matrix is factored in LDS (k <= kCholMaxLds), then
-// W is formed there row by row while R is read from G.  The inverse takes
-// the rows from the bottom up, all columns of a row at once; each entry is
-// the sum over j ascending of R[i][j] W[j][c], as a column-by-column
-// back-substitution forms it.
-constexpr int kCholMaxLds = 140;
-template <bool IN_LDS>
-__global__ void __launch_bounds__(kSolveThreads)
-k_chol_inv(double *__restrict__ G, int k, double *__restrict__ W, double *__restrict__ diag0,
-           int32_t *__restrict__ status, int32_t *__restrict__ shifted, int64_t n_rows,
-           const int32_t *__restrict__ skip, int32_t *__restrict__ run_next) {
-    extern __shared__ double lds_m[];
+// R^-1 by one workgroup, in 16 x 16 tiles on FP64 matrix instructions.
+//
+// Factorisation, right-looking over tile rows j.  The tiles above the diagonal
+// live in the registers of waves 1..7 (accumulator layout: row l / 16 + 4 i,
+// column l % 16), dealt in row order; the diagonal ones in LDS.
+//   - Each tile T of row j becomes X = R_jj^-T T: M T with M the block's
+//     explicit inverse, then one correction X += M (T - R_jj^T X), which
+//     leaves the residual of a substitution.  X goes to LDS (the panel) and G.
+//   - Every tile (I, J), I > j, takes the panel's rank-16 update in four
+//     matrix steps; wave 0 updates and factors the next diagonal block first,
+//     then updates the others.
+// The diagonal block is factored by one wave with a column per lane (the
+// multipliers by lane reads); lanes 16..31 carry the identity through the same
+// row operations, so they end with M.
+// Inverse: W_JJ = M^T; then each wave takes whole tile columns J and forms
+// W_IJ = -W_II sum_{L > I} R_IL W_LJ for I = J-1 .. 0 with no barrier: an
+// accumulator tile is the next product's B operand as it stands (term
+// l / 16 + 4 t in step t).
+// Bound by the 16-step chain of each diagonal block (a reciprocal square root
+// and a lane read per step, with the two barriers of a panel) and, at the
+// widest, by the FP64 matrix rate of one CU.  A column at a time with three
+// barriers each took 3580 us at k = 266, 459 us at 138 and 76 us at 42; this
+// takes 348, 77 and 17 us (the width sets the tiles a wave keeps: MAXT).
+constexpr int kCholThreads = 512;
+constexpr int kCholWaves = kCholThreads / 64;
+constexpr int kCholGroup = 4;   // products of the inverse whose operands are loaded together
+// LDS row stride of the panel: an odd number of tiles, so that two of its rows
+// read by one half wave sit in different banks.
+__host__ __device__ constexpr int panel_ld(int nt) { return 16 * (nt | 1); }
+constexpr int kBlk = 16 * 17;   // a diagonal block in LDS, rows 17 apart
+inline size_t chol_lds(int nt) {
+    return sizeof(double) * (size_t)(16 * panel_ld(nt) + (nt + 1) * kBlk);
+}
+
+template <int MAXT>
+__global__ void __launch_bounds__(kCholThreads)
+k_chol_inv(double *Gb, int k, double *Wb, int32_t *__restrict__ status,
+           int32_t *__restrict__ shifted, int64_t n_rows, const int32_t *__restrict__ skip,
+           int32_t *__restrict__ run_next) {
+    extern __shared__ double lds_c[];
+    __shared__ double diag0[kEigMaxK];
+    __shared__ int bad;
+    __shared__ double sigma_s;
+    double *G = Gb + (int64_t)blockIdx.x * k * k;
+    double *W = Wb + (int64_t)blockIdx.x * k * k;
     {
         const int64_t b = blockIdx.x;
-        G += b * k * k;
-        W += b * k * k;
-        diag0 += b * k;
         status += kFlagStride * b;
         shifted += kFlagStride * b;
         if (skip) skip += kFlagStride * b;
@@ -561,81 +590,251 @@ k_chol_inv(double *__restrict__ G, int k, double *__restrict__ W, double *__rest
         if (run_next && threadIdx.x == 0) *run_next = 0;
         return;
     }
-    const int64_t kk = (int64_t)k * k;
-    __shared__ double trace;
-    double *A = IN_LDS ? lds_m : G;
-    for (int64_t i = threadIdx.x; i < kk; i += kSolveThreads) {
-        W[i] = G[i];
-        if (IN_LDS) A[i] = G[i];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int kr = lane >> 4, kc = lane & 15;
+    const int nt = (k + 15) / 16, PL = panel_ld(nt);
+    double *P = lds_c, *Dg = P + 16 * PL, *M = Dg + nt * kBlk;
+    const __amdgpu_buffer_rsrc_t gb = square_buf(G, k), wb = square_buf(W, k);
+    for (int i = tid; i < k; i += kCholThreads) diag0[i] = G[(int64_t)i * k + i];
+    if (tid == 0) bad = 0;
+    // this wave's tiles: every seventh one above the diagonal, in row order
+    int TI[MAXT], TJ[MAXT];
+#pragma unroll
+    for (int s = 0; s < MAXT; ++s) {
+        int t = (w - 1) + (kCholWaves - 1) * s, I = 0;
+        if (w == 0) t = nt * nt;
+        while (I < nt && t >= nt - 1 - I) { t -= nt - 1 - I; ++I; }
+        TI[s] = I < nt ? I : nt;   // nt: no tile
+        TJ[s] = I < nt ? I + 1 + t : nt;
     }
-    for (int i = threadIdx.x; i < k; i += kSolveThreads) diag0[i] = G[(int64_t)i * k + i];
     __syncthreads();
-    bool ok = chol_upper(A, k, diag0);
-    bool sh = false;
-    if (!ok) {
-        // shifted retry: G + sigma I, sigma = 11 (n k + k (k + 1)) u trace(G)
-        if (threadIdx.x == 0) {
-            double t = 0.0;
-            for (int i = 0; i < k; ++i) t += diag0[i];
-            trace = t;
+    // factors diagonal block j (wave 0): Dg[j] becomes R_jj (zeros below), M
+    auto factor = [&](int j, bool sh) {
+        double *D = Dg + j * kBlk;
+        double a[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const double x = D[i * 17 + kc];
+            a[i] = (lane & 16) ? (i == kc ? 1.0 : 0.0) : x;
+        }
+        // lane i: the least pivot i may be, whether it was
+        const int gi = 16 * j + kc;
+        const double least = sh || gi >= k ? 0.0 : 1e-14 * diag0[gi < k ? gi : 0];
+        int good = 1;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const double piv = readlane_d(a[q], q);
+            const int fine = (int)(a[q] > least) & (int)(a[q] > 0.0) & (int)(a[q] < INFINITY);
+            good &= fine | (int)(lane != q);
+            // 1 / sqrt by the hardware estimate and two Newton steps
+            const double h = 0.5 * piv;
+            double y = __builtin_amdgcn_rsq(piv);
+            y = y * fma(-h * y, y, 1.5);
+            y = y * fma(-h * y, y, 1.5);
+            a[q] *= y;
+#pragma unroll
+            for (int i = q + 1; i < 16; ++i) a[i] = fma(-readlane_d(a[q], i), a[q], a[i]);
+            __builtin_amdgcn_sched_barrier(0);   // (else the lane reads pile up and spill)
+        }
+        if (lane < 32) {
+            double *o = (lane < 16 ? D : M) + kc;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[i * 17] = lane >= 16 || i <= kc ? a[i] : 0.0;
+        }
+        if (__any(!good) && lane == 0) bad = 1;
+    };
+    v4d acc[MAXT];
+    bool ok = false, sh = false;
+    for (int attempt = 0; attempt < 2 && !ok; ++attempt) {
+        // (lane and panel indices are made opaque where a loop starts, so that
+        // the addresses in it are formed there instead of being kept, one per
+        // tile, from outside: they would take more registers than the tiles)
+        asm volatile("" : "+v"(kr), "+v"(kc));
+        sh = attempt == 1;
+        double sigma = 0.0;
+        if (sh) {
+            // shifted retry: G + sigma I, sigma = 11 (n k + k (k + 1)) u trace(G)
+            if (tid == 0) {
+                double t = 0.0;
+                for (int i = 0; i < k; ++i) t += diag0[i];
+                sigma_s = 11.0 * ((double)n_rows * k + (double)k * (k + 1)) *
+                          1.1102230246251565e-16 * t;
+                bad = 0;
+            }
+            __syncthreads();
+            sigma = sigma_s;
+        }
+        // the retry reads G's lower triangle (R is written to the upper one)
+        const int rs = sh ? 1 : k, cs = sh ? k : 1;
+#pragma unroll
+        for (int s = 0; s < MAXT; ++s) {
+            const int c = 16 * TJ[s] + kc, out = out_if(c, k);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc[s][i] = buf_d(gb, 8 * ((16 * TI[s] + kr + 4 * i) * rs + c * cs) | out);
+        }
+        // diagonal blocks from the lower triangle and the saved diagonal,
+        // identity past k
+        for (int e = tid; e < 256 * nt; e += kCholThreads) {
+            const int r = (e >> 4) & 15, c = e & 15, r0 = 16 * (e >> 8) + r, c0 = 16 * (e >> 8) + c;
+            const int hi = max(r0, c0), lo = min(r0, c0);
+            double x = buf_d(gb, 8 * (hi * k + lo) | out_if(hi, k));
+            if (r == c) x = r0 < k ? diag0[min(r0, k - 1)] + sigma : 1.0;
+            Dg[(e >> 8) * kBlk + r * 17 + c] = x;
         }
         __syncthreads();
-        const double sigma = 11.0 * ((double)n_rows * k + (double)k * (k + 1)) *
-                             1.1102230246251565e-16 * trace;
-        for (int64_t i = threadIdx.x; i < kk; i += kSolveThreads)
-            A[i] = W[i] + ((i / k == i % k) ? sigma : 0.0);
+        if (w == 0) factor(0, sh);
         __syncthreads();
-        for (int i = threadIdx.x; i < k; i += kSolveThreads) diag0[i] = 0.0;
+        int nxt = 0;   // this wave's tiles before nxt are done
+        for (int jp = 0; jp < nt && !bad; ++jp) {
+            int j = jp;
+            asm volatile("" : "+s"(j), "+v"(kr), "+v"(kc));
+            if (w == 0) {
+                // diagonal block j to G (upper) and W_jj = M^T
+                const double *D = Dg + j * kBlk;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = kr + 4 * i, gr = 16 * j + r, gc = 16 * j + kc;
+                    const int off = 8 * (gr * k + gc) | out_if(gr, k) | out_if(gc, k);
+                    buf_store(gb, off | out_if(r, kc + 1), D[r * 17 + kc]);
+                    buf_store(wb, off, r <= kc ? M[kc * 17 + r] : 0.0);
+                }
+            } else {
+                double m[4], l[4];   // A operands M and R_jj^T
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    m[t] = M[kc * 17 + kr + 4 * t];
+                    l[t] = Dg[j * kBlk + (kr + 4 * t) * 17 + kc];
+                }
+#pragma unroll
+                for (int s = 0; s < MAXT; ++s) {
+                    if (TI[s] != j) continue;
+                    nxt = s + 1;
+                    const v4d T = acc[s];
+                    v4d X = (v4d){0, 0, 0, 0}, r = T;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        X = __builtin_amdgcn_mfma_f64_16x16x4f64(m[t], T[t], X, 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        r = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[t], X[t], r, 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        X = __builtin_amdgcn_mfma_f64_16x16x4f64(m[t], r[t], X, 0, 0, 0);
+                    const int c = 16 * TJ[s] + kc, out = out_if(c, k);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        P[(kr + 4 * i) * PL + c] = X[i];
+                        buf_store(gb, 8 * ((16 * j + kr + 4 * i) * k + c) | out, X[i]);
+                    }
+                }
+            }
+            __syncthreads();
+            if (j + 1 == nt) break;
+            if (w == 0) {
+                auto update = [&](int t) {
+                    double *D = Dg + t * kBlk + kr * 17 + kc;
+                    const double *row = P + kr * PL + 16 * t + kc;
+                    v4d c;
+                    double x[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        c[i] = D[4 * i * 17];
+                        x[i] = row[4 * i * PL];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        c = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[i], x[i], c, 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) D[4 * i * 17] = c[i];
+                };
+                update(j + 1);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+                __builtin_amdgcn_wave_barrier();
+                factor(j + 1, sh);
+                for (int t = j + 2; t < nt; ++t) update(t);
+            } else {
+#pragma unroll
+                for (int s = 0; s < MAXT; ++s) {
+                    if (s < nxt || TI[s] >= nt) continue;
+                    const double *row = P + kr * PL + kc;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            -row[4 * t * PL + 16 * TI[s]], row[4 * t * PL + 16 * TJ[s]], acc[s], 0,
+                            0, 0);
+                }
+            }
+            __syncthreads();
+        }
+        ok = bad == 0;
         __syncthreads();
-        ok = chol_upper(A, k, diag0);
-        sh = true;
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         if (!ok) *status = 1;
         if (sh) atomicAdd(shifted, 1);
         if (run_next) *run_next = sh ? 1 : 0;
     }
-    // R (upper; its lower triangle zero) to G
-    for (int64_t i = threadIdx.x; i < kk; i += kSolveThreads)
-        G[i] = (i / k > i % k) ? 0.0 : A[i];
-    __syncthreads();
-    // W = R^-1 (upper), in LDS for the LDS variant (A is free now); row i of
-    // R is staged in LDS for its step
-    __shared__ double rrow[kEigMaxK];   // the widest k accepted
-    double *Wm = IN_LDS ? lds_m : W;
-    for (int i = k - 1; i >= 0; --i) {
-        for (int j = i + threadIdx.x; j < k; j += kSolveThreads) rrow[j] = G[(int64_t)i * k + j];
-        __syncthreads();
-        const double rii = rrow[i];
-        for (int c = threadIdx.x; c < k; c += kSolveThreads) {
-            double x;
-            if (c < i) {
-                x = 0.0;
-            } else if (c == i) {
-                x = ok ? 1.0 / rii : 0.0;
-            } else {
-                // the products' operands four at a time (loads ahead of the
-                // still sequential sum)
-                double s = 0.0;
-                int j = i + 1;
-                for (; j + 3 <= c; j += 4) {
-                    const double r0 = rrow[j], r1 = rrow[j + 1], r2 = rrow[j + 2], r3 = rrow[j + 3];
-                    const double w0 = Wm[(int64_t)j * k + c], w1 = Wm[(int64_t)(j + 1) * k + c];
-                    const double w2 = Wm[(int64_t)(j + 2) * k + c], w3 = Wm[(int64_t)(j + 3) * k + c];
-                    s += r0 * w0;
-                    s += r1 * w1;
-                    s += r2 * w2;
-                    s += r3 * w3;
-                }
-                for (; j <= c; ++j) s += rrow[j] * Wm[(int64_t)j * k + c];
-                x = ok ? -s / rii : 0.0;
-            }
-            Wm[(int64_t)i * k + c] = x;
+    // zeros below the diagonal of R and W (W_JJ holds its own)
+    for (int r = w; r < k; r += kCholWaves)
+        for (int c = lane; c < r; c += 64) {
+            G[(int64_t)r * k + c] = 0.0;
+            if (c < (r & ~15)) W[(int64_t)r * k + c] = 0.0;
         }
-        __syncthreads();
+    if (!ok) {   // no factor: W = 0, as the status says
+        for (int i = tid; i < k * k; i += kCholThreads) W[i] = 0.0;
+        return;
     }
-    if constexpr (IN_LDS)
-        for (int64_t i = threadIdx.x; i < kk; i += kSolveThreads) W[i] = Wm[i];
+    for (int q = 0; kCholWaves * q < nt; ++q) {
+        const int J = nt - 1 - (kCholWaves * q + ((q & 1) ? kCholWaves - 1 - w : w));
+        if (J < 1) continue;
+        const int c = 16 * J + kc, co = out_if(c, k);
+        v4d last;   // W_{I+1, J}
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int r = 16 * J + kr + 4 * t;
+            last[t] = buf_d(wb, 8 * (r * k + c) | co | out_if(r, k));
+        }
+        for (int I = J - 1; I >= 0; --I) {
+            v4d S = (v4d){0, 0, 0, 0};
+            const int arow = (16 * I + kc) * k + kr;   // A operands: row 16 I + kc
+            double al[4], d[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int l = 16 * (I + 1) + 4 * t;
+                al[t] = buf_d(gb, 8 * (arow + l) | out_if(l + kr, k));
+                d[t] = buf_d(wb, 8 * (arow + 16 * I + 4 * t));
+            }
+            for (int L0 = J; L0 > I + 1; L0 -= kCholGroup) {
+                double a[kCholGroup][4], b[kCholGroup][4];
+#pragma unroll
+                for (int u = 0; u < kCholGroup; ++u) {
+                    const int L = L0 - u, gone = out_if(I + 2, L + 1);   // L <= I + 1: zeros
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int l = 16 * L + 4 * t, out = gone | out_if(l + kr, k);
+                        a[u][t] = buf_d(gb, 8 * (arow + l) | out);
+                        b[u][t] = buf_d(wb, 8 * ((l + kr) * k + c) | co | out);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kCholGroup; ++u)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        S = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][t], b[u][t], S, 0, 0, 0);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                S = __builtin_amdgcn_mfma_f64_16x16x4f64(al[t], last[t], S, 0, 0, 0);
+            last = (v4d){0, 0, 0, 0};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                last = __builtin_amdgcn_mfma_f64_16x16x4f64(-d[t], S[t], last, 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                buf_store(wb, 8 * ((16 * I + kr + 4 * t) * k + c) | co, last[t]);
+        }
+    }
 }
 
 // ---------------------------------------------------------------- eigen-solver
@@ -669,19 +868,6 @@ k_chol_inv(double *__restrict__ G, int k, double *__restrict__ W, double *__rest
 // half) and V serves as the merge's scratch before it receives the result.
 constexpr int kEigMaxLds = 144;   // largest k of the LDS variant
 constexpr int kEigSplit = 32;   // tear the tridiagonal matrix from this size on
-
-// A double moved between lanes by a DPP pattern (both halves).
-template <int CTRL>
-__device__ inline double dpp_d(double x) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-
-__device__ inline double readlane_d(double x, int l) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
-                            __builtin_amdgcn_readlane(__double2loint(x), l));
-}
 
 // Sum over a fully active wave, the same bits in every lane: pairs, quads,
 // half rows and rows by DPP (each step adds two equal sums in either order),
@@ -1515,36 +1701,23 @@ lne_status chol_inv(lne_ctx *ctx, double *G, int32_t k, double *W, int32_t *stat
                     int32_t *shifted, int64_t n_rows, const int32_t *skip, int32_t *skip_next,
                     int32_t nb) {
     if (k < 1 || k > kEigMaxK) return fail(ctx, LNE_EUNSUPPORTED, "chol_inv: k = %d", k);
-    Buf diag(ctx);
-    LNE_TRY(alloc(ctx, diag, sizeof(double) * (size_t)nb * k));
-    // the LDS variant when k^2 doubles fit beside the kernel's static arrays
-    static int lds_limit = -1;
-    if (lds_limit < 0) {
-        int dev = 0, bytes = 0, base = 0;
-        lds_limit = 0;
-        hipFuncAttributes fa;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&base, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
-                hipSuccess &&
-            hipDeviceGetAttribute(&bytes, hipDeviceAttributeSharedMemPerBlockOptin, dev) ==
-                hipSuccess &&
-            hipFuncGetAttributes(&fa, (const void *)k_chol_inv<true>) == hipSuccess &&
-            (bytes = bytes > base ? bytes : base) > (int)fa.sharedSizeBytes &&
-            hipFuncSetAttribute((const void *)k_chol_inv<true>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                bytes - (int)fa.sharedSizeBytes) == hipSuccess)
-            lds_limit = bytes - (int)fa.sharedSizeBytes;
-        (void)hipGetLastError();
-    }
-    const size_t need = sizeof(double) * (size_t)k * k;
+    const int nt = (k + 15) / 16;
+    const size_t lds = chol_lds(nt);
     {
         Launch L(ctx, "chol_inv");
-        if (k <= kCholMaxLds && need <= (size_t)lds_limit)
-            k_chol_inv<true><<<nb, kSolveThreads, need, ctx->stream>>>(
-                G, k, W, diag.as<double>(), status, shifted, n_rows, skip, skip_next);
-        else
-            k_chol_inv<false><<<nb, kSolveThreads, 0, ctx->stream>>>(
-                G, k, W, diag.as<double>(), status, shifted, n_rows, skip, skip_next);
+        // a wave holds a seventh of the nt (nt - 1) / 2 tiles above the diagonal
+#define LNE_CI(MT)                                                                           \
+    do {                                                                                     \
+        LNE_TRY(lds_opt_in(ctx, (const void *)k_chol_inv<MT>, lds));                         \
+        k_chol_inv<MT><<<nb, kCholThreads, lds, ctx->stream>>>(G, k, W, status, shifted,     \
+                                                               n_rows, skip, skip_next);     \
+    } while (0)
+        if (nt <= 4) LNE_CI(1);
+        else if (nt <= 9) LNE_CI(6);
+        else if (nt <= 13) LNE_CI(12);
+        else if (nt <= 17) LNE_CI(20);
+        else LNE_CI(22);
+#undef LNE_CI
     }
     return check_launch(ctx, "chol_inv");
 }

@@ -134,6 +134,21 @@ def test_orthonormalize(lne, ctx, dtype, k):
     assert principal_angle(Q, Yq) < {"f64": 1e-8, "f32": 1e-2, "bf16": 0.5}[dtype]
 
 
+@pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 64, 65, 144])
+def test_orthonormalize_at_tile_edges(lne, ctx, k):
+    """CholeskyQR2 gives the QR factor with a positive diagonal, so Q is unique.
+    Perturbing Y by k u |Y| (the rounding of the k-term products) moves Q by at
+    most about sqrt(2) cond(Y) k u; the bar allows 64 of those."""
+    import torch
+    n, cond = 700, 100.0
+    Y = _rand_y(n, k, seed=k, cond=cond if k > 1 else 1.0)
+    q, r = np.linalg.qr(Y)
+    q = q * np.sign(np.diag(r))
+    Yd = torch.from_numpy(Y).cuda()
+    lne.orthonormalize(ctx, Yd)
+    assert np.max(np.abs(Yd.cpu().numpy() - q)) <= 64 * cond * k * 1.1102230246251565e-16
+
+
 def test_orthonormalize_ill_conditioned_takes_shift(lne, ctx):
     import torch
     n, k = 4000, 40
