@@ -543,7 +543,8 @@ static lne_status orth_impl(lne_ctx *ctx, void *Y, int64_t n, int32_t k, int64_t
         LNE_TRY(gram(ctx, Y, dtype, n, k, ld, G.as<double>(), skip));
         LNE_TRY(chol_inv(ctx, G.as<double>(), k, W.as<double>(), f.status(), f.shifted(), n,
                          skip, next));
-        LNE_TRY(project(ctx, Y, dtype, ld, n, k, W.as<double>(), k, Y, dtype, ld, skip));
+        LNE_TRY(project(ctx, Y, dtype, ld, n, k, W.as<double>(), k, Y, dtype, ld, skip, 1, 0, 0, 0,
+                        nullptr, true));
     }
     return LNE_OK;
 }

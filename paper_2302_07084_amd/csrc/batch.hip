@@ -94,7 +94,7 @@ lne_status orth_batch(lne_ctx *ctx, float *Y, int64_t n, int k, int64_t ld, int6
         LNE_TRY(gram(ctx, Y, LNE_F32, n, k, ld, G.as<double>(), skip, nb, ys));
         LNE_TRY(chol_inv(ctx, G.as<double>(), k, W.as<double>(), fl, fl + 1, n, skip, next, nb));
         LNE_TRY(project(ctx, Y, LNE_F32, ld, n, k, W.as<double>(), k, Y, LNE_F32, ld, skip, nb, ys,
-                        (int64_t)k * k, ys));
+                        (int64_t)k * k, ys, nullptr, true));
     }
     return LNE_OK;
 }

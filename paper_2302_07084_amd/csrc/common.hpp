@@ -332,10 +332,12 @@ lne_status gram(lne_ctx *ctx, const void *Y, int32_t dtype, int64_t n, int32_t k
                 int64_t ld, double *G, const int32_t *skip, int32_t nb = 1, int64_t ys = 0,
                 double *part_ws = nullptr, size_t part_ws_bytes = 0);
 // out (n x kout, out_t) = Y (n x kin, y_t) W (kin x kout, FP64 device, ld kout).
+// tri: W is square and upper triangular and out is Y itself (only then may it
+// be: other products split the columns of a row over blocks); os is not read.
 lne_status project(lne_ctx *ctx, const void *Y, int32_t y_t, int64_t ldy, int64_t n,
                    int32_t kin, const double *W, int32_t kout, void *out, int32_t out_t,
                    int64_t ldo, const int32_t *skip, int32_t nb = 1, int64_t ys = 0,
-                   int64_t ws = 0, int64_t os = 0, void *wt_ws = nullptr);
+                   int64_t ws = 0, int64_t os = 0, void *wt_ws = nullptr, bool tri = false);
 // Workspace of project's BF16 path (W transposed to BF16).
 size_t project_bf16_ws_bytes(int32_t kin, int32_t kout, int32_t nb = 1);
 // Upper Cholesky G = R^T R in place (R in upper triangle, lower zeroed) and

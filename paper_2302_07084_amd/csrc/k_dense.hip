@@ -11,6 +11,7 @@
 // column l % 16 of the output tile, row 4 (l / 16) + i for the FP32/BF16
 // forms but row l / 16 + 4 i for the FP64 form (checked by a lane probe).
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -289,7 +290,6 @@ k_gram_reduce(const PT *__restrict__ part, int nwg, int KP, int k, double *__res
 constexpr int kProjRows = 128;
 constexpr int kProjThreads = 512;
 constexpr int kKC = 16;           // K chunk (FP64 path)
-constexpr int kAS = kKC + 1;      // padded LDS row stride (doubles)
 
 // Four consecutive elements of row `row` from column c as doubles (zero
 // beyond k or n); vec: 16-byte (FP32) or 2 x 16-byte (FP64) loads allowed.
@@ -401,12 +401,166 @@ k_proj64(const YT *__restrict__ Y, int64_t ldy, int64_t n, int kin,
     }
 }
 
+// FP64-MFMA projection Y <- Y W in place for an upper triangular W (the
+// orthonormaliser's R^-1; k x k).  Output tile J sums the 16-column chunks up
+// to J only, half the matrix steps of a full product.  A block keeps the tiles
+// of W behind its MJ output column tiles in LDS for the whole launch and its
+// eight waves walk 16-row strips of Y on their own, with no barrier between
+// them; a strip's operands come straight from memory, ahead of their use.
+// Lane group kr takes k = 4 kr + t of a chunk in step t (four consecutive
+// elements of its row); W's tiles are stored in the order the lanes read them
+// (two steps per 16-byte read, no bank conflicts).
+// Outputs that need more tiles than fit in LDS go MJ column tiles at a time,
+// the last columns first: a wave writes only rows it has read, and no group
+// reads a column that an earlier one has written.  (Splitting the columns
+// over blocks, as the full product does, lets one block overwrite what
+// another still reads.)
+// 2 10^6 x 138 FP32: 1605 us as a full product with a barrier and the waits
+// for W and Y per chunk, 1566 with half its matrix steps left out, 858 so (46
+// GFLOP in 16 x 16 x 4 steps: 68% of the matrix rate; 1 TB/s of operands each
+// way).
+constexpr int kTriThreads = 512;
+constexpr int kTriWaves = kTriThreads / 64;
+constexpr int kTriMaxTiles = 76;   // 2 KB tiles of W in LDS (152 of 160 KB)
+
+// Tiles of W behind output tiles [J0, J0 + MJ), J0 >= 0.
+constexpr int tri_tiles(int J0, int MJ) { return J0 * MJ + MJ * (MJ + 1) / 2; }
+// Tile (chunk q, output tile J0 + j), j >= q - J0.  The first columns' group
+// may start before column 0 (J0 < 0; its tiles j < -J0 are none).
+template <int MJ>
+__device__ __forceinline__ int tri_index(int q, int J0, int j) {
+    const int d = q - J0;
+    if (d <= 0) return q * MJ + j;
+    return (J0 > 0 ? J0 * MJ : 0) + d * MJ - d * (d - 1) / 2 + (j - d);
+}
+
+// Elements c .. c + 3 of a row (zero from column k on); whole: all inside,
+// and 16-byte aligned.
+template <class T>
+__device__ __forceinline__ void load4(const T *row, int c, int k, bool whole, T out[4]) {
+    if (whole) {
+        if constexpr (sizeof(T) == 4) {
+            const float4 v = *reinterpret_cast<const float4 *>(row + c);
+            out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
+        } else {
+            const double2 v0 = *reinterpret_cast<const double2 *>(row + c);
+            const double2 v1 = *reinterpret_cast<const double2 *>(row + c + 2);
+            out[0] = v0.x; out[1] = v0.y; out[2] = v1.x; out[3] = v1.y;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const T x = row[min(c + i, k - 1)];
+            out[i] = c + i < k ? x : (T)0;
+        }
+    }
+}
+
+// steps(J0 + d, u[d], d) for d = 0 .. MJ - 1 with d a constant in each.
+template <int MJ, int D = 0, class U, class F>
+__device__ __forceinline__ void tri_steps(const U &u, int J0, F &&steps) {
+    if constexpr (D < MJ) {
+        if (J0 + D >= 0) steps(J0 + D, u[D], std::integral_constant<int, D>{});
+        tri_steps<MJ, D + 1>(u, J0, steps);
+    }
+}
+
+template <class T, int MJ>
+__global__ void __launch_bounds__(kTriThreads)
+k_proj_tri(T *Y, int64_t ld, int64_t n, int k, const double *__restrict__ W,
+           const int32_t *__restrict__ skip, int64_t ys, int64_t ws, int vec) {
+    Y += (int64_t)blockIdx.y * ys;
+    W += (int64_t)blockIdx.y * ws;
+    if (skip) skip += kFlagStride * blockIdx.y;
+    if (skip && *skip == 0) return;
+    extern __shared__ __attribute__((aligned(16))) double wl[];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kr = lane >> 4, kc = lane & 15;
+    const int64_t strips = (n + 15) / 16;
+    for (int J0 = (k + 15) / 16 - MJ; J0 > -MJ; J0 -= MJ) {
+        __syncthreads();
+        for (int e = tid; e < (J0 + MJ) * MJ * 256; e += kTriThreads) {
+            const int r = (e >> 4) & 15, c = e & 15, tile = e >> 8;
+            const int q = tile / MJ, j = tile - q * MJ;
+            if (J0 + j < q) continue;
+            const int row = 16 * q + r, col = 16 * (J0 + j) + c;
+            const double x = row < k && col < k ? W[(int64_t)row * k + col] : 0.0;
+            // step t = r & 3 of lane 16 (r / 4) + c, two steps side by side
+            wl[tri_index<MJ>(q, J0, j) * 256 + ((r & 3) >> 1) * 128 + ((r >> 2) * 16 + c) * 2 +
+               (r & 1)] = x;
+        }
+        __syncthreads();
+        for (int64_t st = blockIdx.x + (int64_t)gridDim.x * w; st < strips;
+             st += (int64_t)gridDim.x * kTriWaves) {
+            const int64_t r0 = 16 * st;
+            const T *yr = Y + min(r0 + kc, n - 1) * ld;
+            v4d acc[MJ];
+#pragma unroll
+            for (int J = 0; J < MJ; ++J) acc[J] = (v4d){0, 0, 0, 0};
+            auto load = [&](int q, T (&v)[4]) {
+                load4<T>(yr, 16 * q + 4 * kr, k, vec && 16 * q + 16 <= k, v);
+            };
+            // chunk q from output tile j0 on
+            auto steps = [&](int q, const T (&v)[4], auto j0) {
+                const double *t0 = wl + tri_index<MJ>(q, J0, j0) * 256 + lane * 2;
+#pragma unroll
+                for (int J = j0; J < MJ; ++J) {
+                    const double2 b01 = *reinterpret_cast<const double2 *>(t0 + (J - j0) * 256);
+                    const double2 b23 = *reinterpret_cast<const double2 *>(t0 + (J - j0) * 256 + 128);
+                    acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[0], b01.x, acc[J], 0, 0, 0);
+                    acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[1], b01.y, acc[J], 0, 0, 0);
+                    acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[2], b23.x, acc[J], 0, 0, 0);
+                    acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[3], b23.y, acc[J], 0, 0, 0);
+                }
+                // (else the tiles of later chunks are read ahead, and spill)
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // chunks before the group's own: every tile, two chunks at a time
+            // with the next two requested first
+            if (J0 > 0) {
+                T v[2][4], vn[2][4];
+                load(0, v[0]);
+                load(min(1, J0 - 1), v[1]);
+                for (int q = 0; q < J0; q += 2) {
+                    load(min(q + 2, J0 - 1), vn[0]);
+                    load(min(q + 3, J0 - 1), vn[1]);
+                    steps(q, v[0], std::integral_constant<int, 0>{});
+                    if (q + 1 < J0) steps(q + 1, v[1], std::integral_constant<int, 0>{});
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        v[0][i] = vn[0][i];
+                        v[1][i] = vn[1][i];
+                    }
+                }
+            }
+            // the group's own chunks J0 + d: tiles d .. MJ - 1
+            T u[MJ][4];
+#pragma unroll
+            for (int d = 0; d < MJ; ++d)
+                if (J0 + d >= 0) load(J0 + d, u[d]);
+            tri_steps<MJ>(u, J0, steps);
+#pragma unroll
+            for (int J = 0; J < MJ; ++J) {
+                const int c = 16 * (J0 + J) + kc;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int64_t row = r0 + kr + 4 * i;
+                    if (row < n && c >= 0 && c < k) Y[row * ld + c] = (T)acc[J][i];
+                }
+            }
+        }
+    }
+}
+
 // BF16 projection: each lane reads its A operand (8 consecutive k of one
 // row) straight from memory with one 16-byte load; the 32-k slice of W^T is
 // staged in LDS, double-buffered: the next step's operand and W slice are
 // requested into registers before the current step's matrix-core steps and
 // the slice is stored to the other buffer after them, one barrier per step.
-template <class OT, int MAXJ>
+// TRI: W is upper triangular, and output tile J takes the steps up to its own
+// columns only (out may be Y: a wave reads its rows before it writes them).
+// The full product took 459 us at 10^6 x 266, this 390.
+template <class OT, int MAXJ, bool TRI>
 __global__ void __launch_bounds__(kProjThreads)
 k_proj_bf16(const __bf16 *__restrict__ Y, int64_t ldy, int64_t n, int kin,
             const __bf16 *__restrict__ Wt, int ldw, int kout, OT *__restrict__ out,
@@ -466,7 +620,7 @@ k_proj_bf16(const __bf16 *__restrict__ Y, int64_t ldy, int64_t n, int kin,
         }
 #pragma unroll
         for (int J = 0; J < MAXJ; ++J) {
-            if (J < ntout) {
+            if (J < ntout && (!TRI || 16 * J + 15 >= k0)) {
                 const v8bf b =
                     *reinterpret_cast<const v8bf *>(Ws[cur] + (16 * J + kc) * kTS + 8 * kr);
                 acc[J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[J], 0, 0, 0);
@@ -1634,7 +1788,9 @@ lne_status gram(lne_ctx *ctx, const void *Y, int32_t dtype, int64_t n, int32_t k
 lne_status project(lne_ctx *ctx, const void *Y, int32_t y_t, int64_t ldy, int64_t n,
                    int32_t kin, const double *W, int32_t kout, void *out, int32_t out_t,
                    int64_t ldo, const int32_t *skip, int32_t nb, int64_t ys, int64_t ws,
-                   int64_t os, void *wt_ws) {
+                   int64_t os, void *wt_ws, bool tri) {
+    if (tri && (kin != kout || out_t != y_t || out != Y || ldo != ldy))
+        return fail(ctx, LNE_EINVAL, "project: a triangular W is applied in place");
     if (kout > 288 || kin > 288) return fail(ctx, LNE_EUNSUPPORTED, "project: width above 288");
     if (nb < 1 || nb > 65535) return fail(ctx, LNE_EINVAL, "project: batch of %d", nb);
     const dim3 grid(grid_of(n > 0 ? n : 1, kProjRows), (unsigned)nb);
@@ -1653,22 +1809,63 @@ lne_status project(lne_ctx *ctx, const void *Y, int32_t y_t, int64_t ldy, int64_
         }
         LNE_TRY(check_launch(ctx, "w_to_bf16"));
         Launch L(ctx, "project");
-#define LNE_PB(OT, MJ)                                                                     \
-    k_proj_bf16<OT, MJ><<<grid, kProjThreads, 0, ctx->stream>>>(                           \
+#define LNE_PB(OT, MJ, TRI)                                                                \
+    k_proj_bf16<OT, MJ, TRI><<<grid, kProjThreads, 0, ctx->stream>>>(                      \
         (const __bf16 *)Y, ldy, n, kin, wt.as<__bf16>(), ldw, kout, (OT *)out, ldo, skip, ys, os, \
         vec)
-        if (out_t == LNE_BF16) {
-            if (ntout <= 3) LNE_PB(__bf16, 3);
-            else if (ntout <= 9) LNE_PB(__bf16, 9);
-            else LNE_PB(__bf16, 18);
+#define LNE_PBJ(OT, TRI)                                                                   \
+    do {                                                                                   \
+        if (ntout <= 3) LNE_PB(OT, 3, TRI);                                                \
+        else if (ntout <= 9) LNE_PB(OT, 9, TRI);                                           \
+        else LNE_PB(OT, 18, TRI);                                                          \
+    } while (0)
+        if (out_t == LNE_BF16 && tri) {
+            LNE_PBJ(__bf16, true);
+        } else if (out_t == LNE_BF16) {
+            LNE_PBJ(__bf16, false);
         } else if (out_t == LNE_F32) {
-            if (ntout <= 3) LNE_PB(float, 3);
-            else if (ntout <= 9) LNE_PB(float, 9);
-            else LNE_PB(float, 18);
+            LNE_PBJ(float, false);
         } else {
             return fail(ctx, LNE_EINVAL, "project: bf16 input needs bf16/f32 output");
         }
+#undef LNE_PBJ
 #undef LNE_PB
+    } else if (tri) {
+        const int vmul = y_t == LNE_F64 ? 2 : 4;
+        const int vec = ((uintptr_t)Y % 16 == 0 && ldy % vmul == 0 && ys % vmul == 0) ? 1 : 0;
+        // as many column tiles at a time as keep W's tiles in LDS, in groups
+        // of about one size; a block per CU over the batch (fewer strips of
+        // 16 rows than that: a block each)
+        int mj = std::min(ntout, 9);
+        while (mj > 1 && tri_tiles(ntout - mj, mj) > kTriMaxTiles) --mj;
+        mj = (int)ceil_div(ntout, ceil_div(ntout, mj));
+        const size_t lds = 2048 * (size_t)tri_tiles(ntout - mj, mj);
+        const int64_t strips = ceil_div(n > 0 ? n : 1, 16);
+        const dim3 tgrid((unsigned)std::min<int64_t>(strips, std::max(1, 256 / nb)), (unsigned)nb);
+        Launch L(ctx, "project");
+#define LNE_PT(T, MJ)                                                                     \
+    case MJ:                                                                              \
+        LNE_TRY(lds_opt_in(ctx, (const void *)k_proj_tri<T, MJ>, lds));                   \
+        k_proj_tri<T, MJ><<<tgrid, kTriThreads, lds, ctx->stream>>>((T *)out, ldy, n, kin, W, \
+                                                                    skip, ys, ws, vec);   \
+        break
+#define LNE_PTJ(T)                                                                        \
+    switch (mj) {                                                                         \
+        LNE_PT(T, 1);                                                                     \
+        LNE_PT(T, 2);                                                                     \
+        LNE_PT(T, 3);                                                                     \
+        LNE_PT(T, 4);                                                                     \
+        LNE_PT(T, 5);                                                                     \
+        LNE_PT(T, 6);                                                                     \
+        LNE_PT(T, 7);                                                                     \
+        LNE_PT(T, 8);                                                                     \
+        default:                                                                          \
+            LNE_PT(T, 9);                                                                 \
+    }
+        if (y_t == LNE_F64) LNE_PTJ(double)
+        else LNE_PTJ(float)
+#undef LNE_PTJ
+#undef LNE_PT
     } else {
         const int vmul = y_t == LNE_F64 ? 2 : 4;
         const int vec = ((uintptr_t)Y % 16 == 0 && ldy % vmul == 0 && ys % vmul == 0) ? 1 : 0;

@@ -149,6 +149,29 @@ def test_orthonormalize_at_tile_edges(lne, ctx, k):
     assert np.max(np.abs(Yd.cpu().numpy() - q)) <= 64 * cond * k * 1.1102230246251565e-16
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,k", [(50_003, 145), (100_000, 200), (20_001, 288)])
+def test_orthonormalize_wider_than_one_tile_group(lne, ctx, n, k, dtype):
+    """Past nine column tiles the projection writes its columns in two groups
+    over the block it reads: Q is the QR factor of Y whatever the order in
+    which the row blocks finish.  cond(Y) about 4; the bar is the rounding of
+    the stored type, amplified as in the test above."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(k)
+    Y = torch.randn(n, k, generator=g, device="cuda", dtype=torch.float64)
+    Y *= 1.0 + torch.linspace(0, 1, k, device="cuda")
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    Y = Y.to(tdt)
+    if dtype == "f32":
+        Y = torch.nn.functional.pad(Y, (0, -k % 4))[:, :k]
+    q, r = np.linalg.qr(Y.double().cpu().numpy())
+    q = q * np.sign(np.diag(r))
+    lne.orthonormalize(ctx, Y)
+    err = np.linalg.norm(Y.double().cpu().numpy() - q) / np.linalg.norm(q)
+    u = 2.0 ** -53 if dtype == "f64" else 2.0 ** -24
+    assert err <= 16 * 4 * math.sqrt(k) * u
+
+
 def test_orthonormalize_ill_conditioned_takes_shift(lne, ctx):
     import torch
     n, k = 4000, 40
