@@ -249,10 +249,15 @@ k_gram_bf16(const __bf16 *__restrict__ Y, int64_t n, int k, int64_t ld, int KP,
 }
 
 // G = sum of the per-workgroup upper partial Grams, mirrored.  A block sums
-// 64 consecutive entries (a, b), b >= a, of one row a: its four waves take
-// the workgroups w = q mod 4, two running sums each, combined in a fixed
-// order (the result does not depend on the launch).
-constexpr int kRedThreads = 256;
+// 64 consecutive entries (a, b), b >= a, of one row a: its sixteen waves take
+// the workgroups w = q mod 16, eight running sums each, combined in a fixed
+// order (the result does not depend on the launch).  Bound by latency: up to
+// 768 strided partials an entry, so as many of them in flight as possible (four
+// waves with two sums each took 32 us at k = 16 and 34 us at 138; this takes 8
+// and 16).
+constexpr int kRedThreads = 1024;
+constexpr int kRedWaves = kRedThreads / 64;
+constexpr int kRedSums = 8;
 template <class PT>
 __global__ void __launch_bounds__(kRedThreads)
 k_gram_reduce(const PT *__restrict__ part, int nwg, int KP, int k, double *__restrict__ G,
@@ -264,23 +269,32 @@ k_gram_reduce(const PT *__restrict__ part, int nwg, int KP, int k, double *__res
     const int nbc = (k + 63) / 64;
     const int a = (int)blockIdx.x / nbc, b = ((int)blockIdx.x % nbc) * 64 + (threadIdx.x & 63);
     const int q = threadIdx.x >> 6;
-    __shared__ double sums[4][64];
-    double s0 = 0.0, s1 = 0.0;
+    __shared__ double sums[kRedWaves][64];
+    double s[kRedSums];
+#pragma unroll
+    for (int u = 0; u < kRedSums; ++u) s[u] = 0.0;
     if (b >= a && b < k) {
         const PT *pa = part + (int64_t)a * KP + b;
         const int64_t step = (int64_t)KP * KP;
         int w = q;
-        for (; w + 4 < nwg; w += 8) {
-            s0 += (double)pa[w * step];
-            s1 += (double)pa[(w + 4) * step];
-        }
-        if (w < nwg) s0 += (double)pa[w * step];
+        for (; w + kRedWaves * (kRedSums - 1) < nwg; w += kRedWaves * kRedSums)
+#pragma unroll
+            for (int u = 0; u < kRedSums; ++u) s[u] += (double)pa[(w + kRedWaves * u) * step];
+#pragma unroll
+        for (int u = 0; u < kRedSums; ++u)
+            if (w + kRedWaves * u < nwg) s[u] += (double)pa[(w + kRedWaves * u) * step];
     }
-    sums[q][threadIdx.x & 63] = s0 + s1;
+#pragma unroll
+    for (int h = kRedSums / 2; h > 0; h >>= 1)
+#pragma unroll
+        for (int u = 0; u < h; ++u) s[u] += s[u + h];
+    sums[q][threadIdx.x & 63] = s[0];
     __syncthreads();
     if (q == 0 && b >= a && b < k) {
         const int l = threadIdx.x;
-        const double g = (sums[0][l] + sums[1][l]) + (sums[2][l] + sums[3][l]);
+        double g = 0.0;
+#pragma unroll
+        for (int u = 0; u < kRedWaves; ++u) g += sums[u][l];
         G[(int64_t)a * k + b] = g;
         G[(int64_t)b * k + a] = g;
     }
