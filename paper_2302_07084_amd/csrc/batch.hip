@@ -131,6 +131,8 @@ struct lne_batch {
     lne_csr ext{};
     // device workspace
     Buf om, A, B, X0, P0, P1, P2, PZ, PC, XO, tab, flags, arena;
+    Buf seg;                  // column ranges of ext's rows (make_segments)
+    int nseg = 1;
     size_t off_chan = 0, off_c0 = 0, off_one = 0, off_on = 0, off_pc = 0, tab_bytes = 0;
     int arena_for = 0;        // largest trial count the arena has been sized for
     int spmm_v = 0, gspmm_v = 0;
@@ -159,6 +161,24 @@ void drop_graph(lne_batch *b) {
     b->g_K = -1;
 }
 
+// The table of column ranges of the channel CSR, for operands of the batch's
+// own row stride.
+lne_status make_segments(lne_batch *b) {
+    b->seg.release();
+    b->nseg = chan_ranges(b->n, b->ext.nnz, b->dp);
+    if (b->nseg == 1) return LNE_OK;
+    LNE_TRY(alloc(b->ctx, b->seg, sizeof(uint32_t) * (size_t)b->n * (b->nseg + 1)));
+    return chan_segments(b->ctx, &b->ext, b->nseg, b->seg.as<uint32_t>());
+}
+
+// Y_t = M_t X_t for ntr trials; one gather for all of them when they share X.
+lne_status chan_product(lne_batch *b, int ntr, const float *X, int64_t ldx, int64_t xs, float *Y,
+                        int64_t ldy, int64_t ys, int k) {
+    const bool ranges = b->nseg > 1 && ldx == b->dp;
+    return spmm_chan(b->ctx, &b->ext, ranges ? b->seg.as<uint32_t>() : nullptr, b->nseg, xs == 0,
+                     ntr, b->chan(), X, ldx, xs, Y, ldy, ys, k, b->spmm_v);
+}
+
 // Every step after the sampling pass for trials 0..ntr-1 (coefficient table
 // already on the device), highest Chebyshev order K; no host synchronisation,
 // scratch only from the context allocator.
@@ -172,12 +192,11 @@ lne_status enqueue_trials(lne_batch *b, int ntr, int K) {
 
     // fast randomized SVD (Algorithm "Fast Randomized SVD") of every trial
     float *Q = b->A.as<float>(), *Y = b->B.as<float>();
-    LNE_TRY(spmm_chan(ctx, &b->ext, ntr, b->chan(), b->om.as<float>(), dp, 0, Y, dp, ys, dp,
-                      b->spmm_v));
+    LNE_TRY(chan_product(b, ntr, b->om.as<float>(), dp, 0, Y, dp, ys, dp));
     LNE_TRY(orth_batch(ctx, Y, n, kp, dp, ys, ntr, fl));
     std::swap(Q, Y);
     for (int it = 1; it <= b->p.q; ++it) {
-        LNE_TRY(spmm_chan(ctx, &b->ext, ntr, b->chan(), Q, dp, ys, Y, dp, ys, dp, b->spmm_v));
+        LNE_TRY(chan_product(b, ntr, Q, dp, ys, Y, dp, ys, dp));
         if (it < b->p.q) {
             LNE_TRY(orth_batch(ctx, Y, n, kp, dp, ys, ntr, fl));
             std::swap(Q, Y);
@@ -291,8 +310,8 @@ lne_status tune(lne_batch *b) {
     LNE_HIP(ctx, hipMemcpyAsync(b->pc(), pc.data(), sizeof(float) * pc.size(),
                                 hipMemcpyHostToDevice, ctx->stream));
     LNE_TRY(pick_variant(ctx, tune_key("spmm_chan", b, b->dp), kSpmmChanVariants, [&](int var) {
-        return spmm_chan(ctx, &b->ext, nt, b->chan(), b->om.as<float>(), b->dp, 0,
-                         b->B.as<float>(), b->dp, ys, b->dp, var);
+        return spmm_chan(ctx, &b->ext, nullptr, 1, false, nt, b->chan(), b->om.as<float>(), b->dp,
+                         0, b->B.as<float>(), b->dp, ys, b->dp, var);
     }, &b->spmm_v));
     LNE_TRY(pick_variant(ctx, tune_key("graph_spmm_batch", b, b->d8), kGspmmBatchVariants,
                          [&](int var) {
@@ -435,12 +454,13 @@ lne_status lne_batch_create(lne_ctx *ctx, const lne_graph *gin, const lne_params
     b->d8 = (int32_t)round8(p->d);
     b->scale = tl_scale(g, p);
     for (Buf *x : {&b->om, &b->A, &b->B, &b->X0, &b->P0, &b->P1, &b->P2, &b->PZ, &b->PC, &b->XO,
-                   &b->tab, &b->flags, &b->arena})
+                   &b->tab, &b->flags, &b->arena, &b->seg})
         x->ctx = ctx;
 
     LNE_TRY(channels_pass(ctx, g, p, &b->ext, st));
     if (st) st->nnz_counts = (uint64_t)b->ext.nnz;
     LNE_TRY(norm_channels(ctx, &b->ext, g, b->scale));
+    LNE_TRY(make_segments(b));
 
     const int64_t n = b->n, mt = max_trials;
     LNE_TRY(alloc(ctx, b->om, sizeof(float) * (size_t)n * b->dp));
@@ -571,6 +591,7 @@ lne_status lne_batch_resample(lne_batch *b, const double *pi, lne_stats *st) {
     LNE_TRY(channels_pass(ctx, &b->g, &b->p, &b->ext, st));
     if (st) st->nnz_counts = (uint64_t)b->ext.nnz;
     LNE_TRY(norm_channels(ctx, &b->ext, &b->g, b->scale));
+    LNE_TRY(make_segments(b));
     LNE_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return LNE_OK;
 }
@@ -593,7 +614,7 @@ lne_status lne_batch_spmm(lne_batch *b, const lne_trial *trials, int32_t n_trial
     (void)fill_table(b, trials, n_trials);
     LNE_HIP(ctx, hipMemcpyAsync(b->tab.p, b->host_tab.data(), b->tab_bytes, hipMemcpyHostToDevice,
                                 ctx->stream));
-    LNE_TRY(spmm_chan(ctx, &b->ext, n_trials, b->chan(), X, ldx, xs, Y, ldy, ys, k, b->spmm_v));
+    LNE_TRY(chan_product(b, n_trials, X, ldx, xs, Y, ldy, ys, k));
     LNE_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return LNE_OK;
 }

@@ -373,14 +373,28 @@ lne_status trial_values(lne_ctx *ctx, const Graph *g, const lne_csr *st, const u
 // Channel CSR weights in place: counts W_r -> FP64 scale W_r / (d_a d_b)
 // (val_type becomes LNE_F64).
 lne_status norm_channels(lne_ctx *ctx, lne_csr *ext, const Graph *g, double scale);
-// Y_t (rows ldy apart, trials ys apart) = M_t X_t (ldx, xs; xs = 0 shares one
+// Y_t (rows ldy apart, trials ys apart) = M_t X_t (ldx, xs; xs = 0: one
 // operand) for ntr trials, M_t generated from the normalised channel CSR
 // `ext` with coef[16 t + r - 1] = s_t[r] / pi_r; k <= 256, k % 4 == 0, X's columns
-// up to k zero-padded.  variant: launch shape 0..5.
-lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, int ntr, const double *coef,
-                     const float *X, int64_t ldx, int64_t xs, float *Y, int64_t ldy, int64_t ys,
-                     int k, int variant);
+// up to k zero-padded, ldx < 2^32.  seg: its nseg column ranges
+// (chan_segments), taken one after the other, or NULL for whole rows.
+// shared: gather an operand's row once for several trials (xs = 0).
+// variant: launch shape 0..5 of whole rows with an operand each; the result
+// is the same in every way of these.
+lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int nseg, bool shared,
+                     int ntr, const double *coef, const float *X, int64_t ldx, int64_t xs,
+                     float *Y, int64_t ldy, int64_t ys, int k, int variant);
 constexpr int kSpmmChanVariants = 6;
+// Column ranges of that product: chan_ranges(n, nnz, ldx) of them for an
+// operand of n rows of ldx floats, as many as bring a range's rows of X down
+// to kChanRangeBytes (of an XCD's 4 MB of L2: 1.5, 2.5, 3 and 4 MB measured
+// 69, 65, 65 and 79 ms at 2 10^8 entries, n = 10^5, eight trials) -- or 1 when
+// rows have fewer than kChanMinRun entries a range on average, so that a range
+// would not fill half a wave's step.
+constexpr int64_t kChanRangeBytes = 5ll << 19;
+constexpr int64_t kChanMinRun = 32;
+int chan_ranges(int64_t n, int64_t nnz, int64_t ldx);
+lne_status chan_segments(lne_ctx *ctx, const lne_csr *ext, int nseg, uint32_t *seg);
 // Propagation step for ntr trials (blocks zs apart, rows ld apart, k columns):
 // out = a Z + b D^-1 A Z + c1 E1 + c2 E2, acc += e out, coef[5 t + {a, b, c1,
 // c2, e}]; E1, E2, acc may be NULL.  variant: launch shape 0..3.

@@ -14,6 +14,8 @@
 // one launch per step (batched Gram, Cholesky, eigen-solves and projections,
 // one channel SpMM over every (trial, row) pair, one graph SpMM per
 // propagation step with per-trial epilogue coefficients).
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace lne {
@@ -109,47 +111,76 @@ __global__ void k_norm_chan(const int64_t *__restrict__ rp, const int32_t *__res
     }
 }
 
+// ---- channel SpMM -------------------------------------------------------------
 // Y_t = M_t X_t for trials t = 0..ntr-1 with M_t generated on the fly from
 // the normalised channel CSR: every (row a, column b) structure entry is a
 // run of channel entries with the same b (ascending r); a segmented scan over
 // the wave sums x = sum_r coef_t[r] w_r with coef_t[r] = s_t[r] / pi_r (FP64,
 // so the x > 1 decision is taken in FP64; a run crossing a 64-entry chunk
 // carries its partial sum), and the lane holding the run's last entry forms
-// the truncated logarithm ln x (FP32; 0 if x <= 1).  The nonzero values of a
-// 64-entry chunk are compacted to the low lanes with one ds_permute, then the
-// wave gathers the X rows of those entries, U rows in flight per lane, lane l
-// holding columns 4l..4l+3 (k <= 256, k % 4 == 0, padding columns of X zero).
-// TM: waves enumerate (trial, row) trial-major (consecutive waves share a
-// trial's operand) or row-major (consecutive waves share a row's entries).
-template <int U, bool TM>
+// the truncated logarithm ln x (FP32; 0 if x <= 1).  Then the wave gathers the
+// X rows of the chunk's nonzero values, in column order, U rows in flight,
+// lane l holding VW columns (k <= 256; padding columns of X zero).
+//
+// seg: the columns are cut into ranges whose X rows fit one XCD's L2 beside
+// the stream of entries (chan_ranges); each launch adds range sg's entries to
+// Y, and a row's range is found in a table of offsets (k_chan_segments).
+// Every row still takes its entries in column order, its running sums carried
+// through Y between the launches (FP32 both ways), so that the ranges do not
+// change the result.
+//   TB = 1: wave (trial, row), trial-major (TM: consecutive waves share a
+//   trial's operand) or row-major (they share a row's entries).
+//   TB > 1: wave = row, TB trials of one shared operand: an X row is gathered
+//   once for all of them (a trial that drops the entry adds nothing).
+// 2 10^8 entries, n = 10^5, 144 columns, eight trials: each trial's own operand
+// 132 ms by whole rows with four columns a lane (bound by memory-side lines),
+// 50 by ranges of 2.5 MB; one operand for all 70 ms with a gather each, 24
+// with one.  Bound by instruction issue then: a lane holds the fewest columns
+// that 64 lanes cover k with (48 lanes of three at k = 144, not 36 of four),
+// the kept entries are found by scalar bit operations and their rows addressed
+// by scalars, and the scan stops at the chunk's longest run (seen in the bits
+// of the run heads).
+template <int VW> struct FVec { float v[VW]; };
+
+template <int TB, int VW, int U, bool TM>
 __global__ void __launch_bounds__(256)
-k_spmm_chan(const int64_t *__restrict__ rp, const int32_t *__restrict__ ecol,
-            const double *__restrict__ wn, int64_t n, int ntr,
-            const double *__restrict__ coef, const float *__restrict__ X,
-            int64_t ldx, int64_t xs, float *__restrict__ Y, int64_t ldy, int64_t ys, int k) {
-    const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (w >= n * ntr) return;
-    int64_t row;
-    int t;
-    if (TM) {
-        t = (int)(w / n);
-        row = w - (int64_t)t * n;
-    } else {
-        row = w / ntr;
-        t = (int)(w - row * ntr);
-    }
+k_chan_seg(const int64_t *__restrict__ rp, const uint32_t *__restrict__ seg, int nseg, int sg,
+           const int32_t *__restrict__ ecol, const double *__restrict__ wn, int64_t n, int ntr,
+           const double *__restrict__ coef, const float *__restrict__ X, int64_t ldx, int64_t xs,
+           float *__restrict__ Y, int64_t ldy, int64_t ys, int k, int first) {
+    static_assert(TB == 1 || TM, "shared operands: a wave per row");
+    const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t groups = (ntr + TB - 1) / TB;
+    if (w >= n * groups) return;
+    const int64_t tg = TM ? w / n : w % ntr, row = TM ? w - tg * n : w / ntr;
+    const int t0 = (int)tg * TB;
     const int lane = threadIdx.x & 63;
-    const int c0 = lane * 4;
+    const int c0 = lane * VW;
     const bool act = c0 < k;
-    X += (int64_t)t * xs;
-    Y += (int64_t)t * ys;
-    coef += 16 * t;
-    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    const int64_t beg = rp[row], end = rp[row + 1];
+    // row j at j * ldx (scalar), the lane's columns behind it (idle lanes read
+    // the row's first)
+    X += (int64_t)t0 * xs;
+    const uint32_t ldw = (uint32_t)ldx, xo = act ? 4 * c0 : 0;
+    Y += (int64_t)t0 * ys + row * ldy + c0;
+    coef += 16 * t0;
+    int64_t beg = rp[row], end = rp[row + 1];
+    if (seg) {
+        end = beg + seg[row * (nseg + 1) + sg + 1];
+        beg += seg[row * (nseg + 1) + sg];
+    }
+    if (beg == end && !first) return;
+    using V = FVec<VW>;
+    V acc[TB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+        acc[t] = V{};
+        if (!first && act && t0 + t < ntr) acc[t] = *reinterpret_cast<const V *>(Y + t * ys);
+    }
     const uint64_t upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);   // lanes 0..lane
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    int32_t prev_b = -1;     // base column of the entry before the chunk
-    double carry = 0.0;      // partial sum of the run that reaches into the chunk
+    int32_t prev_b = -1;      // base column of the entry before the chunk
+    double carry[TB];         // partial sum of the run that reaches into the chunk
+#pragma unroll
+    for (int t = 0; t < TB; ++t) carry[t] = 0.0;
     // the next chunk's structure is loaded while the current one is gathered
     int32_t ec_next = beg + lane < end ? ecol[beg + lane] : -16;
     double w_next = beg + lane < end ? wn[beg + lane] : 0.0;
@@ -161,63 +192,112 @@ k_spmm_chan(const int64_t *__restrict__ rp, const int32_t *__restrict__ ecol,
         ec_next = i + 64 < end ? ecol[i + 64] : -16;
         w_next = i + 64 < end ? wn[i + 64] : 0.0;
         const int32_t jb = ec >> 4;
-        const double cw = valid ? coef[ec & 15] * wv : 0.0;
         const int32_t up_b = __shfl_up(jb, 1, 64);
         const bool head = valid && (lane == 0 ? prev_b : up_b) != jb;
         const uint64_t hm = __ballot(head);
-        // segmented inclusive scan: a lane adds the partial of lane - off when
-        // no run starts in (lane - off, lane]; a run holds at most one entry
-        // per length (<= 16), so four doubling steps cover it
-        double sum = cw;
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-            const double o = __shfl_up(sum, off, 64);
-            const int src = lane - off;
-            const uint64_t below = src < 0 ? 0ull : (src == 63 ? ~0ull : ((2ull << src) - 1));
-            if (src >= 0 && (hm & upto & ~below) == 0) sum += o;
-        }
-        if (valid && (hm & upto) == 0) sum += carry;    // the run carried into the chunk
+        // longest run of the chunk: more than off entries iff off neighbouring
+        // lanes are not heads
+        const uint64_t nh = ~hm & __ballot(valid);
         const int32_t dn_b = __shfl_down(jb, 1, 64);
-        const int32_t first_next = __shfl(ec_next, 0, 64) >> 4;
-        int32_t nb = dn_b;
-        if (lane == 63) nb = b0 + 64 < end ? first_next : -2;
+        const int32_t first_next = __builtin_amdgcn_readfirstlane(ec_next) >> 4;
+        const int32_t nb = lane == 63 ? (b0 + 64 < end ? first_next : -2) : dn_b;
         const bool last = valid && (i + 1 >= end || nb != jb);
-        float v = 0.f;
-        if (last) v = sum > 1.0 ? logf((float)sum) : 0.f;
-        carry = __shfl(sum, 63, 64);
-        prev_b = __shfl(jb, 63, 64);
-        const bool take = v != 0.f;
-        const uint64_t mask = __ballot(take);
-        const int cnt = __popcll(mask);
-        // a permutation of the 64 lanes: kept entries first, in order
-        const int dst = take ? __popcll(mask & lt) : cnt + __popcll(~mask & lt);
-        const int jc = __builtin_amdgcn_ds_permute(dst << 2, jb);
-        const float vc = __int_as_float(__builtin_amdgcn_ds_permute(dst << 2, __float_as_int(v)));
-        for (int t0 = 0; t0 < cnt; t0 += U) {
-            int32_t j[U];
-            float vv[U];
-            float4 x[U];
+        const bool open = valid && (hm & upto) == 0;    // in the run carried into the chunk
+        float v[TB];
+        uint64_t any = 0, all = ~0ull;   // entries that some trial keeps, that all do
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
-                j[q] = __shfl(jc, (t0 + q) & 63, 64);
-                vv[q] = __shfl(vc, (t0 + q) & 63, 64);
+        for (int t = 0; t < TB; ++t) {
+            double sum = valid && t0 + t < ntr ? coef[16 * t + (ec & 15)] * wv : 0.0;
+            // segmented inclusive scan: a lane adds the partial of lane - off
+            // when no run starts in (lane - off, lane]; a run holds at most
+            // one entry per length (<= 16), so four doubling steps cover it
+            uint64_t more = nh;
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) {
+                if (more == 0) break;
+                const double o = __shfl_up(sum, off, 64);
+                const int src = lane - off;
+                const uint64_t below = src < 0 ? 0ull : (src == 63 ? ~0ull : ((2ull << src) - 1));
+                if (src >= 0 && (hm & upto & ~below) == 0) sum += o;
+                more &= more >> off;
             }
-#pragma unroll
-            for (int q = 0; q < U; ++q)
-                x[q] = (act && t0 + q < cnt)
-                           ? *reinterpret_cast<const float4 *>(X + (int64_t)j[q] * ldx + c0)
-                           : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const float f = t0 + q < cnt ? vv[q] : 0.f;
-                acc.x += f * x[q].x;
-                acc.y += f * x[q].y;
-                acc.z += f * x[q].z;
-                acc.w += f * x[q].w;
-            }
+            if (open) sum += carry[t];
+            v[t] = 0.f;
+            if (last) v[t] = sum > 1.0 ? logf((float)sum) : 0.f;
+            carry[t] = __shfl(sum, 63, 64);
+            const uint64_t kept = __ballot(v[t] != 0.f);
+            any |= kept;
+            if (t0 + t < ntr) all &= kept;
         }
+        prev_b = __builtin_amdgcn_readlane(jb, 63);
+        // the kept entries in order, U rows in flight
+        auto pop = [&](auto count) {
+            int l[count];
+            uint64_t group = 0;
+#pragma unroll
+            for (int q = 0; q < count; ++q) {
+                l[q] = __builtin_ctzll(any);
+                group |= 1ull << l[q];
+                any &= ~(1ull << l[q]);
+            }
+            V x[count];
+#pragma unroll
+            for (int q = 0; q < count; ++q)
+                x[q] = *reinterpret_cast<const V *>(
+                    reinterpret_cast<const char *>(
+                        X + (uint64_t)(uint32_t)__builtin_amdgcn_readlane(jb, l[q]) * ldw) + xo);
+            auto add = [&](auto every) {
+#pragma unroll
+                for (int q = 0; q < count; ++q)
+#pragma unroll
+                    for (int t = 0; t < TB; ++t) {
+                        const float f =
+                            __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[t]), l[q]));
+                        if (!every && f == 0.f) continue;
+#pragma unroll
+                        for (int i = 0; i < VW; ++i) acc[t].v[i] += f * x[q].v[i];
+                    }
+            };
+            // an entry that only some trials keep adds 0 times its row to the
+            // others, which is nothing unless the row is infinite or undefined
+            bool exact = TB == 1 || (group & ~all) == 0;
+            if (!exact) {
+                float z = 0.f;
+#pragma unroll
+                for (int q = 0; q < count; ++q)
+#pragma unroll
+                    for (int i = 0; i < VW; ++i) z = fmaf(x[q].v[i], 0.f, z);
+                exact = __ballot(z != 0.f) == 0;
+            }
+            if (exact) add(std::true_type{});
+            else add(std::false_type{});
+        };
+        int left = __popcll(any);
+        for (; left >= U; left -= U) pop(std::integral_constant<int, U>{});
+        if constexpr (U > 4) if (left & 4) pop(std::integral_constant<int, 4>{});
+        if constexpr (U > 2) if (left & 2) pop(std::integral_constant<int, 2>{});
+        if (left & 1) pop(std::integral_constant<int, 1>{});
     }
-    if (act) *reinterpret_cast<float4 *>(Y + row * ldy + c0) = acc;
+    if (!act) return;
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+        if (t0 + t < ntr) *reinterpret_cast<V *>(Y + t * ys) = acc[t];
+}
+
+// seg[row * (nseg + 1) + s] = entries of the row (from its first) with base
+// column below s * width, s = 0 .. nseg.
+__global__ void k_chan_segments(const int64_t *__restrict__ rp, const int32_t *__restrict__ ecol,
+                                int64_t n, int nseg, int64_t width, uint32_t *__restrict__ seg) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n * (nseg + 1)) return;
+    const int64_t row = i / (nseg + 1), s = i - row * (nseg + 1);
+    const int64_t beg = rp[row];
+    int64_t lo = beg, hi = rp[row + 1];
+    while (lo < hi) {
+        const int64_t mid = lo + ((hi - lo) >> 1);
+        if ((ecol[mid] >> 4) < s * width) lo = mid + 1; else hi = mid;
+    }
+    seg[i] = (uint32_t)(lo - beg);
 }
 
 // Propagation step of every trial: out_t = a_t Z_t + b_t D^-1 A Z_t + c1_t E1_t
@@ -377,33 +457,64 @@ lne_status norm_channels(lne_ctx *ctx, lne_csr *ext, const Graph *g, double scal
     return LNE_OK;
 }
 
-lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, int ntr, const double *coef,
-                     const float *X, int64_t ldx, int64_t xs, float *Y, int64_t ldy, int64_t ys,
-                     int k, int variant) {
+int chan_ranges(int64_t n, int64_t nnz, int64_t ldx) {
+    const int64_t bytes = n * ldx * (int64_t)sizeof(float);
+    const int64_t ranges = ceil_div(bytes, kChanRangeBytes);
+    if (n == 0 || ranges < 2 || ranges > 4096 || nnz >= n * (int64_t)UINT32_MAX) return 1;
+    return nnz / (n * ranges) >= kChanMinRun ? (int)ranges : 1;
+}
+
+lne_status chan_segments(lne_ctx *ctx, const lne_csr *ext, int nseg, uint32_t *seg) {
+    const int64_t n = ext->n_rows;
+    if (n == 0) return LNE_OK;
+    {
+        Launch L(ctx, "chan_segments");
+        k_chan_segments<<<grid_of(n * (nseg + 1), 256), 256, 0, ctx->stream>>>(
+            ext->row_ptr, ext->col, n, nseg, ceil_div(n, nseg), seg);
+    }
+    return check_launch(ctx, "chan_segments");
+}
+
+lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int nseg, bool shared,
+                     int ntr, const double *coef, const float *X, int64_t ldx, int64_t xs,
+                     float *Y, int64_t ldy, int64_t ys, int k, int variant) {
     if (ext->val_type != LNE_F64)
         return fail(ctx, LNE_EINVAL, "spmm_chan: channel weights must be normalised");
     if (k % 4 || k > 256 || ldx % 4 || ldy % 4 || xs % 4 || ys % 4 || (uintptr_t)X % 16 ||
         (uintptr_t)Y % 16)
         return fail(ctx, LNE_EINVAL, "spmm_chan: k <= 256, k %% 4 == 0 and 16-byte aligned rows");
+    if (ldx >= (int64_t)1 << 32 || (shared && xs != 0) || variant < 0 ||
+        variant >= kSpmmChanVariants)
+        return fail(ctx, LNE_EINVAL, "spmm_chan: ldx, a shared operand's stride or variant %d",
+                    variant);
     const int64_t n = ext->n_rows;
     if (n == 0 || ntr == 0) return LNE_OK;
-    const unsigned grid = grid_of(n * ntr * 64, 256);
-    {
+    if (!seg) nseg = 1;
+    const int tb = !shared || ntr == 1 ? 1 : ntr <= 2 ? 2 : ntr <= 4 ? 4 : 8;
+    for (int s = 0; s < nseg; ++s) {
         Launch L(ctx, "spmm_chan");
-#define LNE_SC(UU, TMM)                                                                   \
-    k_spmm_chan<UU, TMM><<<grid, 256, 0, ctx->stream>>>(ext->row_ptr, ext->col,           \
-                                                        (const double *)ext->val, n, ntr, \
-                                                        coef, X, ldx, xs, Y, ldy, ys, k)
-        switch (variant) {
-            case 0: LNE_SC(4, true); break;
-            case 1: LNE_SC(2, true); break;
-            case 2: LNE_SC(8, true); break;
-            case 3: LNE_SC(4, false); break;
-            case 4: LNE_SC(2, false); break;
-            case 5: LNE_SC(8, false); break;
-            default: return fail(ctx, LNE_EINVAL, "spmm_chan: variant %d", variant);
-        }
-#undef LNE_SC
+#define LNE_CS(TB, VW, U, TM)                                                               \
+    k_chan_seg<TB, VW, U, TM><<<grid_of(n * ceil_div(ntr, TB), 4), 256, 0, ctx->stream>>>(  \
+        ext->row_ptr, seg, nseg, s, ext->col, (const double *)ext->val, n, ntr, coef, X, ldx, xs, \
+        Y, ldy, ys, k, s == 0 ? 1 : 0)
+#define LNE_CV(VW)                                                                          \
+    do {                                                                                    \
+        if (tb == 2) LNE_CS(2, VW, 4, true);                                                \
+        else if (tb == 4) LNE_CS(4, VW, 4, true);                                           \
+        else if (tb == 8) LNE_CS(8, VW, 4, true);                                           \
+        else if (seg || variant == 0) LNE_CS(1, VW, 4, true);                               \
+        else if (variant == 1) LNE_CS(1, VW, 2, true);                                      \
+        else if (variant == 2) LNE_CS(1, VW, 8, true);                                      \
+        else if (variant == 3) LNE_CS(1, VW, 4, false);                                     \
+        else if (variant == 4) LNE_CS(1, VW, 2, false);                                     \
+        else LNE_CS(1, VW, 8, false);                                                       \
+    } while (0)
+        if (k <= 64) LNE_CV(1);
+        else if (k <= 128) LNE_CV(2);
+        else if (k <= 192 && k % 3 == 0) LNE_CV(3);
+        else LNE_CV(4);
+#undef LNE_CV
+#undef LNE_CS
     }
     return check_launch(ctx, "spmm_chan");
 }

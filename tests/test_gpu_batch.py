@@ -108,6 +108,45 @@ def test_batch_spmm_matches_oracle(lne, ctx):
     B.close()
 
 
+@pytest.mark.parametrize("ntr", [1, 2, 9])
+def test_batch_spmm_by_column_ranges(lne, ctx, ntr):
+    """An operand wider than one cache-sized range of columns (6,000 rows of
+    144 floats: two ranges) against the oracle's trial matrices and against the
+    same columns as a narrower operand, which is taken in one piece: each
+    column's sum is the same chain either way, so the two agree bit for bit.
+    Shared operands go through groups of up to eight trials; a row that one
+    trial drops everywhere does not reach it, infinite or not."""
+    import torch
+    g = sbm([300] * 20, 0.03, 0.0008, seed=8)
+    p = gs.params(T=4, M_per_m=60, C=math.log(g.n), m=g.m, seed=3, d=134, oversample=10,
+                  precision="f32")
+    rp, col = to_dev(g)
+    R0, C0, W0, _, _ = oracle.count_csr(g, p, channels=True)
+    assert len(C0) >= 2 * 32 * g.n and g.n * 144 * 4 > 5 << 19
+    trials = trial_vectors(ntr, seed=4, T=4)
+    trials[0]["s"] = np.array([1.0, 0, 0, 0])     # one length only: drops most entries
+    B = lne.Batch(ctx, rp, col, p, max_trials=9)
+    rng = np.random.default_rng(0)
+    X = rng.standard_normal((ntr, g.n, 144)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    Y = B.spmm(trials, Xd)
+    assert torch.equal(Y[..., :132], B.spmm(trials, Xd[..., :132].contiguous()))
+    S = B.spmm(trials, Xd[0].contiguous())
+    assert torch.equal(S[0], Y[0])
+    for t in range(0, ntr, 4):
+        M = oracle.trial_matrix(g, p, R0, C0, W0, trials[t]["s"])
+        ref = M @ X[t].astype(np.float64)
+        assert np.all(np.abs(Y[t].cpu().numpy() - ref) <= _spmm_bar(M, X[t].astype(np.float64)))
+    M = oracle.trial_matrix(g, p, R0, C0, W0, trials[0]["s"])
+    Xi = Xd[0].clone()
+    Xi[17] = float("inf")
+    hit = np.asarray((M != 0).tocsc()[:, 17].todense())[:, 0]
+    assert hit.any() and not hit.all()
+    Si = B.spmm(trials, Xi)[0].cpu().numpy()
+    assert np.array_equal(np.isfinite(Si).all(axis=1), ~hit)
+    B.close()
+
+
 def _single_trial_reference(lne, ctx, rp, col, p, ch, tr):
     M = lne.trial_matrix(ctx, rp, col, p, ch, tr)
     pt = dict(p, s=tr["s"], cheb_k=tr["k"], theta=tr["theta"], mu=tr["mu"])
