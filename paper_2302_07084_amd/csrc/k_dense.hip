@@ -1006,8 +1006,8 @@ k_chol_inv(double *Gb, int k, double *Wb, int32_t *__restrict__ status,
 }
 
 // ---------------------------------------------------------------- eigen-solver
-// Symmetric eigen-decomposition of a k x k matrix by one workgroup, in three
-// phases (Householder reduction to tridiagonal form, the tridiagonal
+// Symmetric eigen-decomposition of a k x k matrix, in three phases, the first
+// two by one workgroup (Householder reduction to tridiagonal form, the tridiagonal
 // eigen-problem, the reflectors applied to its eigenvectors):
 //  1. k - 2 Householder steps.  Step j reflects the entries of column j below
 //     the subdiagonal to zero: with x = A[j+1.., j], beta = -sign(x0) |x|,
@@ -1025,17 +1025,28 @@ k_chol_inv(double *Gb, int k, double *Wb, int32_t *__restrict__ status,
 //     matrix is first torn in two halves plus a rank-one term (Cuppen), the
 //     halves are swept side by side by two waves, and a merge solves the
 //     rank-one problem (its comment gives the steps).
-//  3. Every wave takes whole eigenvectors (in registers) and applies the
-//     reflectors k-3 .. 0 to them without block barriers, then writes them to
-//     V in order of decreasing eigenvalue.
-// IN_LDS: A (and then the reflectors) lives in LDS (k^2 doubles of dynamic
-// shared memory); otherwise it is worked on in place in global memory.  The
-// eigenvectors of the tridiagonal matrix are kept transposed in Zt (row i =
-// eigenvector i), so a rotation of eigenvectors (i, i+1) reads two rows; the
-// workspace Zt holds 2 k^2 doubles (the merge writes its rows to the second
-// half) and V serves as the merge's scratch before it receives the result.
+//  3. k_eig_back multiplies the halves' eigenvectors by the rank-one
+//     problem's and applies the reflectors.
+// IN_LDS: A lives in LDS (k^2 doubles of dynamic shared memory) during phase
+// 1; otherwise it is worked on in place in global memory.  The eigenvectors of
+// the tridiagonal matrix are kept transposed in Zt (row i = eigenvector i), so
+// a rotation of eigenvectors (i, i+1) reads two rows.
 constexpr int kEigMaxLds = 144;   // largest k of the LDS variant
 constexpr int kEigSplit = 32;   // tear the tridiagonal matrix from this size on
+
+// What k_sym_eig hands to k_eig_back: rows of eigenvectors of the tridiagonal
+// matrix (or of its halves), the rank-one problem's eigenvectors (U, K x K,
+// rows k apart), the eigenvalues, the reflectors' factors, the rows of Zt the
+// columns of the result are built from, and K.
+struct EigWs {
+    double *Zt, *U, *eig, *tau;
+    int32_t *kept, *K;
+};
+__host__ __device__ constexpr int64_t eig_ws_one(int64_t k) { return 2 * k * k + 3 * k + 1; }
+__device__ __forceinline__ EigWs eig_ws(double *ws, int k, int64_t batch) {
+    double *p = ws + batch * eig_ws_one(k), *q = p + 2 * (int64_t)k * k;
+    return {p, p + (int64_t)k * k, q, q + k, (int32_t *)(q + 2 * k), (int32_t *)(q + 3 * k)};
+}
 
 // Sum over a fully active wave, the same bits in every lane: pairs, quads,
 // half rows and rows by DPP (each step adds two equal sums in either order),
@@ -1181,8 +1192,7 @@ __device__ bool ql_sweep(double *d, double *e, int k, QlState &st, double *rc, d
 
 template <bool IN_LDS>
 __global__ void __launch_bounds__(kSolveThreads)
-k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ Zt, double *__restrict__ V,
-          double *__restrict__ lam) {
+k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
     constexpr int MK = IN_LDS ? kEigMaxLds : kEigMaxK;
     extern __shared__ double lds_a[];
     __shared__ double dg[MK], eg[MK], taus[MK];
@@ -1191,17 +1201,12 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ Zt, double *__res
     __shared__ int idx[2 * MK];                             // merge: order, kept and deflated rows
     __shared__ double s_rho, s_unit, s_tol;
     __shared__ int s_K, s_flip;
-    {
-        const int64_t b = blockIdx.x;
-        Ag += b * k * k;
-        Zt += b * 2 * k * k;
-        V += b * k * k;
-        lam += b * k;
-    }
+    Ag += (int64_t)blockIdx.x * k * k;
+    const EigWs out = eig_ws(ws, k, blockIdx.x);
+    double *__restrict__ Zt = out.Zt;
     // the wave index as a scalar, so that code under `w == 0` branches as a
     // uniform wave
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int NW = kSolveThreads / 64;
     double *__restrict__ A = Ag;
     if constexpr (IN_LDS) {
         for (int64_t i = tid; i < (int64_t)k * k; i += kSolveThreads) lds_a[i] = Ag[i];
@@ -1282,9 +1287,14 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ Zt, double *__res
         for (int j = (k >= 2 ? k - 2 : 0); j < k; ++j) dg[j] = A[(int64_t)j * k + j];
         if (k >= 2) eg[k - 2] = A[(int64_t)(k - 2) * k + k - 1];
         eg[k - 1] = 0.0;
+        taus[k - 1] = 0.0;
+        if (k >= 2) taus[k - 2] = 0.0;
         s_more[0][0] = s_more[0][1] = s_more[1][0] = s_more[1][1] = 0;
     }
     __syncthreads();
+    for (int i = tid; i < k; i += kSolveThreads) out.tau[i] = taus[i];
+    if constexpr (IN_LDS)
+        for (int64_t i = tid; i < (int64_t)k * k; i += kSolveThreads) Ag[i] = lds_a[i];
 
     // ---- 2. eigen-decomposition of the tridiagonal matrix T = (d, e).
     // Wave 0 scales (d, e) by a power of two to unit size (exact).  For
@@ -1365,9 +1375,12 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ Zt, double *__res
             if (!s_more[0][b] && !s_more[1][b]) break;
         }
     }
-    const double *Zv = Zt;   // the eigenvector rows phase 3 starts from
     if (np == 1) {
-        for (int i = tid; i < k; i += kSolveThreads) dg[i] /= s_unit;
+        for (int i = tid; i < k; i += kSolveThreads) {
+            out.eig[i] = dg[i] / s_unit;
+            out.kept[i] = i;
+        }
+        if (tid == 0) *out.K = 0;
     } else {
         // ---- merge: eigenvalues and eigenvectors of D + rho z z^T, D the
         // eigenvalues of T1 and T2, z the rows h-1 / h of their eigenvectors.
@@ -1375,12 +1388,10 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ Zt, double *__res
         // leaves a negligible coupling), then per root a bisection of the
         // secular equation 1 + rho sum z_i^2 / (d_i - lambda) = 0 in its
         // interval between poles (its distance to the nearer pole kept as
-        // (origin, tau) so that differences stay accurate), weights
+        // (origin, tau) so that differences stay accurate), and weights
         // recomputed from the roots (Gu and Eisenstat) so that the
-        // eigenvectors z_i / (d_i - lambda_j) come out orthogonal, and the
-        // new rows Zt2 = U Zt[kept] (U in V as scratch).
-        double *Zt2 = Zt + (int64_t)k * k;
-        double *Ut = V;
+        // eigenvectors z_i / (d_i - lambda_j) come out orthogonal (column j
+        // of U; k_eig_back multiplies).
         int *ord = idx, *kept = idx + MK;
         double *dk = buf, *zk = buf + MK, *tau = buf + 2 * MK, *zh = buf + 3 * MK;
         for (int i = tid; i < k; i += kSolveThreads)
@@ -1551,118 +1562,201 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ Zt, double *__res
                     nrm += u * u;
                 }
                 const double inv = 1.0 / sqrt(nrm);
-                for (int i = 0; i < K; ++i) Ut[(int64_t)j * K + i] = zh[i] / ((dk[i] - dj) - tj) * inv;
+                for (int i = 0; i < K; ++i)
+                    out.U[(int64_t)i * k + j] = zh[i] / ((dk[i] - dj) - tj) * inv;
             }
-            __syncthreads();
-            // zk is free now: the final eigenvalues
-            for (int j = tid; j < k; j += kSolveThreads)
-                zk[j] = sgn * (j < K ? dk[ord[j]] + tau[j] : dg[kept[j]]) / un;
-        }
-        __syncthreads();
-        for (int j = tid; j < k; j += kSolveThreads) dg[j] = zk[j];
-        // new rows: Zt2[j] = sum_i Ut[j][i] Zt[kept_i] (j < K); the deflated
-        // rows are copied.  4 x 4 output tiles per thread.
-        {
-            const int nt4 = (k + 3) / 4;
-            for (int tt = tid; tt < nt4 * nt4; tt += kSolveThreads) {
-                const int j0 = (tt / nt4) * 4, c0 = (tt % nt4) * 4;
-                double acc[4][4];
-#pragma unroll
-                for (int a4 = 0; a4 < 4; ++a4)
-#pragma unroll
-                    for (int b4 = 0; b4 < 4; ++b4) acc[a4][b4] = 0.0;
-                const int jn = K - j0;   // rows of this tile that are sums
-                if (jn > 0) {
-                    for (int i = 0; i < K; ++i) {
-                        const double *zr = Zt + (int64_t)kept[i] * k + c0;
-                        double zv[4], uv[4];
-#pragma unroll
-                        for (int b4 = 0; b4 < 4; ++b4) zv[b4] = c0 + b4 < k ? zr[b4] : 0.0;
-#pragma unroll
-                        for (int a4 = 0; a4 < 4; ++a4)
-                            uv[a4] = a4 < jn ? Ut[(int64_t)(j0 + a4) * K + i] : 0.0;
-#pragma unroll
-                        for (int a4 = 0; a4 < 4; ++a4)
-#pragma unroll
-                            for (int b4 = 0; b4 < 4; ++b4) acc[a4][b4] += uv[a4] * zv[b4];
-                    }
-                }
-#pragma unroll
-                for (int a4 = 0; a4 < 4; ++a4) {
-                    const int j = j0 + a4;
-                    if (j >= k) break;
-#pragma unroll
-                    for (int b4 = 0; b4 < 4; ++b4) {
-                        const int c = c0 + b4;
-                        if (c >= k) break;
-                        Zt2[(int64_t)j * k + c] = j < K ? acc[a4][b4] : Zt[(int64_t)kept[j] * k + c];
-                    }
-                }
+            for (int j = tid; j < k; j += kSolveThreads) {
+                out.eig[j] = sgn * (j < K ? dk[ord[j]] + tau[j] : dg[kept[j]]) / un;
+                out.kept[j] = kept[j];
             }
+            if (tid == 0) *out.K = K;
         }
-        __syncthreads();
-        Zv = Zt2;
+    }
+}
+
+// The eigenvectors from what k_sym_eig leaves: a wave takes a strip of 16 of
+// them, as 16 x 16 accumulator tiles (row = component) it keeps throughout,
+//   - forms them: columns c < K sum_r Zt[kept_r] U[r][c], the others Zt[kept_c];
+//   - applies the reflectors in blocks of 16, last to first, in the compact
+//     form of Schreiber and Van Loan: Z -= V (T (V^T Z)), V the block's
+//     reflectors (rows of A, staged in LDS), T upper triangular with T_ii =
+//     tau_i and column i above it -tau_i T (V^T v_i).  An accumulator tile is
+//     the next product's B operand as it stands (term l / 16 + 4 t in step t);
+//   - writes them to V in order of decreasing eigenvalue, and these to lam.
+// Four waves share the blocks' T, which they compute first, a block each in
+// turn.  Reflectors one at a time by the waves of k_sym_eig, with a sum over
+// the wave each, and the sums over kept rows by its threads took 0.37 ms at k =
+// 128 and 2.6 ms at 266; this takes 53 and 154 us (6 at 16, where the launch
+// costs what it saves), bound by the latency of the chain of blocks.
+constexpr int kBackThreads = 256;
+constexpr int kBackWaves = kBackThreads / 64;
+constexpr int kBackGroup = 3;   // tiles whose operands are read together
+__host__ __device__ constexpr int back_ld(int nt) { return 16 * nt + 2; }
+inline size_t back_lds(int maxt) {
+    return sizeof(double) * (size_t)(maxt * kBlk + 2 * 16 * back_ld(maxt));
+}
+template <int MAXT>
+__global__ void __launch_bounds__(kBackThreads, 1)
+k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__restrict__ V,
+           double *__restrict__ lam) {
+    static_assert(MAXT % kBackGroup == 0);
+    extern __shared__ double lds_a[];
+    const int64_t batch = blockIdx.y;
+    A += batch * k * k;
+    V += batch * k * k;
+    lam += batch * k;
+    const EigWs in = eig_ws(ws, k, batch);
+    constexpr int LD = back_ld(MAXT), VB = 16 * LD;
+    double *Ts = lds_a, *Vs = lds_a + MAXT * kBlk;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kr = lane >> 4, c16 = lane & 15;
+    const int c = 16 * (kBackWaves * (int)blockIdx.x + w) + c16;   // this lane's eigenvector
+    const int nblk = (k - 2 + 15) / 16;                            // blocks of reflectors
+    const __amdgpu_buffer_rsrc_t ab = square_buf(A, k), zb = square_buf(in.Zt, k),
+                                 ub = square_buf(in.U, k);
+    // entry i of reflector j (rows 0 .. k-3 of A right of the diagonal)
+    auto refl = [&](int j, int i) {
+        return buf_d(ab, 8 * (j * k + i) | out_if(i, k) | out_if(j, k - 2) | out_if(j, i));
+    };
+
+    // T of each block: V^T V by matrix steps, then row c16 of T by its lane
+    for (int b = w; b < nblk; b += kBackWaves) {
+        v4d g[kBackGroup] = {};
+        for (int I0 = b; I0 * 16 < k; I0 += kBackGroup) {
+            double x[kBackGroup][4];
+#pragma unroll
+            for (int u = 0; u < kBackGroup; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    x[u][t] = refl(16 * b + c16, 16 * (I0 + u) + kr + 4 * t);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < kBackGroup; ++u)
+                    g[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u][t], x[u][t], g[u], 0, 0, 0);
+        }
+        double *T = Ts + b * kBlk;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) T[(kr + 4 * t) * 17 + c16] = g[0][t] + g[1][t] + g[2][t];
+        __builtin_amdgcn_wave_barrier();
+        double tr[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const double tau = 16 * b + i < k ? in.tau[16 * b + i] : 0.0;
+            double acc = 0.0;
+#pragma unroll
+            for (int s = 0; s < i; ++s) acc = fma(tr[s], T[s * 17 + i], acc);
+            tr[i] = i == c16 ? tau : i > c16 ? -tau * acc : 0.0;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (kr == 0)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) T[c16 * 17 + i] = tr[i];
     }
 
-    // ---- 3. reflectors applied to each eigenvector, then sorted output.  A
-    // wave takes three eigenvectors at a time (three independent sums per
-    // reflector); reflector j is row j of A from column j + 1 on.
-    constexpr int R = (MK + 63) / 64;
-    for (int c0 = w; c0 < k; c0 += 3 * NW) {
-        double z[3][R];
+    // the eigenvectors of the tridiagonal matrix
+    const int K = *in.K;
+    v4d z[MAXT];
+    {
+        const int kc = c < k ? in.kept[c] : 0, copied = out_if(c, k) | out_if(K, c + 1);
 #pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const int c = c0 + r * NW;
+        for (int I = 0; I < MAXT; ++I)
 #pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int i = lane + 64 * q;
-                z[r][q] = c < k && i < k ? Zv[(int64_t)c * k + i] : 0.0;
+            for (int t = 0; t < 4; ++t) {
+                const int i = 16 * I + kr + 4 * t;
+                z[I][t] = buf_d(zb, 8 * (kc * k + i) | out_if(i, k) | copied);
             }
-        }
-        for (int j = k - 3; j >= 0; --j) {
-            const double tau = taus[j];
-            if (tau == 0.0) continue;
-            double v[R];
+        // the operands of a step are read two steps ahead, the row indices three
+        double x[2][MAXT], u[2];
+        auto row = [&](int r) { return in.kept[min(r, k - 1)]; };
+        auto read = [&](int h, int r, int kept) {
+            const int past = out_if(r, K);
+            u[h] = buf_d(ub, 8 * (r * k + c) | past | out_if(c, K));
 #pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int i = lane + 64 * q;
-                v[q] = i > j && i < k ? A[(int64_t)j * k + i] : 0.0;
-            }
-            double f[3];
+            for (int I = 0; I < MAXT; ++I)
+                x[h][I] = buf_d(zb, 8 * (kept * k + 16 * I + c16) | past | out_if(16 * I + c16, k));
+        };
+        read(0, kr, row(kr));
+        read(1, 4 + kr, row(4 + kr));
+        int next[2] = {row(8 + kr), row(12 + kr)};
+        for (int r0 = 0; r0 < K; r0 += 8) {
 #pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                double dot = 0.0;
+            for (int h = 0; h < 2; ++h) {
 #pragma unroll
-                for (int q = 0; q < R; ++q) dot += v[q] * z[r][q];
-                f[r] = dot;
-            }
-#pragma unroll
-            for (int r = 0; r < 3; ++r) f[r] = tau * wave_sum(f[r]);
-#pragma unroll
-            for (int r = 0; r < 3; ++r)
-#pragma unroll
-                for (int q = 0; q < R; ++q) z[r][q] -= f[r] * v[q];
-        }
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const int c = c0 + r * NW;
-            if (c >= k) break;
-            // rank by decreasing eigenvalue, ties by index
-            const double lc = dg[c];
-            int rank = 0;
-            for (int j0 = 0; j0 < k; j0 += 64) {
-                const int j = j0 + lane;
-                const bool before = j < k && (dg[j] > lc || (dg[j] == lc && j < c));
-                rank += __popcll(__ballot(before));
-            }
-            if (lane == 0) lam[rank] = lc;
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int i = lane + 64 * q;
-                if (i < k) V[(int64_t)i * k + rank] = z[r][q];
+                for (int I = 0; I < MAXT; ++I)
+                    z[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[h][I], u[h], z[I], 0, 0, 0);
+                read(h, r0 + 4 * h + 8 + kr, next[h]);
+                next[h] = row(r0 + 4 * h + 16 + kr);
             }
         }
     }
+
+    // reflectors, block nblk - 1 first
+    const int sr = tid >> 4, si = tid & 15;   // staging: row, column of a tile
+    double st[MAXT];
+    auto fetch = [&](int b) {
+#pragma unroll
+        for (int I = 0; I < MAXT; ++I) st[I] = refl(16 * b + sr, 16 * I + si);
+    };
+    auto store = [&](int b) {
+#pragma unroll
+        for (int I = 0; I < MAXT; ++I) Vs[(b & 1) * VB + sr * LD + 16 * I + si] = st[I];
+    };
+    fetch(nblk - 1);
+    store(nblk - 1);
+    __syncthreads();
+    for (int b = nblk - 1; b >= 0; --b) {
+        if (b > 0) fetch(b - 1);
+        const double *v = Vs + (b & 1) * VB, *T = Ts + b * kBlk;
+        v4d p[kBackGroup] = {};
+#pragma unroll
+        for (int I0 = 0; I0 < MAXT; I0 += kBackGroup) {
+            if (I0 + kBackGroup <= b || 16 * I0 >= k) continue;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < kBackGroup; ++u)
+                    p[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        v[c16 * LD + 16 * (I0 + u) + kr + 4 * t], z[I0 + u][t], p[u], 0, 0, 0);
+        }
+        v4d q = {};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            q = __builtin_amdgcn_mfma_f64_16x16x4f64(T[c16 * 17 + kr + 4 * t],
+                                                     -(p[0][t] + p[1][t] + p[2][t]), q, 0, 0, 0);
+#pragma unroll
+        for (int I0 = 0; I0 < MAXT; I0 += kBackGroup) {
+            if (I0 + kBackGroup <= b || 16 * I0 >= k) continue;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < kBackGroup; ++u)
+                    z[I0 + u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        v[(kr + 4 * t) * LD + 16 * (I0 + u) + c16], q[t], z[I0 + u], 0, 0, 0);
+        }
+        if (b > 0) store(b - 1);
+        __syncthreads();
+    }
+
+    // rank by decreasing eigenvalue, ties by index; four lanes share a column
+    if (c - c16 >= k) return;
+    const double lc = c < k ? in.eig[c] : 0.0;
+    int rank = 0;
+    for (int j = kr; j < k; j += 4) {
+        const double lj = in.eig[j];
+        rank += lj > lc || (lj == lc && j < c) ? 1 : 0;
+    }
+    rank += __shfl_xor(rank, 16, 64);
+    rank += __shfl_xor(rank, 32, 64);
+    if (c >= k) return;
+    if (kr == 0) lam[rank] = lc;
+#pragma unroll
+    for (int I = 0; I < MAXT; ++I)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int i = 16 * I + kr + 4 * t;
+            if (i < k) V[(int64_t)i * k + rank] = z[I][t];
+        }
 }
 
 __global__ void k_eig_weights(const double *__restrict__ V, const double *__restrict__ lam,
@@ -1933,7 +2027,7 @@ lne_status chol_inv(lne_ctx *ctx, double *G, int32_t k, double *W, int32_t *stat
     return check_launch(ctx, "chol_inv");
 }
 
-size_t sym_eig_ws_doubles(int32_t k, int32_t nb) { return (size_t)nb * 2 * k * k; }
+size_t sym_eig_ws_doubles(int32_t k, int32_t nb) { return (size_t)nb * eig_ws_one(k); }
 
 lne_status sym_eig(lne_ctx *ctx, double *C, int32_t k, double *V, double *lam, int32_t nb,
                    double *vw_ws) {
@@ -1965,11 +2059,25 @@ lne_status sym_eig(lne_ctx *ctx, double *C, int32_t k, double *V, double *lam, i
     const size_t need = sizeof(double) * (size_t)k * k;
     if (k <= kEigMaxLds && need <= (size_t)lds_limit) {
         Launch L(ctx, "sym_eig");
-        k_sym_eig<true><<<nb, kSolveThreads, need, ctx->stream>>>(C, k, vw.as<double>(), V, lam);
+        k_sym_eig<true><<<nb, kSolveThreads, need, ctx->stream>>>(C, k, vw.as<double>());
     } else {
         Launch L(ctx, "sym_eig");
-        k_sym_eig<false><<<nb, kSolveThreads, 0, ctx->stream>>>(C, k, vw.as<double>(), V, lam);
+        k_sym_eig<false><<<nb, kSolveThreads, 0, ctx->stream>>>(C, k, vw.as<double>());
     }
+    LNE_TRY(check_launch(ctx, "sym_eig"));
+    const int nt = (k + 15) / 16;
+    const dim3 grid((unsigned)((nt + kBackWaves - 1) / kBackWaves), (unsigned)nb);
+#define LNE_EB(M)                                                                              \
+    do {                                                                                       \
+        LNE_TRY(lds_opt_in(ctx, (const void *)k_eig_back<M>, back_lds(M)));                    \
+        Launch L(ctx, "sym_eig");                                                              \
+        k_eig_back<M><<<grid, kBackThreads, back_lds(M), ctx->stream>>>(C, k, vw.as<double>(), \
+                                                                        V, lam);               \
+    } while (0)
+    if (nt <= 3) LNE_EB(3);
+    else if (nt <= 9) LNE_EB(9);
+    else LNE_EB(18);
+#undef LNE_EB
     return check_launch(ctx, "sym_eig");
 }
 

@@ -116,6 +116,23 @@ def test_eigsvd_structured_spectra(lne, ctx, k, kind):
     assert np.all(Un[:, ~keep] == 0.0)
 
 
+# the reflectors' blocks and the strips of eigenvectors are 16 wide, four strips
+# a workgroup, in widths of 3, 9 and 18 tiles; 2 has no reflector
+@pytest.mark.parametrize("k", [1, 2, 3, 16, 17, 18, 19, 48, 49, 64, 65, 128, 144, 145])
+def test_eigsvd_at_tile_edges(lne, ctx, k):
+    """V orthogonal and diagonalising G = Y^T Y: each of the k plane rotations
+    and reflectors a column takes errs by some units of rounding, so the bars
+    allow 16 k of them, relative to the largest eigenvalue."""
+    import torch
+    Y = _rand_y(600, k, seed=7 + k, cond=1e2 if k > 1 else 1.0)
+    _, S, V = lne.eigsvd(ctx, torch.from_numpy(Y).cuda())
+    S, V = S.cpu().numpy(), V.cpu().numpy()
+    bar = 16 * k * 2.0 ** -53
+    assert np.max(np.abs(V.T @ V - np.eye(k))) <= bar
+    assert np.max(np.abs(V.T @ (Y.T @ Y) @ V - np.diag(S ** 2))) <= bar * S[0] ** 2
+    assert np.all(S[:-1] >= S[1:])
+
+
 @pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
 @pytest.mark.parametrize("k", [42, 138])
 def test_orthonormalize(lne, ctx, dtype, k):
