@@ -1029,9 +1029,13 @@ k_chol_inv(double *Gb, int k, double *Wb, int32_t *__restrict__ status,
 //     problem's and applies the reflectors.
 // IN_LDS: A lives in LDS (k^2 doubles of dynamic shared memory) during phase
 // 1; otherwise it is worked on in place in global memory.  The eigenvectors of
-// the tridiagonal matrix are kept transposed in Zt (row i = eigenvector i), so
-// a rotation of eigenvectors (i, i+1) reads two rows.
+// the tridiagonal matrix are kept transposed (row i = eigenvector i), so a
+// rotation of eigenvectors (i, i+1) reads two rows; with IN_LDS the halves'
+// take A's place during phase 2, as the sweeps' rotations would wait for
+// global memory otherwise (phase 2 at k = 128: 0.97 ms in global memory with
+// the slower chain, 0.58 ms now).
 constexpr int kEigMaxLds = 144;   // largest k of the LDS variant
+constexpr int kZStride = kEigMaxLds / 2;   // LDS rows of a half's eigenvector components
 constexpr int kEigSplit = 32;   // tear the tridiagonal matrix from this size on
 
 // What k_sym_eig hands to k_eig_back: rows of eigenvectors of the tridiagonal
@@ -1065,129 +1069,196 @@ struct QlState {
     int iter = 0;   // sweeps spent on eigenvalue l
 };
 
-// The rotations of one QL sweep, rows m-1 up to l, from the values (d, e)
-// held when the sweep started: lane j keeps entries 64 q + j in D[q], E[q]
-// and the serial chain reads them by lane index; lane 0 stores the new d, e
-// and the rotations (rc, rs at the index of their upper row).  The matrix is
-// scaled to unit size, so f^2 + g^2 is a normal number unless both are
-// negligible (below 2^-500), which is where the sweep must deflate instead.
+// The rotations of one QL sweep, rows m-1 up to l, by one lane: a serial chain
+// that takes the (d, e) pairs from LDS a group of rows ahead of their use and
+// writes the new ones and the rotations (cosine, sine, by upper row) as it
+// goes.  Bound by the instructions a single wave issues (some 28 a rotation,
+// five to six cycles each, 18 for the root's estimate), hence pairs in one
+// access, no clamped addresses (up to 2 kChain - 1 rows above l are read and
+// not used) and one refined root: 200 cycles a rotation, against 470 with the
+// pairs in registers read by lane index and every lane's stores masked.  The
+// matrix is scaled to unit size, so f^2 + g^2 is a normal number unless both
+// are negligible (below 2^-500), which is where the sweep must deflate instead.
 // CHECK = false runs the chain with no branch on that test and returns -2 if
 // it failed anywhere (the stored values are then void); CHECK = true returns
 // the row at which it deflated, or -1 when the sweep completed.
-template <int R, bool CHECK>
-__device__ int ql_chain(const double (&D)[R], const double (&E)[R], int l, int m, double g,
-                        double dn, double dl, double *d, double *e, double *rc, double *rs,
-                        bool w0) {
-    double s = 1.0, c = 1.0, p = 0.0;
-    bool bad = false;
-    // segments of 64 rows from the bottom, each reading its own registers
-    // (q is a constant in each unrolled copy)
-#pragma unroll
-    for (int q = R - 1; q >= 0; --q) {
-        if (q > ((m - 1) >> 6) || q < (l >> 6)) continue;
-        const double Dq = D[q], Eq = E[q];
-        const int ilo = l > 64 * q ? l : 64 * q;
-        for (int i = (m - 1 < 64 * q + 63 ? m - 1 : 64 * q + 63); i >= ilo; --i) {
-            const double di = readlane_d(Dq, i - 64 * q), ei = readlane_d(Eq, i - 64 * q);
-            const double f = s * ei, b = c * ei;
-            const double x = fma(f, f, g * g);
-            if constexpr (CHECK) {
-                if (!(x >= 0x1p-1000)) {   // both vanished: deflate at i + 1
-                    if (w0) {
-                        e[i + 1] = 0.0;
-                        d[i + 1] = dn - p;
-                        e[m] = 0.0;
-                    }
-                    return i;
-                }
-            } else {
-                bad |= !(x >= 0x1p-1000);
+constexpr int kChain = 4;
+template <bool CHECK>
+__device__ int ql_chain(int l, int m, double g, double2 *de, double2 *rot) {
+    double s = 1.0, c = 1.0, p = 0.0, dn = de[m].x, least = 1.0;
+    const double dl = de[l].x;
+    auto rotate = [&](int i, double2 x0) {
+        const double f = s * x0.y, b = c * x0.y;
+        const double x = fma(f, f, g * g);
+        least = fmin(least, x);
+        // 1/sqrt(x) by the hardware estimate y (to 2^-23) and one cubic step,
+        // y (1 + h/2 + 3 h^2 / 8) with h = 1 - x y^2
+        const double y = __builtin_amdgcn_rsq(x);
+        const double h = fma(-(x * y), y, 1.0);
+        const double y1 = fma(y, h * fma(0.375, h, 0.5), y);
+        c = g * y1;
+        s = f * y1;
+        const double gp = dn - p;
+        const double r2 = fma(b + b, c, (x0.x - gp) * s);
+        p = s * r2;
+        g = fma(c, r2, -b);
+        de[i + 1] = make_double2(gp + p, x * y1);
+        rot[i] = make_double2(c, s);
+        dn = x0.x;
+    };
+    int i = m - 1;
+    if constexpr (CHECK) {
+        for (; i >= l; --i) {
+            const double2 x0 = de[i];
+            const double f = s * x0.y;
+            if (!(fma(f, f, g * g) >= 0x1p-1000)) {   // both vanished: deflate at i + 1
+                de[i + 1] = make_double2(dn - p, 0.0);
+                de[m].y = 0.0;
+                return i;
             }
-            // 1/sqrt(x) by the hardware estimate and two Newton steps, the
-            // last step's product folded into c, s and r
-            const double h = 0.5 * x, y0 = __builtin_amdgcn_rsq(x);
-            const double y1 = y0 * fma(-h * y0, y0, 1.5);
-            const double u2 = fma(-h * y1, y1, 1.5);
-            c = (g * y1) * u2;
-            s = (f * y1) * u2;
-            const double gp = dn - p;
-            const double r2 = fma(di - gp, s, (2.0 * b) * c);
-            p = s * r2;
-            g = fma(c, r2, -b);
-            if (w0) {
-                e[i + 1] = (x * y1) * u2;
-                d[i + 1] = gp + p;
-                rc[i] = c;
-                rs[i] = s;
-            }
-            dn = di;
+            rotate(i, x0);
         }
+    } else {
+        double2 x0[kChain], x1[kChain];
+#pragma unroll
+        for (int u = 0; u < kChain; ++u) x0[u] = de[i - u];
+        for (; i - 2 * kChain + 1 >= l; i -= 2 * kChain) {
+#pragma unroll
+            for (int u = 0; u < kChain; ++u) x1[u] = de[i - kChain - u];
+#pragma unroll
+            for (int u = 0; u < kChain; ++u) rotate(i - u, x0[u]);
+#pragma unroll
+            for (int u = 0; u < kChain; ++u) x0[u] = de[i - 2 * kChain - u];
+#pragma unroll
+            for (int u = 0; u < kChain; ++u) rotate(i - kChain - u, x1[u]);
+        }
+        if (i - kChain + 1 >= l) {
+#pragma unroll
+            for (int u = 0; u < kChain; ++u) x1[u] = de[i - kChain - u];
+#pragma unroll
+            for (int u = 0; u < kChain; ++u) rotate(i - u, x0[u]);
+#pragma unroll
+            for (int u = 0; u < kChain; ++u) x0[u] = x1[u];
+            i -= kChain;
+        }
+#pragma unroll
+        for (int u = 0; u < kChain - 1; ++u)
+            if (i - u >= l) rotate(i - u, x0[u]);
+        if (!(least >= 0x1p-1000) || g != g) return -2;
     }
-    if (!CHECK && bad) return -2;
-    if (w0) {
-        d[l] = dl - p;
-        e[l] = g;
-        e[m] = 0.0;
-    }
+    de[l] = make_double2(dl - p, g);
+    de[m].y = 0.0;
     return -1;
 }
 
-// One QL sweep on (d, e) (length-k diagonal and coupling e[i] between i and
-// i+1, e[k-1] = 0), run by a whole wave computing the same values.  Returns
-// false once every eigenvalue has converged; else the sweep's rotations are
-// in rc, rs over [*lo, *hi).
+// One QL sweep on the pairs de (length-k diagonal and coupling between i and
+// i+1, the last 0), run by a whole wave.  Returns false once every eigenvalue
+// has converged; else the sweep's rotations are in rot over [*lo, *hi).
 template <int R>
-__device__ bool ql_sweep(double *d, double *e, int k, QlState &st, double *rc, double *rs,
-                         int *lo, int *hi, int lane) {
+__device__ bool ql_sweep(double2 *de, int k, QlState &st, double2 *rot, int *lo, int *hi,
+                         int lane) {
     const double eps = 2.220446049250313e-16;
-    const bool w0 = lane == 0;
-    while (st.l < k) {
-        const int l = st.l;
-        double D[R], E[R];
-        int m = k - 1;
+    for (;;) {
+        double2 x[R];
+        uint64_t split[R];   // couplings that are negligible
 #pragma unroll
         for (int q = 0; q < R; ++q) {
             const int j = 64 * q + lane;
-            D[q] = j < k ? d[j] : 0.0;
-            E[q] = j < k ? e[j] : 0.0;
-            const double dn = j + 1 < k ? d[j + 1] : 0.0;
-            // the first coupling at or after l that is negligible
-            const bool split = j >= l && j < k - 1 && fabs(E[q]) <= eps * (fabs(D[q]) + fabs(dn));
-            const uint64_t bal = __ballot(split);
-            if (bal && m == k - 1) m = 64 * q + __builtin_ctzll(bal);
+            x[q] = de[min(j, k - 1)];
+            const double dn = de[min(j + 1, k - 1)].x;
+            split[q] = __ballot(j < k - 1 && fabs(x[q].y) <= eps * (fabs(x[q].x) + fabs(dn)));
         }
-        if (m == l) {
-            st.l = l + 1;
+        // l: the first eigenvalue not yet converged, m: the first negligible
+        // coupling at or after it
+        int l = st.l, m = 0;
+        for (; l < k; ++l) {
+            m = k - 1;
+#pragma unroll
+            for (int q = R - 1; q >= 0; --q) {
+                const int from = min(max(l - 64 * q, 0), 64);
+                const uint64_t left = from < 64 ? split[q] >> from << from : 0;
+                if (left) m = 64 * q + __builtin_ctzll(left);
+            }
+            if (m != l) break;
+        }
+        if (l != st.l) {
+            st.l = l;
             st.iter = 0;
-            continue;
         }
+        if (l >= k) return false;
         if (st.iter++ >= 64) {   // not expected: give up on this coupling
-            if (w0) e[l] = 0.0;
+            if (lane == 0) de[l].y = 0.0;
             __builtin_amdgcn_wave_barrier();
             continue;
         }
-        const double dl = d[l], dl1 = d[l + 1], el = e[l], dm = d[m];
-        // shift: the eigenvalue of the leading 2 x 2 block nearer d[l]
-        double g = (dl1 - dl) / (2.0 * el);
-        const double r = hypot(g, 1.0);
-        g = dm - dl + el / (g + (g >= 0.0 ? r : -r));
-        int at = ql_chain<R, false>(D, E, l, m, g, dm, dl, d, e, rc, rs, w0);
+        int at = 0;
+        double g = 0.0;
+        if (lane == 0) {
+            // shift: the eigenvalue of the leading 2 x 2 block nearer d[l]; the
+            // coupling is not negligible, so the quotient is below 2^52
+            const double2 xl = de[l];
+            g = (de[l + 1].x - xl.x) / (2.0 * xl.y);
+            const double r = sqrt(fma(g, g, 1.0));
+            g = de[m].x - xl.x + xl.y / (g + (g >= 0.0 ? r : -r));
+            at = ql_chain<false>(l, m, g, de, rot);
+        }
+        __builtin_amdgcn_wave_barrier();
+        at = __builtin_amdgcn_readfirstlane(at);
         if (at == -2) {
             // put the sweep's starting values back, then take the checked path
 #pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int j = 64 * q + lane;
-                if (j < k) { d[j] = D[q]; e[j] = E[q]; }
-            }
+            for (int q = 0; q < R; ++q)
+                if (64 * q + lane < k) de[64 * q + lane] = x[q];
             __builtin_amdgcn_wave_barrier();
-            at = ql_chain<R, true>(D, E, l, m, g, dm, dl, d, e, rc, rs, w0);
+            if (lane == 0) at = ql_chain<true>(l, m, g, de, rot);
+            __builtin_amdgcn_wave_barrier();
+            at = __builtin_amdgcn_readfirstlane(at);
         }
-        __builtin_amdgcn_wave_barrier();
         *lo = at >= 0 ? at + 1 : l;
         *hi = m;
         if (*lo < *hi) return true;
     }
-    return false;
+}
+
+// The rotations hi-1 .. lo of a sweep applied to one component of the
+// eigenvectors, rows ld apart at z (row 0), the operands of G rotations read
+// ahead of their use.
+template <int G>
+__device__ void ql_apply(double *z, int ld, const double2 *rot, int lo, int hi) {
+    double *p = z + hi * ld;
+    double carry = *p;
+    auto turn = [&](double *q, double x, double2 f) {   // q: the lower row
+        *q = fma(f.x, carry, f.y * x);
+        carry = fma(-f.y, carry, f.x * x);
+    };
+    int i = hi - 1;
+    double x[G];
+    double2 f[G];
+    auto read = [&](int from) {
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            const int j = max(from - u, lo);
+            x[u] = z[j * ld];
+            f[u] = rot[j];
+        }
+    };
+    read(i);
+    for (; i - G + 1 >= lo; i -= G, p -= G * ld) {
+        double x0[G];
+        double2 f0[G];
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            x0[u] = x[u];
+            f0[u] = f[u];
+        }
+        read(i - G);
+#pragma unroll
+        for (int u = 0; u < G; ++u) turn(p - u * ld, x0[u], f0[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < G - 1; ++u)
+        if (i - u >= lo) turn(p - u * ld, x[u], f[u]);
+    z[lo * ld] = carry;
 }
 
 template <bool IN_LDS>
@@ -1196,9 +1267,12 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
     constexpr int MK = IN_LDS ? kEigMaxLds : kEigMaxK;
     extern __shared__ double lds_a[];
     __shared__ double dg[MK], eg[MK], taus[MK];
-    __shared__ double buf[4 * MK];   // p of a Householder step, then the rotation buffers
+    __shared__ double2 rot[2 * MK];   // the rotation buffers; before and after, vectors:
+    double *buf = (double *)rot;      // of a Householder step, of the merge
+    __shared__ double2 de_pad[2 * kChain + MK];
+    double2 *de = de_pad + 2 * kChain;   // the pairs (d, e) of the sweeps; then
+    int *idx = (int *)de_pad;            // merge: order, kept and deflated rows
     __shared__ int s_lo[2][2], s_hi[2][2], s_more[2][2];   // [problem][buffer]
-    __shared__ int idx[2 * MK];                             // merge: order, kept and deflated rows
     __shared__ double s_rho, s_unit, s_tol;
     __shared__ int s_K, s_flip;
     Ag += (int64_t)blockIdx.x * k * k;
@@ -1212,8 +1286,9 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         for (int64_t i = tid; i < (int64_t)k * k; i += kSolveThreads) lds_a[i] = Ag[i];
         A = lds_a;
     }
-    for (int64_t i = tid; i < (int64_t)k * k; i += kSolveThreads)
-        Zt[i] = (i / k == i % k) ? 1.0 : 0.0;
+    if constexpr (!IN_LDS)
+        for (int64_t i = tid; i < (int64_t)k * k; i += kSolveThreads)
+            Zt[i] = (i / k == i % k) ? 1.0 : 0.0;
     __syncthreads();
 
     // ---- 1. Householder reduction.  Per step: every wave forms the
@@ -1302,45 +1377,48 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
     // (w = e_{h-1} + e_h, rho the coupling, taken off d[h-1] and d[h]); waves
     // 0 and 1 run the QL sweeps of T1 and T2 side by side while waves 2..
     // apply each problem's previous sweep to its block of eigenvector rows
-    // (component c by thread c; rotation buffer b: cosines at buf + 2 MK b,
-    // sines MK further, indexed by global row).  The merge below then solves
-    // the rank-one problem.  Smaller k: one problem, waves 1.. apply.
+    // (component c by thread c; rotation buffer b at rot + MK b, indexed by
+    // global row).  The merge below then solves the rank-one problem.  Smaller
+    // k: one problem, waves 1.. apply.
     const int h = k >= kEigSplit ? k / 2 : k;
     const int np = h < k ? 2 : 1;
+    if constexpr (IN_LDS) {   // the identity in A's place: row i of its half's components
+        __syncthreads();
+        for (int i = tid; i < k * kZStride; i += kSolveThreads) {
+            const int r = i / kZStride, c = i % kZStride;
+            lds_a[i] = c == (r >= h ? r - h : r) ? 1.0 : 0.0;
+        }
+    }
     if (w == 0) {
         double amax = 0.0;
         for (int i = lane; i < k; i += 64) amax = fmax(amax, fmax(fabs(dg[i]), fabs(eg[i])));
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) amax = fmax(amax, __shfl_xor(amax, o, 64));
         double unit = 1.0;
-        if (amax > 0.0 && isfinite(amax)) {
-            unit = ldexp(1.0, -ilogb(amax));
-            for (int i = lane; i < k; i += 64) { dg[i] *= unit; eg[i] *= unit; }
+        if (amax > 0.0 && isfinite(amax)) unit = ldexp(1.0, -ilogb(amax));
+        // the tear's rank-one term leaves d[h-1] and d[h]
+        const double rho = np == 2 ? eg[h - 1] * unit : 0.0;
+        for (int i = lane; i < k; i += 64) {
+            const bool torn = np == 2 && (i == h - 1 || i == h);
+            de[i] = make_double2(torn ? dg[i] * unit - rho : dg[i] * unit,
+                                 np == 2 && i == h - 1 ? 0.0 : eg[i] * unit);
         }
-        __builtin_amdgcn_wave_barrier();
         if (lane == 0) {
             s_unit = unit;
-            s_rho = 0.0;
-            if (np == 2) {
-                const double rho = eg[h - 1];
-                dg[h - 1] -= rho;
-                dg[h] -= rho;
-                eg[h - 1] = 0.0;
-                s_rho = rho;
-            }
+            s_rho = rho;
         }
     }
     __syncthreads();
     {
         QlState st;
+        if (w < np) __builtin_amdgcn_s_setprio(3);   // a chain goes before its SIMD's other waves
         for (int t = 0;; ++t) {
             const int b = t & 1;
             if (w < np) {
                 const int base = w == 0 ? 0 : h, n = w == 0 ? h : k - h;
                 int lo = 0, hi = 0;
-                double *cb = buf + 2 * MK * b + base;
-                const bool more = ql_sweep<(MK + 63) / 64>(dg + base, eg + base, n, st, cb,
-                                                          cb + MK, &lo, &hi, lane);
+                const bool more = ql_sweep<(MK / 2 + 63) / 64>(de + base, n, st,
+                                                              rot + MK * b + base, &lo, &hi, lane);
                 if (lane == 0) {
                     s_more[w][b] = more ? 1 : 0;
                     s_lo[w][b] = base + lo;
@@ -1348,32 +1426,28 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
                 }
             }
             const int pb = b ^ 1;
-            const int kk = tid - 64 * np;
-            const int pr = kk >= h ? 1 : 0;
-            if (t > 0 && kk >= 0 && kk < k && s_more[pr][pb]) {
-                const int lo = s_lo[pr][pb], hi = s_hi[pr][pb];
-                const double *c = buf + 2 * MK * pb, *s = c + MK;
-                double carry = Zt[(int64_t)hi * k + kk];
-                // rotations hi-1 .. lo, loads of up to 16 rows issued ahead
-                for (int i0 = hi - 1; i0 >= lo; i0 -= 16) {
-                    double z[16];
-                    const int cnt = i0 - lo + 1 < 16 ? i0 - lo + 1 : 16;
-#pragma unroll
-                    for (int u = 0; u < 16; ++u)
-                        if (u < cnt) z[u] = Zt[(int64_t)(i0 - u) * k + kk];
-#pragma unroll
-                    for (int u = 0; u < 16; ++u)
-                        if (u < cnt) {
-                            const int i = i0 - u;
-                            Zt[(int64_t)(i + 1) * k + kk] = s[i] * z[u] + c[i] * carry;
-                            carry = c[i] * z[u] - s[i] * carry;
-                        }
-                }
-                Zt[(int64_t)lo * k + kk] = carry;
+            const int pr = w - np >= (h + 63) / 64 ? 1 : 0;   // whole waves for each half
+            const int kk = tid - 64 * (np + (pr ? (h + 63) / 64 : 0));
+            if (t > 0 && w >= np && kk < (pr ? k - h : h) && s_more[pr][pb]) {
+                const int lo = __builtin_amdgcn_readfirstlane(s_lo[pr][pb]);
+                const int hi = __builtin_amdgcn_readfirstlane(s_hi[pr][pb]);
+                if constexpr (IN_LDS)
+                    ql_apply<4>(lds_a + kk, kZStride, rot + MK * pb, lo, hi);
+                else
+                    ql_apply<8>(Zt + (pr ? h : 0) + kk, k, rot + MK * pb, lo, hi);
             }
             __syncthreads();
             if (!s_more[0][b] && !s_more[1][b]) break;
         }
+        __builtin_amdgcn_s_setprio(0);
+        if constexpr (IN_LDS) {
+            for (int i = tid; i < k * k; i += kSolveThreads) {
+                const int r = i / k, c = i % k;
+                Zt[i] = (r >= h) == (c >= h) ? lds_a[r * kZStride + (c >= h ? c - h : c)] : 0.0;
+            }
+        }
+        for (int i = tid; i < k; i += kSolveThreads) dg[i] = de[i].x;
+        __syncthreads();
     }
     if (np == 1) {
         for (int i = tid; i < k; i += kSolveThreads) {
@@ -2056,7 +2130,7 @@ lne_status sym_eig(lne_ctx *ctx, double *C, int32_t k, double *V, double *lam, i
             lds_limit = bytes - (int)fa.sharedSizeBytes;
         (void)hipGetLastError();
     }
-    const size_t need = sizeof(double) * (size_t)k * k;
+    const size_t need = sizeof(double) * (size_t)k * std::max(k, kZStride);
     if (k <= kEigMaxLds && need <= (size_t)lds_limit) {
         Launch L(ctx, "sym_eig");
         k_sym_eig<true><<<nb, kSolveThreads, need, ctx->stream>>>(C, k, vw.as<double>());
