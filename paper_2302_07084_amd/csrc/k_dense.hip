@@ -1007,15 +1007,13 @@ k_chol_inv(double *Gb, int k, double *Wb, int32_t *__restrict__ status,
 
 // ---------------------------------------------------------------- eigen-solver
 // Symmetric eigen-decomposition of a k x k matrix, in three phases, the first
-// two by one workgroup (Householder reduction to tridiagonal form, the tridiagonal
-// eigen-problem, the reflectors applied to its eigenvectors):
+// two by one workgroup each (Householder reduction to tridiagonal form, the
+// tridiagonal eigen-problem, the reflectors applied to its eigenvectors):
 //  1. k - 2 Householder steps.  Step j reflects the entries of column j below
 //     the subdiagonal to zero: with x = A[j+1.., j], beta = -sign(x0) |x|,
 //     v = (1, x1 / (x0 - beta), ...), tau = (beta - x0) / beta, the trailing
 //     block becomes A - v w^T - w v^T with p = tau A v, w = p - (tau/2)(p.v) v.
-//     v is written into row j (which later steps never touch).  The two
-//     products of the rank-2 update are rounded separately, so the block
-//     stays exactly symmetric.
+//     v is written into row j (which later steps never touch).
 //  2. The tridiagonal matrix (d, e): implicit QL sweeps (Wilkinson's shift)
 //     chase the shifted bulge from the bottom of an unreduced block to its
 //     top with plane rotations.  One wave computes a sweep's rotations while
@@ -1027,29 +1025,29 @@ k_chol_inv(double *Gb, int k, double *Wb, int32_t *__restrict__ status,
 //     rank-one problem (its comment gives the steps).
 //  3. k_eig_back multiplies the halves' eigenvectors by the rank-one
 //     problem's and applies the reflectors.
-// IN_LDS: A lives in LDS (k^2 doubles of dynamic shared memory) during phase
-// 1; otherwise it is worked on in place in global memory.  The eigenvectors of
-// the tridiagonal matrix are kept transposed (row i = eigenvector i), so a
-// rotation of eigenvectors (i, i+1) reads two rows; with IN_LDS the halves'
-// take A's place during phase 2, as the sweeps' rotations would wait for
-// global memory otherwise (phase 2 at k = 128: 0.97 ms in global memory with
-// the slower chain, 0.58 ms now).
+// The eigenvectors of the tridiagonal matrix are kept transposed (row i =
+// eigenvector i), so a rotation of eigenvectors (i, i+1) reads two rows; with
+// IN_LDS the halves' are in LDS during phase 2, as the sweeps' rotations would
+// wait for global memory otherwise (phase 2 at k = 128: 0.97 ms in global
+// memory with the slower chain, 0.58 ms now).
 constexpr int kEigMaxLds = 144;   // largest k of the LDS variant
 constexpr int kZStride = kEigMaxLds / 2;   // LDS rows of a half's eigenvector components
 constexpr int kEigSplit = 32;   // tear the tridiagonal matrix from this size on
 
 // What k_sym_eig hands to k_eig_back: rows of eigenvectors of the tridiagonal
 // matrix (or of its halves), the rank-one problem's eigenvectors (U, K x K,
-// rows k apart), the eigenvalues, the reflectors' factors, the rows of Zt the
-// columns of the result are built from, and K.
+// rows k apart), the eigenvalues (before, the diagonal), the reflectors'
+// factors, the coupling, the rows of Zt the columns of the result are built
+// from, and K.
 struct EigWs {
-    double *Zt, *U, *eig, *tau;
+    double *Zt, *U, *eig, *tau, *off;
     int32_t *kept, *K;
 };
-__host__ __device__ constexpr int64_t eig_ws_one(int64_t k) { return 2 * k * k + 3 * k + 1; }
+__host__ __device__ constexpr int64_t eig_ws_one(int64_t k) { return 2 * k * k + 4 * k + 1; }
 __device__ __forceinline__ EigWs eig_ws(double *ws, int k, int64_t batch) {
     double *p = ws + batch * eig_ws_one(k), *q = p + 2 * (int64_t)k * k;
-    return {p, p + (int64_t)k * k, q, q + k, (int32_t *)(q + 2 * k), (int32_t *)(q + 3 * k)};
+    return {p,     p + (int64_t)k * k,        q,
+            q + k, q + 2 * k, (int32_t *)(q + 3 * k), (int32_t *)(q + 4 * k)};
 }
 
 // Sum over a fully active wave, the same bits in every lane: pairs, quads,
@@ -1261,44 +1259,172 @@ __device__ void ql_apply(double *z, int ld, const double2 *rot, int lo, int hi) 
     z[lo * ld] = carry;
 }
 
-template <bool IN_LDS>
-__global__ void __launch_bounds__(kSolveThreads)
-k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
-    constexpr int MK = IN_LDS ? kEigMaxLds : kEigMaxK;
-    extern __shared__ double lds_a[];
-    __shared__ double dg[MK], eg[MK], taus[MK];
-    __shared__ double2 rot[2 * MK];   // the rotation buffers; before and after, vectors:
-    double *buf = (double *)rot;      // of a Householder step, of the merge
-    __shared__ double2 de_pad[2 * kChain + MK];
-    double2 *de = de_pad + 2 * kChain;   // the pairs (d, e) of the sweeps; then
-    int *idx = (int *)de_pad;            // merge: order, kept and deflated rows
-    __shared__ int s_lo[2][2], s_hi[2][2], s_more[2][2];   // [problem][buffer]
-    __shared__ double s_rho, s_unit, s_tol;
-    __shared__ int s_K, s_flip;
-    Ag += (int64_t)blockIdx.x * k * k;
-    const EigWs out = eig_ws(ws, k, blockIdx.x);
-    double *__restrict__ Zt = out.Zt;
-    // the wave index as a scalar, so that code under `w == 0` branches as a
-    // uniform wave
+// Phase 1 for k <= 64 C: the matrix in registers, wave w of W holding the
+// pairs of rows w + W q, lane l of it columns l + 64 c.  Step j: with x row j, u = x past the
+// diagonal, its first entry less beta, and H = I - g u u^T, g = 1 / (beta^2 -
+// beta x0), the trailing block becomes A - u w^T - w u^T, w = p - (g/2)(p.u) u,
+// p = g A u.  The waves' parts of p meet in LDS; every wave forms the same sums
+// and its own w, so a step has two block barriers.  Bound by its chain (two
+// sums over a wave, a root, a reciprocal, three trips through LDS): with the
+// matrix in LDS, read twice and written once a step, and three barriers, 380
+// us at k = 128 and 71 at 42; this takes 199 and 46.
+constexpr int kTriDiagThreads = 512;
+constexpr int kTriDiagWaves = kTriDiagThreads / 64;
+// A block barrier that waits for the wave's LDS accesses only (__syncthreads
+// waits for its stores to global memory too, some 1500 cycles a step here).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+template <int C, int W>
+__device__ __forceinline__ void tridiag(double *__restrict__ A, int k, const EigWs &out) {
+    constexpr int Q = C == 3 ? kEigMaxLds / W : 64 * C / W;
+    constexpr int H = Q / 4 * 2;
+    __shared__ __align__(16) double row[64 * C], part[W][64 * C], own[W][64 * C];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    double *__restrict__ A = Ag;
-    if constexpr (IN_LDS) {
-        for (int64_t i = tid; i < (int64_t)k * k; i += kSolveThreads) lds_a[i] = Ag[i];
-        A = lds_a;
+    const __amdgpu_buffer_rsrc_t ab = square_buf(A, k);
+    auto held = [&](int q) { return 2 * (w + W * (q / 2)) + q % 2; };   // row of a[q]
+    double a[Q][C];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int i = held(q), l = lane + 64 * c;
+            a[q][c] = buf_d(ab, 8 * (i * k + l) | out_if(i, k) | out_if(l, k));
+        }
+    // row j to LDS by the wave that holds it
+    auto publish = [&](int j) {
+        if (w != j / 2 % W) return;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (held(q) == j)
+#pragma unroll
+                for (int c = 0; c < C; ++c) row[lane + 64 * c] = a[q][c];
+    };
+    publish(0);
+    lds_barrier();
+    for (int j = 0; j + 2 < k; ++j) {
+        double u[C], sg = 0.0;
+        const double x0 = row[j + 1];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int l = lane + 64 * c;
+            u[c] = l > j + 1 && l < k ? row[l] : 0.0;
+            sg = fma(u[c], u[c], sg);
+        }
+        sg = wave_sum(sg);
+        if (tid == 0) out.eig[j] = row[j];
+        if (sg == 0.0) {   // already reduced: H = I
+            if (tid == 0) {
+                out.off[j] = x0;
+                out.tau[j] = 0.0;
+            }
+            lds_barrier();
+        } else {
+            const double beta = -copysign(sqrt(fma(x0, x0, sg)), x0), u0 = x0 - beta;
+            const double g = -1.0 / (beta * u0);
+            // u by rows: zero for rows up to j and past k
+            double p[C] = {}, ui[Q];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (lane + 64 * c == j + 1) u[c] = u0;
+                own[w][lane + 64 * c] = u[c];
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < Q; ++q) ui[q] = own[w][held(q)];
+            // the first H of a wave's rows only until all waves' are reduced
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+                if (half || j < 2 * W * (H / 2))
+#pragma unroll
+                    for (int q = half ? H : 0; q < (half ? Q : H); ++q)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) p[c] = fma(a[q][c], ui[q], p[c]);
+#pragma unroll
+            for (int c = 0; c < C; ++c) part[w][lane + 64 * c] = p[c];
+            lds_barrier();
+            double pu = 0.0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                double t[W];
+#pragma unroll
+                for (int v = 0; v < W; ++v) t[v] = part[v][lane + 64 * c];
+#pragma unroll
+                for (int o = W / 2; o > 0; o /= 2)
+#pragma unroll
+                    for (int v = 0; v < o; ++v) t[v] += t[v + o];
+                p[c] = g * t[0];
+                pu = fma(p[c], u[c], pu);
+            }
+            const double K = 0.5 * g * wave_sum(pu);
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                p[c] = fma(-K, u[c], p[c]);
+                own[w][lane + 64 * c] = p[c];
+            }
+            __builtin_amdgcn_wave_barrier();
+            double wi[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) wi[q] = own[w][held(q)];
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+                if (half || j < 2 * W * (H / 2))
+#pragma unroll
+                    for (int q = half ? H : 0; q < (half ? Q : H); ++q)
+#pragma unroll
+                        for (int c = 0; c < C; ++c)
+                            a[q][c] = fma(-ui[q], p[c], fma(-wi[q], u[c], a[q][c]));
+            // the reflector, scaled to a first entry of 1, where k_eig_back reads it
+            if (w == j / 2 % W) {
+                const double sc = 1.0 / u0;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const int l = lane + 64 * c;
+                    if (l > j && l < k) A[(int64_t)j * k + l] = l == j + 1 ? 1.0 : u[c] * sc;
+                }
+                if (lane == 0) {
+                    out.off[j] = beta;
+                    out.tau[j] = -u0 / beta;
+                }
+            }
+        }
+        publish(j + 1);
+        lds_barrier();
     }
-    if constexpr (!IN_LDS)
-        for (int64_t i = tid; i < (int64_t)k * k; i += kSolveThreads)
-            Zt[i] = (i / k == i % k) ? 1.0 : 0.0;
-    __syncthreads();
+    if (tid == 0) {
+        const int j = max(k - 2, 0);
+        out.eig[j] = row[j];
+        out.tau[j] = out.tau[k - 1] = 0.0;
+        out.off[j] = k >= 2 ? row[k - 1] : 0.0;
+        out.off[k - 1] = 0.0;
+    }
+    lds_barrier();
+    if (k >= 2) publish(k - 1);
+    lds_barrier();
+    if (tid == 0) out.eig[k - 1] = row[k - 1];
+}
+template <int C>
+__global__ void __launch_bounds__(kTriDiagThreads)
+k_tridiag(double *__restrict__ A, int k, double *__restrict__ ws) {
+    tridiag<C, kTriDiagWaves>(A + (int64_t)blockIdx.x * k * k, k, eig_ws(ws, k, blockIdx.x));
+}
 
-    // ---- 1. Householder reduction.  Per step: every wave forms the
-    // reflector from row j; threads (row i, part q) sum parts of p = tau A v;
-    // thread i < m finishes p_i and writes v_i into row j (where phase 3
-    // reads it back, first entry 1); threads (column l, row group g) apply
-    // the rank-2 update.  Three block barriers per step.
+// Phase 1 for wider matrices, worked on in place in global memory.  Per step:
+// every wave forms the reflector from row j; threads (row i, part q) sum parts
+// of p = tau A v; thread i < m finishes p_i and writes v_i into row j (first
+// entry 1); threads (column l, row group g) apply the rank-2 update.  Three
+// block barriers per step.
+__global__ void __launch_bounds__(kSolveThreads)
+k_tridiag_wide(double *__restrict__ A, int k, double *__restrict__ ws) {
+    constexpr int MK = kEigMaxK;
+    __shared__ double pq[4 * MK];   // P x MK partial sums, then p (row 0) and v (row 1)
+    A += (int64_t)blockIdx.x * k * k;
+    const EigWs out = eig_ws(ws, k, blockIdx.x);
+    const int tid = threadIdx.x, lane = tid & 63;
     constexpr int P = kSolveThreads / MK < 4 ? kSolveThreads / MK : 4;   // parts per row sum
     constexpr int G = kSolveThreads / MK;                                 // row groups
-    double *pq = buf;   // P x MK partial sums, then p (row 0) and v (row 1)
     for (int j = 0; j + 2 < k; ++j) {
         const int m = k - j - 1;   // trailing indices j+1 .. k-1
         double *x = A + (int64_t)j * k + j + 1;
@@ -1306,14 +1432,14 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         for (int l = 1 + lane; l < m; l += 64) sg += x[l] * x[l];
         sg = wave_sum(sg);
         const double x0 = x[0];
-        if (tid == 0) dg[j] = A[(int64_t)j * k + j];
+        if (tid == 0) out.eig[j] = A[(int64_t)j * k + j];
         if (sg == 0.0) {   // already reduced: H = I
-            if (tid == 0) { eg[j] = x0; taus[j] = 0.0; }
+            if (tid == 0) { out.off[j] = x0; out.tau[j] = 0.0; }
             continue;
         }
         const double beta = -copysign(sqrt(x0 * x0 + sg), x0);
         const double tau = (beta - x0) / beta, sc = 1.0 / (x0 - beta);
-        if (tid == 0) { eg[j] = beta; taus[j] = tau; }
+        if (tid == 0) { out.off[j] = beta; out.tau[j] = tau; }
         {
             const int i = tid % MK, q = tid / MK, L = (m + P - 1) / P;
             if (q < P && i < m) {
@@ -1359,17 +1485,41 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         __syncthreads();
     }
     if (tid == 0) {
-        for (int j = (k >= 2 ? k - 2 : 0); j < k; ++j) dg[j] = A[(int64_t)j * k + j];
-        if (k >= 2) eg[k - 2] = A[(int64_t)(k - 2) * k + k - 1];
-        eg[k - 1] = 0.0;
-        taus[k - 1] = 0.0;
-        if (k >= 2) taus[k - 2] = 0.0;
-        s_more[0][0] = s_more[0][1] = s_more[1][0] = s_more[1][1] = 0;
+        for (int j = k - 2; j < k; ++j) {
+            out.eig[j] = A[(int64_t)j * k + j];
+            out.tau[j] = 0.0;
+        }
+        out.off[k - 2] = A[(int64_t)(k - 2) * k + k - 1];
+        out.off[k - 1] = 0.0;
     }
+}
+
+template <bool IN_LDS, int NT>
+__device__ __forceinline__ void tridiag_eig(int k, const EigWs &out) {
+    constexpr int MK = IN_LDS ? kEigMaxLds : kEigMaxK;
+    extern __shared__ double lds_a[];
+    __shared__ double dg[MK], eg[MK];
+    __shared__ double2 rot[2 * MK];   // the rotation buffers; after, vectors
+    double *buf = (double *)rot;      // of the merge
+    __shared__ double2 de_pad[2 * kChain + MK];
+    double2 *de = de_pad + 2 * kChain;   // the pairs (d, e) of the sweeps; then
+    int *idx = (int *)de_pad;            // merge: order, kept and deflated rows
+    __shared__ int s_lo[2][2], s_hi[2][2], s_more[2][2];   // [problem][buffer]
+    __shared__ double s_rho, s_unit, s_tol;
+    __shared__ int s_K, s_flip;
+    double *__restrict__ Zt = out.Zt;
+    // the wave index as a scalar, so that code under `w == 0` branches as a
+    // uniform wave
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if constexpr (!IN_LDS)
+        for (int64_t i = tid; i < (int64_t)k * k; i += NT)
+            Zt[i] = (i / k == i % k) ? 1.0 : 0.0;
+    for (int i = tid; i < k; i += NT) {
+        dg[i] = out.eig[i];
+        eg[i] = out.off[i];
+    }
+    if (tid == 0) s_more[0][0] = s_more[0][1] = s_more[1][0] = s_more[1][1] = 0;
     __syncthreads();
-    for (int i = tid; i < k; i += kSolveThreads) out.tau[i] = taus[i];
-    if constexpr (IN_LDS)
-        for (int64_t i = tid; i < (int64_t)k * k; i += kSolveThreads) Ag[i] = lds_a[i];
 
     // ---- 2. eigen-decomposition of the tridiagonal matrix T = (d, e).
     // Wave 0 scales (d, e) by a power of two to unit size (exact).  For
@@ -1382,9 +1532,8 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
     // k: one problem, waves 1.. apply.
     const int h = k >= kEigSplit ? k / 2 : k;
     const int np = h < k ? 2 : 1;
-    if constexpr (IN_LDS) {   // the identity in A's place: row i of its half's components
-        __syncthreads();
-        for (int i = tid; i < k * kZStride; i += kSolveThreads) {
+    if constexpr (IN_LDS) {   // the identity, row i of its half's components
+        for (int i = tid; i < k * kZStride; i += NT) {
             const int r = i / kZStride, c = i % kZStride;
             lds_a[i] = c == (r >= h ? r - h : r) ? 1.0 : 0.0;
         }
@@ -1441,16 +1590,16 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         }
         __builtin_amdgcn_s_setprio(0);
         if constexpr (IN_LDS) {
-            for (int i = tid; i < k * k; i += kSolveThreads) {
+            for (int i = tid; i < k * k; i += NT) {
                 const int r = i / k, c = i % k;
                 Zt[i] = (r >= h) == (c >= h) ? lds_a[r * kZStride + (c >= h ? c - h : c)] : 0.0;
             }
         }
-        for (int i = tid; i < k; i += kSolveThreads) dg[i] = de[i].x;
+        for (int i = tid; i < k; i += NT) dg[i] = de[i].x;
         __syncthreads();
     }
     if (np == 1) {
-        for (int i = tid; i < k; i += kSolveThreads) {
+        for (int i = tid; i < k; i += NT) {
             out.eig[i] = dg[i] / s_unit;
             out.kept[i] = i;
         }
@@ -1468,7 +1617,7 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         // of U; k_eig_back multiplies).
         int *ord = idx, *kept = idx + MK;
         double *dk = buf, *zk = buf + MK, *tau = buf + 2 * MK, *zh = buf + 3 * MK;
-        for (int i = tid; i < k; i += kSolveThreads)
+        for (int i = tid; i < k; i += NT)
             eg[i] = i < h ? Zt[(int64_t)i * k + h - 1] : Zt[(int64_t)i * k + h];
         __syncthreads();
         if (w == 0) {
@@ -1492,14 +1641,14 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         {
             const double sz = zh[0];
             const bool flip = s_flip != 0;
-            for (int i = tid; i < k; i += kSolveThreads) {
+            for (int i = tid; i < k; i += NT) {
                 eg[i] *= sz;
                 if (flip) dg[i] = -dg[i];
             }
         }
         __syncthreads();
         // ascending order of the poles (ties by index)
-        for (int i = tid; i < k; i += kSolveThreads) {
+        for (int i = tid; i < k; i += NT) {
             const double di = dg[i];
             int r = 0;
             for (int j = 0; j < k; ++j) r += (dg[j] < di || (dg[j] == di && j < i)) ? 1 : 0;
@@ -1577,7 +1726,7 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         __syncthreads();
         const int K = s_K;
         const double rho = s_rho;
-        for (int j = tid; j < K; j += kSolveThreads) {
+        for (int j = tid; j < K; j += NT) {
             dk[j] = dg[kept[j]];
             zk[j] = eg[kept[j]];
         }
@@ -1597,9 +1746,9 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
             x += dpp_d<0x4E>(x);
             return x + dpp_d<0x141>(x);
         };
-        for (int i = tid; i < K; i += kSolveThreads) zh[i] = rho * zk[i] * zk[i];
+        for (int i = tid; i < K; i += NT) zh[i] = rho * zk[i] * zk[i];
         __syncthreads();
-        for (int j = tid / LR; j < K; j += kSolveThreads / LR) {
+        for (int j = tid / LR; j < K; j += NT / LR) {
             // 1 + rho sum z^2 / delta, delta_i = (dk_i - dk_o) - t, and its
             // derivative over the poles up to j and past j
             auto secular = [&](int oo, double tt, double &below, double &above) {
@@ -1661,7 +1810,7 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         }
         __syncthreads();
         // recomputed weights: zh_i^2 = prod_j (lambda_j - dk_i) / (rho prod_l!=i (dk_l - dk_i))
-        for (int i = tid / LR; i < K; i += kSolveThreads / LR) {
+        for (int i = tid / LR; i < K; i += NT / LR) {
             auto lmd = [&](int j) { return (dk[ord[j]] - dk[i]) + tau[j]; };   // lambda_j - dk_i
             double P = 1.0;
             for (int j = sub; j < K - 1; j += LR) P *= lmd(j) / (dk[j < i ? j : j + 1] - dk[i]);
@@ -1676,7 +1825,7 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
         // eigenvalues (unscaled, sign restored) next to the deflated ones
         {
             const double sgn = s_flip ? -1.0 : 1.0, un = s_unit;
-            for (int j = tid / LR; j < K; j += kSolveThreads / LR) {
+            for (int j = tid / LR; j < K; j += NT / LR) {
                 const double dj = dk[ord[j]], tj = tau[j];
                 double nrm = 0.0;
                 for (int i = sub; i < K; i += LR) {
@@ -1687,7 +1836,7 @@ k_sym_eig(double *__restrict__ Ag, int k, double *__restrict__ ws) {
                 const double inv = 1.0 / sqrt(lanes_sum(nrm));
                 for (int i = sub; i < K; i += LR) out.U[(int64_t)i * k + j] *= inv;
             }
-            for (int j = tid; j < k; j += kSolveThreads) {
+            for (int j = tid; j < k; j += NT) {
                 out.eig[j] = sgn * (j < K ? dk[ord[j]] + tau[j] : dg[kept[j]]) / un;
                 out.kept[j] = kept[j];
             }
@@ -1717,22 +1866,18 @@ __host__ __device__ constexpr int back_ld(int nt) { return 16 * nt + 2; }
 inline size_t back_lds(int maxt) {
     return sizeof(double) * (size_t)(maxt * kBlk + 2 * 16 * back_ld(maxt));
 }
-template <int MAXT>
-__global__ void __launch_bounds__(kBackThreads, 1)
-k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__restrict__ V,
-           double *__restrict__ lam) {
+template <int MAXT, int WAVES>
+__device__ __forceinline__ void eig_back(double *__restrict__ A, int k, const EigWs &in,
+                                         double *__restrict__ V, double *__restrict__ lam,
+                                         int block) {
     static_assert(MAXT % kBackGroup == 0);
     extern __shared__ double lds_a[];
-    const int64_t batch = blockIdx.y;
-    A += batch * k * k;
-    V += batch * k * k;
-    lam += batch * k;
-    const EigWs in = eig_ws(ws, k, batch);
     constexpr int LD = back_ld(MAXT), VB = 16 * LD;
     double *Ts = lds_a, *Vs = lds_a + MAXT * kBlk;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kr = lane >> 4, c16 = lane & 15;
-    const int c = 16 * (kBackWaves * (int)blockIdx.x + w) + c16;   // this lane's eigenvector
+    const int c = 16 * (WAVES * block + w) + c16;   // this lane's eigenvector
+    const bool work = c - c16 < k;                  // the wave has a strip
     const int nblk = (k - 2 + 15) / 16;                            // blocks of reflectors
     const __amdgpu_buffer_rsrc_t ab = square_buf(A, k), zb = square_buf(in.Zt, k),
                                  ub = square_buf(in.U, k);
@@ -1742,7 +1887,7 @@ k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__res
     };
 
     // T of each block: V^T V by matrix steps, then row c16 of T by its lane
-    for (int b = w; b < nblk; b += kBackWaves) {
+    for (int b = w; b < nblk; b += WAVES) {
         v4d g[kBackGroup] = {};
         for (int I0 = b; I0 * 16 < k; I0 += kBackGroup) {
             double x[kBackGroup][4];
@@ -1779,7 +1924,7 @@ k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__res
     // the eigenvectors of the tridiagonal matrix
     const int K = *in.K;
     v4d z[MAXT];
-    {
+    if (work) {
         const int kc = c < k ? in.kept[c] : 0, copied = out_if(c, k) | out_if(K, c + 1);
 #pragma unroll
         for (int I = 0; I < MAXT; ++I)
@@ -1815,6 +1960,7 @@ k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__res
 
     // reflectors, block nblk - 1 first
     const int sr = tid >> 4, si = tid & 15;   // staging: row, column of a tile
+    const bool stages = w < 4;
     double st[MAXT];
     auto fetch = [&](int b) {
 #pragma unroll
@@ -1824,44 +1970,48 @@ k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__res
 #pragma unroll
         for (int I = 0; I < MAXT; ++I) Vs[(b & 1) * VB + sr * LD + 16 * I + si] = st[I];
     };
-    fetch(nblk - 1);
-    store(nblk - 1);
+    if (stages) {
+        fetch(nblk - 1);
+        store(nblk - 1);
+    }
     __syncthreads();
     for (int b = nblk - 1; b >= 0; --b) {
-        if (b > 0) fetch(b - 1);
+        if (stages && b > 0) fetch(b - 1);
         const double *v = Vs + (b & 1) * VB, *T = Ts + b * kBlk;
-        v4d p[kBackGroup] = {};
+        if (work) {
+            v4d p[kBackGroup] = {};
 #pragma unroll
-        for (int I0 = 0; I0 < MAXT; I0 += kBackGroup) {
-            if (I0 + kBackGroup <= b || 16 * I0 >= k) continue;
+            for (int I0 = 0; I0 < MAXT; I0 += kBackGroup) {
+                if (I0 + kBackGroup <= b || 16 * I0 >= k) continue;
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+                for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int u = 0; u < kBackGroup; ++u)
-                    p[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        v[c16 * LD + 16 * (I0 + u) + kr + 4 * t], z[I0 + u][t], p[u], 0, 0, 0);
-        }
-        v4d q = {};
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            q = __builtin_amdgcn_mfma_f64_16x16x4f64(T[c16 * 17 + kr + 4 * t],
-                                                     -(p[0][t] + p[1][t] + p[2][t]), q, 0, 0, 0);
-#pragma unroll
-        for (int I0 = 0; I0 < MAXT; I0 += kBackGroup) {
-            if (I0 + kBackGroup <= b || 16 * I0 >= k) continue;
+                    for (int u = 0; u < kBackGroup; ++u)
+                        p[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            v[c16 * LD + 16 * (I0 + u) + kr + 4 * t], z[I0 + u][t], p[u], 0, 0, 0);
+            }
+            v4d q = {};
 #pragma unroll
             for (int t = 0; t < 4; ++t)
+                q = __builtin_amdgcn_mfma_f64_16x16x4f64(T[c16 * 17 + kr + 4 * t],
+                                                         -(p[0][t] + p[1][t] + p[2][t]), q, 0, 0, 0);
 #pragma unroll
-                for (int u = 0; u < kBackGroup; ++u)
-                    z[I0 + u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        v[(kr + 4 * t) * LD + 16 * (I0 + u) + c16], q[t], z[I0 + u], 0, 0, 0);
+            for (int I0 = 0; I0 < MAXT; I0 += kBackGroup) {
+                if (I0 + kBackGroup <= b || 16 * I0 >= k) continue;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int u = 0; u < kBackGroup; ++u)
+                        z[I0 + u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            v[(kr + 4 * t) * LD + 16 * (I0 + u) + c16], q[t], z[I0 + u], 0, 0, 0);
+            }
         }
-        if (b > 0) store(b - 1);
+        if (stages && b > 0) store(b - 1);
         __syncthreads();
     }
 
     // rank by decreasing eigenvalue, ties by index; four lanes share a column
-    if (c - c16 >= k) return;
+    if (!work) return;
     const double lc = c < k ? in.eig[c] : 0.0;
     int rank = 0;
     for (int j = kr; j < k; j += 4) {
@@ -1879,6 +2029,36 @@ k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__res
             const int i = 16 * I + kr + 4 * t;
             if (i < k) V[(int64_t)i * k + rank] = z[I][t];
         }
+}
+
+template <bool IN_LDS>
+__global__ void __launch_bounds__(kSolveThreads) k_sym_eig(int k, double *__restrict__ ws) {
+    tridiag_eig<IN_LDS, kSolveThreads>(k, eig_ws(ws, k, blockIdx.x));
+}
+
+template <int MAXT>
+__global__ void __launch_bounds__(kBackThreads, 1)
+k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__restrict__ V,
+           double *__restrict__ lam) {
+    const int64_t b = blockIdx.y;
+    eig_back<MAXT, kBackWaves>(A + b * k * k, k, eig_ws(ws, k, b), V + b * k * k, lam + b * k,
+                               (int)blockIdx.x);
+}
+
+// All three phases in one launch for matrices that are not torn, whose phases
+// are as short as a launch (k = 3: 23 us in three launches, 16 in one; k = 16:
+// 103 and 93).
+__global__ void __launch_bounds__(kTriDiagThreads)
+k_sym_eig_small(double *__restrict__ A, int k, double *__restrict__ ws, double *__restrict__ V,
+                double *__restrict__ lam) {
+    const int64_t b = blockIdx.x;
+    const EigWs w = eig_ws(ws, k, b);
+    A += b * k * k;
+    tridiag<1, kTriDiagWaves>(A, k, w);
+    __syncthreads();
+    tridiag_eig<true, kTriDiagThreads>(k, w);
+    __syncthreads();
+    eig_back<3, kTriDiagWaves>(A, k, w, V + b * k * k, lam + b * k, 0);
 }
 
 __global__ void k_eig_weights(const double *__restrict__ V, const double *__restrict__ lam,
@@ -2158,33 +2338,28 @@ lne_status sym_eig(lne_ctx *ctx, double *C, int32_t k, double *V, double *lam, i
     // vw_ws (if given) holds sym_eig_ws_doubles(k, nb) doubles
     if (vw_ws) vw.p = vw_ws, vw.ctx = nullptr;
     else LNE_TRY(alloc(ctx, vw, sizeof(double) * sym_eig_ws_doubles(k, nb)));
-    // the LDS variant when k^2 doubles fit next to the kernel's static arrays
-    static int lds_limit = -1;
-    if (lds_limit < 0) {
-        int dev = 0, bytes = 0;
-        lds_limit = 0;
-        int base = 0;
-        hipFuncAttributes fa;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&base, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
-                hipSuccess &&
-            hipDeviceGetAttribute(&bytes, hipDeviceAttributeSharedMemPerBlockOptin, dev) ==
-                hipSuccess &&
-            hipFuncGetAttributes(&fa, (const void *)k_sym_eig<true>) == hipSuccess &&
-            (bytes = bytes > base ? bytes : base) > (int)fa.sharedSizeBytes &&
-            hipFuncSetAttribute((const void *)k_sym_eig<true>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                bytes - (int)fa.sharedSizeBytes) == hipSuccess)
-            lds_limit = bytes - (int)fa.sharedSizeBytes;
-        (void)hipGetLastError();
+    double *ws = vw.as<double>();
+    if (k < kEigSplit) {
+        const size_t lds = std::max(sizeof(double) * (size_t)k * kZStride, back_lds(3));
+        Launch L(ctx, "sym_eig");
+        k_sym_eig_small<<<nb, kTriDiagThreads, lds, ctx->stream>>>(C, k, ws, V, lam);
+        return check_launch(ctx, "sym_eig");
     }
-    const size_t need = sizeof(double) * (size_t)k * std::max(k, kZStride);
-    if (k <= kEigMaxLds && need <= (size_t)lds_limit) {
+    {
         Launch L(ctx, "sym_eig");
-        k_sym_eig<true><<<nb, kSolveThreads, need, ctx->stream>>>(C, k, vw.as<double>());
-    } else {
+        if (k <= 64) k_tridiag<1><<<nb, kTriDiagThreads, 0, ctx->stream>>>(C, k, ws);
+        else if (k <= 128) k_tridiag<2><<<nb, kTriDiagThreads, 0, ctx->stream>>>(C, k, ws);
+        else if (k <= kEigMaxLds) k_tridiag<3><<<nb, kTriDiagThreads, 0, ctx->stream>>>(C, k, ws);
+        else k_tridiag_wide<<<nb, kSolveThreads, 0, ctx->stream>>>(C, k, ws);
+    }
+    LNE_TRY(check_launch(ctx, "sym_eig"));
+    // the halves' eigenvectors in LDS where they fit
+    const size_t need = sizeof(double) * (size_t)k * kZStride;
+    if (k <= kEigMaxLds) LNE_TRY(lds_opt_in(ctx, (const void *)k_sym_eig<true>, need));
+    {
         Launch L(ctx, "sym_eig");
-        k_sym_eig<false><<<nb, kSolveThreads, 0, ctx->stream>>>(C, k, vw.as<double>());
+        if (k <= kEigMaxLds) k_sym_eig<true><<<nb, kSolveThreads, need, ctx->stream>>>(k, ws);
+        else k_sym_eig<false><<<nb, kSolveThreads, 0, ctx->stream>>>(k, ws);
     }
     LNE_TRY(check_launch(ctx, "sym_eig"));
     const int nt = (k + 15) / 16;
@@ -2193,8 +2368,7 @@ lne_status sym_eig(lne_ctx *ctx, double *C, int32_t k, double *V, double *lam, i
     do {                                                                                       \
         LNE_TRY(lds_opt_in(ctx, (const void *)k_eig_back<M>, back_lds(M)));                    \
         Launch L(ctx, "sym_eig");                                                              \
-        k_eig_back<M><<<grid, kBackThreads, back_lds(M), ctx->stream>>>(C, k, vw.as<double>(), \
-                                                                        V, lam);               \
+        k_eig_back<M><<<grid, kBackThreads, back_lds(M), ctx->stream>>>(C, k, ws, V, lam);     \
     } while (0)
     if (nt <= 3) LNE_EB(3);
     else if (nt <= 9) LNE_EB(9);
