@@ -174,9 +174,9 @@ static void host_plan(const lne_params *p, int64_t n, int64_t n_arcs, SamplePlan
     pl.seed = p->seed;
     pl.T = p->T;
     pl.wt = nullptr;
-    pl.cw = nullptr;
-    pl.guide = nullptr;
     pl.ea = nullptr;
+    pl.arcs = nullptr;
+    pl.rows = nullptr;
     if (m > 0) {
         pl.base = p->M / (uint64_t)m;
         const uint64_t rem = p->M % (uint64_t)m;
@@ -251,23 +251,24 @@ static double range_bytes(uint64_t entries) { return 36.0 * (double)entries; }
 
 struct Sampler {
     SamplePlan pl;
-    Buf eu, ev, wc, wo, ea, cw, guide;
+    Buf eu, ev, wc, wo, ea, arcs, rows;
     int64_t m = 0, nw = 0;
     uint64_t attempted = 0, accepted = 0;
 };
 
 // Edge list of the sampler and, on a weighted graph, its weight tables: the
-// prefix sums of the arc weights and each edge's weight.
+// walk steps' records and each edge's weight.
 static lne_status sampler_edges(lne_ctx *ctx, const Graph *g, Sampler &S) {
     LNE_TRY(build_edges(ctx, g, S.eu, S.ev, S.m, g->weight ? &S.ea : nullptr));
     if (!g->weight) return LNE_OK;
     uint64_t vol = 0;
-    LNE_TRY(weight_info(ctx, g, S.cw, &vol));
-    LNE_TRY(weight_guide(ctx, g, S.cw.as<uint64_t>(), S.guide));
+    Buf cw(ctx);
+    LNE_TRY(weight_info(ctx, g, cw, &vol));
+    LNE_TRY(weight_guide(ctx, g, cw.as<uint64_t>(), S.arcs, S.rows));
     S.pl.wt = g->weight;
-    S.pl.cw = S.cw.as<uint64_t>();
     S.pl.ea = S.ea.as<uint32_t>();
-    S.pl.guide = S.guide.as<uint32_t>();
+    S.pl.arcs = S.arcs.as<uint4>();
+    S.pl.rows = S.rows.as<uint4>();
     return LNE_OK;
 }
 

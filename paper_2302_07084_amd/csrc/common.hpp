@@ -143,9 +143,9 @@ struct SamplePlan {
                           // channels), instead of both orientations
     // weighted graphs (all null on an unweighted one)
     const uint32_t *wt;   // arc weights A
-    const uint64_t *cw;   // cw[k] = sum of wt[0..k), n_arcs + 1 entries
     const uint32_t *ea;   // weight of edge e (u < v arcs in CSR order)
-    const uint32_t *guide;  // guide table of each row (weight_guide)
+    const uint4 *arcs;    // a walk step's record of each arc (weight_guide)
+    const uint4 *rows;    // and of each vertex
 };
 
 lne_status make_plan(lne_ctx *ctx, const lne_params *p, int64_t n, int64_t n_arcs,
@@ -161,13 +161,16 @@ lne_status build_edges(lne_ctx *ctx, const Graph *g, Buf &eu, Buf &ev, int64_t m
 // weights; EINVAL on a zero weight, EUNSUPPORTED when a weighted degree or vol
 // reaches 2^32.  Synchronises the stream.
 lne_status weight_info(lne_ctx *ctx, const Graph *g, Buf &cw, uint64_t *vol);
-// Guide table of the weighted walk step (one uint32 per arc): for row x with
-// k arcs and weighted degree W, entry b (stored at rp[x] + b) is the local
-// index of the arc whose cumulative-weight slice holds ceil(b W / k).  A step
-// drawing t in [0, W) starts its scan at entry floor(t k / W), at or before
-// the arc that holds t, and passes about one slice on average (the guide
-// tables of Chen and Asau's cutpoint method).  cw from weight_info.
-lne_status weight_guide(lne_ctx *ctx, const Graph *g, const uint64_t *cw, Buf &guide);
+// Records of the weighted walk step, 16 bytes each, so that a step reads three
+// cache lines and not eight.  arcs: (end of the arc's slice of the row's
+// cumulative weights, weight, column, guide entry); rows: (offset of the first
+// arc, low and high word, arcs k, weighted degree W).  Guide entry b of row x
+// (in the record of its arc b) is the local index of the arc whose slice holds
+// ceil(b W / k).  A step drawing t in [0, W) starts its scan at entry floor(t k
+// / W) or before, at or before the arc that holds t, and passes about one slice
+// on average (the guide tables of Chen and Asau's cutpoint method).  cw from
+// weight_info.
+lne_status weight_guide(lne_ctx *ctx, const Graph *g, const uint64_t *cw, Buf &arcs, Buf &rows);
 
 // Sparse-sign test matrix (LNE_FLAG_SPARSE_OMEGA): kSparseOmega signed
 // column entries per row, int16 sign (column + 1), one 16-byte vector per row.

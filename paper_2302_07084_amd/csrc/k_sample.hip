@@ -22,8 +22,8 @@
 //
 // Weighted graphs (positive integer weights A): p_e = min(1, C A_uv (1/d_u +
 // 1/d_v)) with weighted degrees; a walk step from x takes t = z mod d_x and
-// the neighbour whose slice of the row's cumulative weights holds t (binary
-// search in the prefix sums cw); an accepted sample weighs h / p_e with
+// the neighbour whose slice of the row's cumulative weights holds t (scan from
+// a guide table's entry); an accepted sample weighs h / p_e with
 // h = r / sum_j 1/A_j over its path's edges (the centre edge, the steps from
 // u, then the steps from v), NetSMF's path estimator, 1 on unweighted graphs.
 #include "common.hpp"
@@ -67,7 +67,7 @@ __device__ __forceinline__ Coin edge_coin(const SamplePlan &pl, uint32_t A, uint
 template <bool W>
 __device__ __forceinline__ uint64_t vdeg(const SamplePlan &pl, const int64_t *__restrict__ rp,
                                          int64_t x) {
-    if constexpr (W) return pl.cw[rp[x + 1]] - pl.cw[rp[x]];
+    if constexpr (W) return pl.rows[x].w;
     else return (uint64_t)(rp[x + 1] - rp[x]);
 }
 
@@ -103,29 +103,36 @@ __device__ __forceinline__ int draw_r(const SamplePlan &pl, uint32_t z) {
     return r;
 }
 
+// Local index of the bucket of t at or before floor(t k / deg): the quotient in
+// double precision, taken down by more than its rounding (three roundings of
+// 2^-53), so never past it; one scan step more where it falls short.
+__device__ __forceinline__ uint32_t guide_bucket(uint32_t t, uint32_t k, uint32_t deg) {
+    const double q = (double)((uint64_t)t * k) / (double)deg;
+    return (uint32_t)(q * (1.0 - 0x1p-50));
+}
+
 // One walk step from x with word z; on a weighted graph inv += 1 / A of the
 // arc taken.
 template <bool W>
 __device__ __forceinline__ int32_t walk_step(const SamplePlan &pl, const int64_t *__restrict__ rp,
                                              const int32_t *__restrict__ col, int32_t x,
                                              uint32_t z, double &inv) {
-    const int64_t beg = rp[x], end = rp[x + 1];
     if constexpr (!W) {
+        const int64_t beg = rp[x], end = rp[x + 1];
         const uint32_t deg = (uint32_t)(end - beg);
         return deg ? col[beg + (int64_t)(z % deg)] : x;   // a sink (asymmetric input) holds
     } else {
-        const uint64_t base = pl.cw[beg];
-        const uint32_t deg = (uint32_t)(pl.cw[end] - base);   // < 2^32 (validated)
+        const uint4 row = pl.rows[x];
+        const uint32_t k = row.z, deg = row.w;
         if (deg == 0) return x;
-        const uint64_t t = base + (uint64_t)(z % deg);
-        // the arc k of the row with cw[k] <= t < cw[k + 1]: from the guide
-        // entry of t's bucket forward
-        const uint64_t k = (uint64_t)(end - beg);
-        const uint64_t bkt = (t - base) * k / deg;
-        int64_t i = beg + (int64_t)min((uint64_t)pl.guide[beg + (int64_t)bkt], k - 1);
-        while (i < end - 1 && pl.cw[i + 1] <= t) ++i;
-        inv += 1.0 / (double)pl.wt[i];
-        return col[i];
+        // the arc whose slice holds t: from the guide entry of t's bucket forward
+        const uint4 *arc = pl.arcs + (int64_t)(((uint64_t)row.y << 32) | row.x);
+        const uint32_t t = z % deg;
+        uint32_t i = min(arc[guide_bucket(t, k, deg)].w, k - 1);
+        uint4 a = arc[i];
+        while (i < k - 1 && a.x <= t) a = arc[++i];
+        inv += 1.0 / (double)a.y;
+        return (int32_t)a.z;
     }
 }
 
@@ -506,9 +513,12 @@ k_sample_emit(SamplePlan pl, const int64_t *__restrict__ rp, const int32_t *__re
         }
     } else {
         // the weighted walk, kWalkQ slots at a time as above: each level of a
-        // step's dependent loads (row bounds, cumulative weights at them, the
-        // guide entry, the arc's weight and column) is requested for every
-        // slot before the next level; each slot keeps its own path factor
+        // step's dependent loads (the vertex' record, the guide entry, the
+        // arc's record) is requested for every slot before the next level;
+        // each slot keeps its own path factor.  Bound by the lines a step
+        // reads at random: with offsets, prefix sums, guide, weights and
+        // columns in arrays of their own (eight lines a step) this pass took
+        // 9.4 ms at 2 10^7 edges and 8 10^7 slots, now 5.7.
         const double inv0 = e < m ? 1.0 / (double)pl.ea[e] : 1.0;
         for (int64_t jj = 0; jj < pl.J; jj += kWalkQ) {
             int32_t x[kWalkQ], y[kWalkQ];
@@ -559,45 +569,38 @@ k_sample_emit(SamplePlan pl, const int64_t *__restrict__ rp, const int32_t *__re
                     }
                     cur[q] = act[q] ? (i < split[q] ? x[q] : y[q]) : u;
                 }
-                int64_t beg[kWalkQ], end[kWalkQ];
+                uint4 row[kWalkQ];
 #pragma unroll
-                for (int q = 0; q < kWalkQ; ++q) { beg[q] = rp[cur[q]]; end[q] = rp[cur[q] + 1]; }
-                uint64_t base[kWalkQ], top[kWalkQ];
-#pragma unroll
-                for (int q = 0; q < kWalkQ; ++q) { base[q] = pl.cw[beg[q]]; top[q] = pl.cw[end[q]]; }
-                // the arc k of the row with cw[k] <= t < cw[k + 1]: from the
-                // guide entry of t's bucket forward (as in walk_step)
-                uint32_t deg[kWalkQ];
-                uint64_t tt[kWalkQ];
-                int64_t ai[kWalkQ];
+                for (int q = 0; q < kWalkQ; ++q) row[q] = pl.rows[cur[q]];
+                // the arc whose slice holds t: from the guide entry of t's
+                // bucket forward (as in walk_step)
+                uint32_t deg[kWalkQ], tt[kWalkQ], ai[kWalkQ];
+                int64_t beg[kWalkQ];
+                const int64_t last = 2 * m - 1;
 #pragma unroll
                 for (int q = 0; q < kWalkQ; ++q) {
-                    deg[q] = (uint32_t)(top[q] - base[q]);   // < 2^32 (validated)
-                    const uint64_t k = (uint64_t)(end[q] - beg[q]);
-                    tt[q] = base[q] + (uint64_t)(deg[q] ? z[q] % deg[q] : 0u);
-                    const uint64_t bkt = deg[q] ? (tt[q] - base[q]) * k / deg[q] : 0;
-                    ai[q] = deg[q] ? beg[q] + (int64_t)min((uint64_t)pl.guide[beg[q] + (int64_t)bkt],
-                                                           k - 1)
-                                   : beg[q];
+                    beg[q] = (int64_t)(((uint64_t)row[q].y << 32) | row[q].x);
+                    deg[q] = row[q].w;
+                    tt[q] = deg[q] ? z[q] % deg[q] : 0u;
+                    ai[q] = deg[q] ? guide_bucket(tt[q], row[q].z, deg[q]) : 0u;
                 }
 #pragma unroll
                 for (int q = 0; q < kWalkQ; ++q)
-                    if (act[q] && deg[q])
-                        while (ai[q] < end[q] - 1 && pl.cw[ai[q] + 1] <= tt[q]) ++ai[q];
-                uint32_t wa[kWalkQ];
-                int32_t nb[kWalkQ];
+                    ai[q] = deg[q] ? min(pl.arcs[min(beg[q] + ai[q], last)].w, row[q].z - 1) : 0u;
+                uint4 arc[kWalkQ];
 #pragma unroll
-                for (int q = 0; q < kWalkQ; ++q) {
-                    const int64_t at = min(ai[q], 2 * m - 1);
-                    wa[q] = pl.wt[at];
-                    nb[q] = col[at];
-                }
+                for (int q = 0; q < kWalkQ; ++q) arc[q] = pl.arcs[min(beg[q] + ai[q], last)];
+#pragma unroll
+                for (int q = 0; q < kWalkQ; ++q)
+                    if (act[q])
+                        while (ai[q] + 1 < row[q].z && arc[q].x <= tt[q])
+                            arc[q] = pl.arcs[beg[q] + ++ai[q]];
 #pragma unroll
                 for (int q = 0; q < kWalkQ; ++q) {
                     if (act[q] && deg[q]) {
-                        inv[q] += 1.0 / (double)wa[q];
-                        if (i < split[q]) x[q] = nb[q];
-                        else y[q] = nb[q];
+                        inv[q] += 1.0 / (double)arc[q].y;
+                        if (i < split[q]) x[q] = (int32_t)arc[q].z;
+                        else y[q] = (int32_t)arc[q].z;
                     }
                     // a sink (asymmetric input) holds
                 }
@@ -809,29 +812,39 @@ __global__ void k_weight_check(const int64_t *__restrict__ rp, const uint32_t *_
 // value ceil(b W / k) lies in the slice [s, e) of the arcs with
 // B(s) <= b < B(e), B(s) = number of buckets whose value is below s =
 // floor((s - 1) k / W) + 1 (0 for s = 0); B(W) = k as weights are >= 1.
-__global__ void k_guide(const int64_t *__restrict__ rp, const uint64_t *__restrict__ cw,
-                        int64_t n, uint32_t *__restrict__ guide) {
+__global__ void k_guide(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+                        const uint32_t *__restrict__ wt, const uint64_t *__restrict__ cw,
+                        int64_t n, uint4 *__restrict__ arcs, uint4 *__restrict__ rows) {
     const int64_t u = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kValLanes;
     const int sub = threadIdx.x % kValLanes;
     if (u >= n) return;
     const int64_t b0 = rp[u], e0 = rp[u + 1];
     const uint64_t k = (uint64_t)(e0 - b0);
-    if (k == 0) return;
     const uint64_t base = cw[b0], W = cw[e0] - base;
+    if (sub == 0)
+        rows[u] = make_uint4((uint32_t)b0, (uint32_t)((uint64_t)b0 >> 32), (uint32_t)k,
+                             (uint32_t)W);
+    if (k == 0) return;
     for (int64_t i = sub; i < (int64_t)k; i += kValLanes) {
         const uint64_t s = cw[b0 + i] - base, e = cw[b0 + i + 1] - base;
+        uint32_t *a = reinterpret_cast<uint32_t *>(arcs + b0 + i);
+        a[0] = (uint32_t)e;
+        a[1] = wt[b0 + i];
+        a[2] = (uint32_t)col[b0 + i];
         const uint64_t lo = s == 0 ? 0 : (s - 1) * k / W + 1;
         const uint64_t hi = min((e - 1) * k / W + 1, k);
-        for (uint64_t b = lo; b < hi; ++b) guide[b0 + (int64_t)b] = (uint32_t)i;
+        for (uint64_t b = lo; b < hi; ++b)
+            reinterpret_cast<uint32_t *>(arcs + b0 + (int64_t)b)[3] = (uint32_t)i;
     }
 }
 
-lne_status weight_guide(lne_ctx *ctx, const Graph *g, const uint64_t *cw, Buf &guide) {
-    LNE_TRY(alloc(ctx, guide, sizeof(uint32_t) * (size_t)(g->n_arcs > 0 ? g->n_arcs : 1)));
+lne_status weight_guide(lne_ctx *ctx, const Graph *g, const uint64_t *cw, Buf &arcs, Buf &rows) {
+    LNE_TRY(alloc(ctx, arcs, sizeof(uint4) * (size_t)(g->n_arcs > 0 ? g->n_arcs : 1)));
+    LNE_TRY(alloc(ctx, rows, sizeof(uint4) * (size_t)(g->n > 0 ? g->n : 1)));
     if (g->n > 0) {
         Launch L(ctx, "weight_guide");
         k_guide<<<grid_of(g->n * kValLanes, 256), 256, 0, ctx->stream>>>(
-            g->row_ptr, cw, g->n, guide.as<uint32_t>());
+            g->row_ptr, g->col, g->weight, cw, g->n, arcs.as<uint4>(), rows.as<uint4>());
     }
     return check_launch(ctx, "weight_guide");
 }

@@ -83,6 +83,28 @@ def test_weighted_slots_skewed_weights_bit_exact(lne, ctx, graph):
     np.testing.assert_array_equal(w[e, j], ref["w"])
 
 
+@pytest.mark.parametrize("weights", ["equal", "mixed"])
+def test_weighted_slots_bit_exact_near_the_largest_degree(lne, ctx, weights):
+    """A hub whose weighted degree is just under 2^31 (the volume's limit is
+    2^32): the bucket of a draw is a quotient of 41-bit numbers, and with equal
+    weights every slice ends where a bucket does."""
+    g = gs.star(1000)
+    rows = np.repeat(np.arange(g.n), np.diff(g.rowptr))
+    leaf = np.maximum(rows, g.col)
+    w = np.full(len(g.col), 2_147_000) if weights == "equal" else 2_147_000 - leaf * leaf % 1999
+    g = type(g)(g.n, g.rowptr, g.col, g.labels, g.name, w.astype(np.uint32))
+    p = gs.params(T=4, s=[0.1, 0.3, 0.3, 0.3], M_per_m=20, C=None, m=g.m, seed=11)
+    rp, col = to_dev(g)
+    out = lne.sample_slots(ctx, rp, col, p, 0, g.m, weight=_dev_w(g))
+    S = out["S"]
+    ref = oracle.sample_slots(g, p)
+    e, j = ref["e"], ref["j"].astype(np.int64)
+    for key in ("a", "b", "r"):
+        np.testing.assert_array_equal(out[key].cpu().numpy().reshape(-1, S)[e, j], ref[key])
+    w = out["w"].cpu().numpy().view(np.uint64).reshape(-1, S)
+    np.testing.assert_array_equal(w[e, j], ref["w"])
+
+
 def test_weighted_counts_and_trunc_log(lne, ctx, wtiny):
     g, p = wtiny
     rp, col = to_dev(g)
