@@ -256,11 +256,15 @@ struct Sampler {
     uint64_t attempted = 0, accepted = 0;
 };
 
-// Edge list of the sampler and, on a weighted graph, its weight tables: the
-// walk steps' records and each edge's weight.
+// Edge list of the sampler and its tables: the walk steps' records and, on a
+// weighted graph, each edge's weight.
 static lne_status sampler_edges(lne_ctx *ctx, const Graph *g, Sampler &S) {
     LNE_TRY(build_edges(ctx, g, S.eu, S.ev, S.m, g->weight ? &S.ea : nullptr));
-    if (!g->weight) return LNE_OK;
+    if (!g->weight) {
+        LNE_TRY(row_records(ctx, g, S.rows));
+        S.pl.rows = S.rows.as<uint4>();
+        return LNE_OK;
+    }
     uint64_t vol = 0;
     Buf cw(ctx);
     LNE_TRY(weight_info(ctx, g, cw, &vol));

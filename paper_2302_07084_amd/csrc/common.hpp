@@ -141,11 +141,11 @@ struct SamplePlan {
     int32_t upper;        // emit one entry per sample, (min, max) of its two
                           // endpoints (the upper triangle; no row filter, no
                           // channels), instead of both orientations
+    const uint4 *rows;    // a walk step's record of each vertex (row_records, weight_guide)
     // weighted graphs (all null on an unweighted one)
     const uint32_t *wt;   // arc weights A
     const uint32_t *ea;   // weight of edge e (u < v arcs in CSR order)
     const uint4 *arcs;    // a walk step's record of each arc (weight_guide)
-    const uint4 *rows;    // and of each vertex
 };
 
 lne_status make_plan(lne_ctx *ctx, const lne_params *p, int64_t n, int64_t n_arcs,
@@ -161,6 +161,9 @@ lne_status build_edges(lne_ctx *ctx, const Graph *g, Buf &eu, Buf &ev, int64_t m
 // weights; EINVAL on a zero weight, EUNSUPPORTED when a weighted degree or vol
 // reaches 2^32.  Synchronises the stream.
 lne_status weight_info(lne_ctx *ctx, const Graph *g, Buf &cw, uint64_t *vol);
+// Records of the unweighted walk step, 16 bytes per vertex: (offset of the first
+// arc, low and high word, degree d, floor((2^32 - 1) / d)).
+lne_status row_records(lne_ctx *ctx, const Graph *g, Buf &rows);
 // Records of the weighted walk step, 16 bytes each, so that a step reads three
 // cache lines and not eight.  arcs: (end of the arc's slice of the row's
 // cumulative weights, weight, column, guide entry); rows: (offset of the first

@@ -73,6 +73,16 @@ def test_count_csr_small_graphs(lne, ctx, name):
         _count_parity(lne, ctx, g, p)
 
 
+@pytest.mark.parametrize("leaves", [2, 3, 255, 256, 257, 4095, 4097])
+def test_count_csr_degrees_around_powers_of_two(lne, ctx, leaves):
+    """A walk step's z mod d through floor((2^32 - 1) / d), whose quotient may
+    be one short: degrees 1 (the leaves) and around powers of two (the hub),
+    where it is exact, one short for most words, or one short for few."""
+    g = gs.star(leaves)
+    p = gs.params(T=3, s=[0.2, 0.3, 0.5], M_per_m=20, C=None, m=g.m, seed=leaves)
+    _count_parity(lne, ctx, g, p)
+
+
 def test_count_csr_fewer_samples_than_edges(lne, ctx):
     g = sbm([40, 40], 0.3, 0.05, seed=3)
     p = gs.params(T=3, s=[0.5, 0.25, 0.25], M_per_m=1, C=math.log(g.n), m=g.m, seed=2)
