@@ -278,6 +278,7 @@ lne_status lne_spmm(lne_ctx *ctx, const lne_csr *A, const void *X, int64_t ldx,
  * secular equation; the reflectors applied to the eigenvectors), S = sqrt(D) sorted descending, U = Y V S^-1 (columns with
  * S <= k eps S_1 are zero).  U: device n x k (ldu, dtype; BF16 input gives F32
  * U), S: device k doubles, V: device k x k doubles.  Any output may be NULL.
+ * A Y^T Y with an entry that is infinite or undefined gives NaN everywhere.
  * Errors: EINVAL, ENOMEM, EUNSUPPORTED (k > 288). */
 lne_status lne_eigsvd(lne_ctx *ctx, const void *Y, int64_t n, int32_t k, int64_t ld,
                       int32_t dtype, void *U, int64_t ldu, double *S, double *V);

@@ -1061,6 +1061,12 @@ __device__ inline double wave_sum(double x) {
     return (readlane_d(x, 0) + readlane_d(x, 16)) + (readlane_d(x, 32) + readlane_d(x, 48));
 }
 
+// The power of two that brings the largest of some finite numbers, m > 0, to
+// [1, 2) (or to a normal number, where it is itself near the type's limits).
+__device__ inline double unit_scale(double m) {
+    return ldexp(1.0, -min(max(ilogb(m), -1000), 1000));
+}
+
 // Serial QL state of the producing wave.
 struct QlState {
     int l = 0;      // eigenvalues 0 .. l-1 have converged
@@ -1151,7 +1157,9 @@ __device__ int ql_chain(int l, int m, double g, double2 *de, double2 *rot) {
 
 // One QL sweep on the pairs de (length-k diagonal and coupling between i and
 // i+1, the last 0), run by a whole wave.  Returns false once every eigenvalue
-// has converged; else the sweep's rotations are in rot over [*lo, *hi).
+// has converged; else the sweep's rotations are in rot over [*lo, *hi).  Ends
+// whatever the values: an undefined coupling or neighbour counts as negligible
+// (hence the negated test), and so does the zero of a coupling given up.
 template <int R>
 __device__ bool ql_sweep(double2 *de, int k, QlState &st, double2 *rot, int *lo, int *hi,
                          int lane) {
@@ -1164,7 +1172,7 @@ __device__ bool ql_sweep(double2 *de, int k, QlState &st, double2 *rot, int *lo,
             const int j = 64 * q + lane;
             x[q] = de[min(j, k - 1)];
             const double dn = de[min(j + 1, k - 1)].x;
-            split[q] = __ballot(j < k - 1 && fabs(x[q].y) <= eps * (fabs(x[q].x) + fabs(dn)));
+            split[q] = __ballot(j < k - 1 && !(fabs(x[q].y) > eps * (fabs(x[q].x) + fabs(dn))));
         }
         // l: the first eigenvalue not yet converged, m: the first negligible
         // coupling at or after it
@@ -1506,7 +1514,7 @@ __device__ __forceinline__ void tridiag_eig(int k, const EigWs &out) {
     int *idx = (int *)de_pad;            // merge: order, kept and deflated rows
     __shared__ int s_lo[2][2], s_hi[2][2], s_more[2][2];   // [problem][buffer]
     __shared__ double s_rho, s_unit, s_tol;
-    __shared__ int s_K, s_flip;
+    __shared__ int s_K, s_flip, s_finite;
     double *__restrict__ Zt = out.Zt;
     // the wave index as a scalar, so that code under `w == 0` branches as a
     // uniform wave
@@ -1540,11 +1548,15 @@ __device__ __forceinline__ void tridiag_eig(int k, const EigWs &out) {
     }
     if (w == 0) {
         double amax = 0.0;
-        for (int i = lane; i < k; i += 64) amax = fmax(amax, fmax(fabs(dg[i]), fabs(eg[i])));
+        bool finite = true;
+        for (int i = lane; i < k; i += 64) {
+            amax = fmax(amax, fmax(fabs(dg[i]), fabs(eg[i])));
+            finite &= isfinite(dg[i]) && isfinite(eg[i]);
+        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) amax = fmax(amax, __shfl_xor(amax, o, 64));
         double unit = 1.0;
-        if (amax > 0.0 && isfinite(amax)) unit = ldexp(1.0, -ilogb(amax));
+        if (amax > 0.0 && isfinite(amax)) unit = unit_scale(amax);
         // the tear's rank-one term leaves d[h-1] and d[h]
         const double rho = np == 2 ? eg[h - 1] * unit : 0.0;
         for (int i = lane; i < k; i += 64) {
@@ -1556,8 +1568,19 @@ __device__ __forceinline__ void tridiag_eig(int k, const EigWs &out) {
             s_unit = unit;
             s_rho = rho;
         }
+        const bool all_finite = __all(finite);
+        if (lane == 0) s_finite = all_finite ? 1 : 0;
     }
     __syncthreads();
+    if (!s_finite) {   // no eigenvalues: all of the result is undefined
+        for (int i = tid; i < k * k; i += NT) Zt[i] = NAN;
+        for (int i = tid; i < k; i += NT) {
+            out.eig[i] = NAN;
+            out.kept[i] = i;
+        }
+        if (tid == 0) *out.K = 0;
+        return;
+    }
     {
         QlState st;
         if (w < np) __builtin_amdgcn_s_setprio(3);   // a chain goes before its SIMD's other waves
@@ -2010,13 +2033,14 @@ __device__ __forceinline__ void eig_back(double *__restrict__ A, int k, const Ei
         __syncthreads();
     }
 
-    // rank by decreasing eigenvalue, ties by index; four lanes share a column
+    // rank by decreasing eigenvalue, ties (and undefined ones) by index; four
+    // lanes share a column
     if (!work) return;
     const double lc = c < k ? in.eig[c] : 0.0;
     int rank = 0;
     for (int j = kr; j < k; j += 4) {
         const double lj = in.eig[j];
-        rank += lj > lc || (lj == lc && j < c) ? 1 : 0;
+        rank += lj > lc || (!(lc > lj) && j < c) ? 1 : 0;
     }
     rank += __shfl_xor(rank, 16, 64);
     rank += __shfl_xor(rank, 32, 64);
@@ -2080,12 +2104,12 @@ __global__ void k_eig_weights(const double *__restrict__ V, const double *__rest
     const double floor_ = (double)k * 2.220446049250313e-16 * lmax;
     if (S && t < kout) {
         const double l = lam[t];
-        S[t] = l > floor_ ? sqrt(l) : 0.0;
+        S[t] = l > floor_ ? sqrt(l) : l != l ? l : 0.0;
     }
     if (W && t < (int64_t)k * kout) {
         const int i = (int)(t / kout), c = (int)(t % kout);
         const double l = lam[c];
-        W[t] = l > floor_ ? V[(int64_t)i * k + c] * pow(l, power) : 0.0;
+        W[t] = l > floor_ ? V[(int64_t)i * k + c] * pow(l, power) : l != l ? l : 0.0;
     }
 }
 

@@ -133,6 +133,29 @@ def test_eigsvd_at_tile_edges(lne, ctx, k):
     assert np.all(S[:-1] >= S[1:])
 
 
+# below and above the single-launch solver, the torn matrix, the widths of the
+# reduction in registers and the wide one
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("k", [1, 2, 3, 16, 31, 32, 33, 64, 138, 144, 145, 266])
+def test_eigsvd_of_a_block_that_is_not_finite_ends(lne, ctx, k, dtype):
+    """The solver's loops end on an infinite or undefined Gram matrix, whose
+    decomposition is undefined throughout, and leave nothing behind for the
+    next call on the context."""
+    import torch
+    tdt = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    Y = torch.from_numpy(_rand_y(500, k, seed=k, cond=10.0 if k > 1 else 1.0)).cuda()
+    ld = (k + 7) // 8 * 8
+    for bad, col in ((float("nan"), k - 1), (float("nan"), 0), (float("inf"), k // 2)):
+        Yd = torch.zeros((500, ld), dtype=tdt, device="cuda")
+        Yd[:, :k] = Y.to(tdt)
+        Yd[17, col] = bad
+        U, S, V = lne.eigsvd(ctx, Yd[:, :k])
+        assert bool(S.isnan().all()) and bool(V.isnan().all()) and bool(U.isnan().all())
+    _, S, _ = lne.eigsvd(ctx, Y)
+    S2 = np.linalg.svd(Y.cpu().numpy(), compute_uv=False)
+    np.testing.assert_allclose(S.cpu().numpy(), S2, rtol=1e-10)
+
+
 @pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
 @pytest.mark.parametrize("k", [42, 138])
 def test_orthonormalize(lne, ctx, dtype, k):
