@@ -1061,10 +1061,18 @@ __device__ inline double wave_sum(double x) {
     return (readlane_d(x, 0) + readlane_d(x, 16)) + (readlane_d(x, 32) + readlane_d(x, 48));
 }
 
-// The power of two that brings the largest of some finite numbers, m > 0, to
-// [1, 2) (or to a normal number, where it is itself near the type's limits).
+// Largest of a fully active wave's values, in every lane (undefined ones passed
+// over).
+__device__ inline double wave_max(double x) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
+    return x;
+}
+
+// The power of two that brings numbers of largest size m to unit size (or to
+// normal numbers, where m is near the type's limits); 1 where none does.
 __device__ inline double unit_scale(double m) {
-    return ldexp(1.0, -min(max(ilogb(m), -1000), 1000));
+    return m > 0.0 && isfinite(m) ? ldexp(1.0, -min(max(ilogb(m), -1000), 1000)) : 1.0;
 }
 
 // Serial QL state of the producing wave.
@@ -1271,11 +1279,15 @@ __device__ void ql_apply(double *z, int ld, const double2 *rot, int lo, int hi) 
 // pairs of rows w + W q, lane l of it columns l + 64 c.  Step j: with x row j, u = x past the
 // diagonal, its first entry less beta, and H = I - g u u^T, g = 1 / (beta^2 -
 // beta x0), the trailing block becomes A - u w^T - w u^T, w = p - (g/2)(p.u) u,
-// p = g A u.  The waves' parts of p meet in LDS; every wave forms the same sums
+// p = g A u.  The matrix is scaled by a power of two first (exact; taken back
+// in d and e), so that no square overflows and a row whose squares vanish (u
+// below 2^-500 of the largest entry) is negligible: it counts as reduced, as g
+// would overflow.  The waves' parts of p meet in LDS; every wave forms the same sums
 // and its own w, so a step has two block barriers.  Bound by its chain (two
 // sums over a wave, a root, a reciprocal, three trips through LDS): with the
 // matrix in LDS, read twice and written once a step, and three barriers, 380
 // us at k = 128 and 71 at 42; this takes 199 and 46.
+constexpr double kSquareLeast = 0x1p-1000;   // least sum of squares of a row not yet reduced
 constexpr int kTriDiagThreads = 512;
 constexpr int kTriDiagWaves = kTriDiagThreads / 64;
 // A block barrier that waits for the wave's LDS accesses only (__syncthreads
@@ -1310,6 +1322,20 @@ __device__ __forceinline__ void tridiag(double *__restrict__ A, int k, const Eig
 #pragma unroll
                 for (int c = 0; c < C; ++c) row[lane + 64 * c] = a[q][c];
     };
+    double amax = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int c = 0; c < C; ++c) amax = fmax(amax, fabs(a[q][c]));
+    part[w][lane] = wave_max(amax);
+    lds_barrier();
+#pragma unroll
+    for (int v = 0; v < W; ++v) amax = fmax(amax, part[v][lane]);
+    const double unit = unit_scale(wave_max(amax)), back = 1.0 / unit;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int c = 0; c < C; ++c) a[q][c] *= unit;
     publish(0);
     lds_barrier();
     for (int j = 0; j + 2 < k; ++j) {
@@ -1322,10 +1348,10 @@ __device__ __forceinline__ void tridiag(double *__restrict__ A, int k, const Eig
             sg = fma(u[c], u[c], sg);
         }
         sg = wave_sum(sg);
-        if (tid == 0) out.eig[j] = row[j];
-        if (sg == 0.0) {   // already reduced: H = I
+        if (tid == 0) out.eig[j] = row[j] * back;
+        if (sg < kSquareLeast) {   // already reduced: H = I
             if (tid == 0) {
-                out.off[j] = x0;
+                out.off[j] = x0 * back;
                 out.tau[j] = 0.0;
             }
             lds_barrier();
@@ -1393,7 +1419,7 @@ __device__ __forceinline__ void tridiag(double *__restrict__ A, int k, const Eig
                     if (l > j && l < k) A[(int64_t)j * k + l] = l == j + 1 ? 1.0 : u[c] * sc;
                 }
                 if (lane == 0) {
-                    out.off[j] = beta;
+                    out.off[j] = beta * back;
                     out.tau[j] = -u0 / beta;
                 }
             }
@@ -1403,15 +1429,15 @@ __device__ __forceinline__ void tridiag(double *__restrict__ A, int k, const Eig
     }
     if (tid == 0) {
         const int j = max(k - 2, 0);
-        out.eig[j] = row[j];
+        out.eig[j] = row[j] * back;
         out.tau[j] = out.tau[k - 1] = 0.0;
-        out.off[j] = k >= 2 ? row[k - 1] : 0.0;
+        out.off[j] = k >= 2 ? row[k - 1] * back : 0.0;
         out.off[k - 1] = 0.0;
     }
     lds_barrier();
     if (k >= 2) publish(k - 1);
     lds_barrier();
-    if (tid == 0) out.eig[k - 1] = row[k - 1];
+    if (tid == 0) out.eig[k - 1] = row[k - 1] * back;
 }
 template <int C>
 __global__ void __launch_bounds__(kTriDiagThreads)
@@ -1419,7 +1445,8 @@ k_tridiag(double *__restrict__ A, int k, double *__restrict__ ws) {
     tridiag<C, kTriDiagWaves>(A + (int64_t)blockIdx.x * k * k, k, eig_ws(ws, k, blockIdx.x));
 }
 
-// Phase 1 for wider matrices, worked on in place in global memory.  Per step:
+// Phase 1 for wider matrices, worked on in place in global memory, scaled as
+// above.  Per step:
 // every wave forms the reflector from row j; threads (row i, part q) sum parts
 // of p = tau A v; thread i < m finishes p_i and writes v_i into row j (first
 // entry 1); threads (column l, row group g) apply the rank-2 update.  Three
@@ -1433,6 +1460,15 @@ k_tridiag_wide(double *__restrict__ A, int k, double *__restrict__ ws) {
     const int tid = threadIdx.x, lane = tid & 63;
     constexpr int P = kSolveThreads / MK < 4 ? kSolveThreads / MK : 4;   // parts per row sum
     constexpr int G = kSolveThreads / MK;                                 // row groups
+    double amax = 0.0;
+    for (int i = tid; i < k * k; i += kSolveThreads) amax = fmax(amax, fabs(A[i]));
+    amax = wave_max(amax);
+    if (lane == 0) pq[tid >> 6] = amax;
+    __syncthreads();
+    for (int v = 0; v < kSolveThreads / 64; ++v) amax = fmax(amax, pq[v]);
+    const double unit = unit_scale(amax), back = 1.0 / unit;
+    for (int i = tid; i < k * k; i += kSolveThreads) A[i] *= unit;
+    __syncthreads();
     for (int j = 0; j + 2 < k; ++j) {
         const int m = k - j - 1;   // trailing indices j+1 .. k-1
         double *x = A + (int64_t)j * k + j + 1;
@@ -1440,14 +1476,14 @@ k_tridiag_wide(double *__restrict__ A, int k, double *__restrict__ ws) {
         for (int l = 1 + lane; l < m; l += 64) sg += x[l] * x[l];
         sg = wave_sum(sg);
         const double x0 = x[0];
-        if (tid == 0) out.eig[j] = A[(int64_t)j * k + j];
-        if (sg == 0.0) {   // already reduced: H = I
-            if (tid == 0) { out.off[j] = x0; out.tau[j] = 0.0; }
+        if (tid == 0) out.eig[j] = A[(int64_t)j * k + j] * back;
+        if (sg < kSquareLeast) {   // already reduced: H = I
+            if (tid == 0) { out.off[j] = x0 * back; out.tau[j] = 0.0; }
             continue;
         }
         const double beta = -copysign(sqrt(x0 * x0 + sg), x0);
         const double tau = (beta - x0) / beta, sc = 1.0 / (x0 - beta);
-        if (tid == 0) { out.off[j] = beta; out.tau[j] = tau; }
+        if (tid == 0) { out.off[j] = beta * back; out.tau[j] = tau; }
         {
             const int i = tid % MK, q = tid / MK, L = (m + P - 1) / P;
             if (q < P && i < m) {
@@ -1494,10 +1530,10 @@ k_tridiag_wide(double *__restrict__ A, int k, double *__restrict__ ws) {
     }
     if (tid == 0) {
         for (int j = k - 2; j < k; ++j) {
-            out.eig[j] = A[(int64_t)j * k + j];
+            out.eig[j] = A[(int64_t)j * k + j] * back;
             out.tau[j] = 0.0;
         }
-        out.off[k - 2] = A[(int64_t)(k - 2) * k + k - 1];
+        out.off[k - 2] = A[(int64_t)(k - 2) * k + k - 1] * back;
         out.off[k - 1] = 0.0;
     }
 }
@@ -1553,10 +1589,7 @@ __device__ __forceinline__ void tridiag_eig(int k, const EigWs &out) {
             amax = fmax(amax, fmax(fabs(dg[i]), fabs(eg[i])));
             finite &= isfinite(dg[i]) && isfinite(eg[i]);
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) amax = fmax(amax, __shfl_xor(amax, o, 64));
-        double unit = 1.0;
-        if (amax > 0.0 && isfinite(amax)) unit = unit_scale(amax);
+        const double unit = unit_scale(wave_max(amax));
         // the tear's rank-one term leaves d[h-1] and d[h]
         const double rho = np == 2 ? eg[h - 1] * unit : 0.0;
         for (int i = lane; i < k; i += 64) {
@@ -1650,8 +1683,7 @@ __device__ __forceinline__ void tridiag_eig(int k, const EigWs &out) {
                 dmax = fmax(dmax, fabs(dg[i]));
             }
             zz = wave_sum(zz);
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o, 64));
+            dmax = wave_max(dmax);
             if (lane == 0) {
                 const double rt = s_rho * zz;
                 s_flip = rt < 0.0 ? 1 : 0;

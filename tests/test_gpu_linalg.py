@@ -133,6 +133,31 @@ def test_eigsvd_at_tile_edges(lne, ctx, k):
     assert np.all(S[:-1] >= S[1:])
 
 
+@pytest.mark.parametrize("k", [2, 8, 33, 138, 145])
+def test_eigsvd_of_tiny_huge_and_graded_blocks(lne, ctx, k):
+    """Scaling Y by a power of two scales every step of the solver exactly, so
+    V and S / scale are the same bits as long as the Gram matrix itself is in
+    range.  Columns that fall by factors of two down to 2^-600 (or all but one
+    at 2^-525): V stays orthogonal and diagonalises the Gram matrix to the
+    bars of the tests above."""
+    import torch
+    Y = _rand_y(600, k, seed=k, cond=1e2)
+    _, S0, V0 = lne.eigsvd(ctx, torch.from_numpy(Y).cuda())
+    for e in (-340, -262, -258, 260, 340):
+        _, S, V = lne.eigsvd(ctx, torch.from_numpy(np.ldexp(Y, e)).cuda())
+        assert torch.equal(V, V0), e
+        assert torch.equal(S * 2.0 ** -e, S0), e
+    bar = 16 * k * 2.0 ** -53
+    for e in (-600 * np.arange(k) // (k - 1), np.where(np.arange(k) == k // 2, 0, -525)):
+        Z = np.ldexp(Y, e)
+        _, S, V = (x.cpu().numpy() if x is not None else x
+                   for x in lne.eigsvd(ctx, torch.from_numpy(Z).cuda()))
+        assert np.max(np.abs(V.T @ V - np.eye(k))) <= bar
+        assert np.max(np.abs(V.T @ (Z.T @ Z) @ V - np.diag(S ** 2))) <= bar * S[0] ** 2
+        S2 = np.linalg.svd(Z, compute_uv=False)
+        assert np.max(np.abs(S ** 2 - S2 ** 2)) <= 1e-13 * S2[0] ** 2 * k
+
+
 # below and above the single-launch solver, the torn matrix, the widths of the
 # reduction in registers and the wide one
 @pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
