@@ -173,36 +173,39 @@ __global__ void k_inv_sqrt_deg(const int64_t *__restrict__ rp, int64_t n, double
 // wave a row 18 us.
 constexpr int kWalkG = 64 / kWalkB;
 constexpr int kWalkU = 4;
+constexpr int64_t kWalkBlocks = 1 << 22;   // a launch has fewer than 2^32 threads: more rows than
+                                           // waves are taken in turn
 __global__ void __launch_bounds__(kStatThreads)
 k_half_walk(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             const double *__restrict__ s, const double *__restrict__ X, double *__restrict__ Y,
             int64_t n, int b) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (i >= n) return;
     const int lane = threadIdx.x & 63, grp = lane / kWalkB, c = lane % kWalkB;
     const double *xc = X + (c < b ? c : 0);   // idle lanes read column 0
-    double acc = 0.0;
-    const int64_t end = rp[i + 1];
-    for (int64_t e0 = rp[i]; e0 < end; e0 += 64) {
-        const int cnt = (int)min((int64_t)64, end - e0);
-        const int32_t j = col[e0 + min(lane, cnt - 1)];
-        const double sj = lane < cnt ? s[j] : 0.0;
-        for (int t0 = 0; t0 < cnt; t0 += kWalkG * kWalkU) {
-            double x[kWalkU], f[kWalkU];
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < n;
+         i += (int64_t)gridDim.x * blockDim.x >> 6) {
+        double acc = 0.0;
+        const int64_t end = rp[i + 1];
+        for (int64_t e0 = rp[i]; e0 < end; e0 += 64) {
+            const int cnt = (int)min((int64_t)64, end - e0);
+            const int32_t j = col[e0 + min(lane, cnt - 1)];
+            const double sj = lane < cnt ? s[j] : 0.0;
+            for (int t0 = 0; t0 < cnt; t0 += kWalkG * kWalkU) {
+                double x[kWalkU], f[kWalkU];
 #pragma unroll
-            for (int u = 0; u < kWalkU; ++u) {
-                const int t = t0 + kWalkG * u + grp;   // past cnt: the last one, weight 0
-                const int32_t jt = __shfl(j, min(t, 63), 64);
-                f[u] = t < 64 ? __shfl(sj, min(t, 63), 64) : 0.0;
-                x[u] = xc[(int64_t)jt * b];
+                for (int u = 0; u < kWalkU; ++u) {
+                    const int t = t0 + kWalkG * u + grp;   // past cnt: the last one, weight 0
+                    const int32_t jt = __shfl(j, min(t, 63), 64);
+                    f[u] = t < 64 ? __shfl(sj, min(t, 63), 64) : 0.0;
+                    x[u] = xc[(int64_t)jt * b];
+                }
+#pragma unroll
+                for (int u = 0; u < kWalkU; ++u) acc += f[u] * x[u];
             }
-#pragma unroll
-            for (int u = 0; u < kWalkU; ++u) acc += f[u] * x[u];
         }
-    }
 #pragma unroll
-    for (int o = kWalkB; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
-    if (grp == 0 && c < b) Y[i * b + c] = 0.5 * (X[i * b + c] + s[i] * acc);
+        for (int o = kWalkB; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+        if (grp == 0 && c < b) Y[i * b + c] = 0.5 * (X[i * b + c] + s[i] * acc);
+    }
 }
 
 }  // namespace
@@ -339,8 +342,10 @@ lne_status graph_stats_impl(lne_ctx *ctx, const Graph *g, uint64_t seed, int32_t
         for (int it = 0; it < iters; ++it) {
             {
                 Launch L(ctx, "graph_stats");
-                k_half_walk<<<grid_of(n * 64, kStatThreads), kStatThreads, 0, ctx->stream>>>(
-                    rp, g->col, s.as<double>(), x, y, n, b);
+                k_half_walk<<<(unsigned)std::min<int64_t>(ceil_div(n * 64, kStatThreads),
+                                                          kWalkBlocks),
+                              kStatThreads, 0, ctx->stream>>>(rp, g->col, s.as<double>(), x, y, n,
+                                                              b);
             }
             LNE_TRY(check_launch(ctx, "graph_stats"));
             if (it + 1 == iters) {

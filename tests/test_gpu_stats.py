@@ -49,3 +49,29 @@ def test_graph_stats_rejects_bad_input(lne, ctx):
     empty_col = torch.zeros(0, dtype=torch.int32, device="cuda")
     with pytest.raises(lne.LneError):
         lne.graph_stats(ctx, empty_rp, empty_col)
+
+
+@pytest.mark.parametrize("n", [(1 << 24) + 1, (1 << 26) + 5])
+def test_spectral_step_of_a_graph_of_many_vertices(lne, ctx, n):
+    """One step on a cycle whose rows outnumber the waves of a launch (and, the
+    larger, a launch's threads at a wave a row): S_2 of (X + A X / 2) / 2 from
+    the Gaussian start, the Gram matrix summed by torch; its n products of
+    terms of one size are off by less than 1e-9 of it however they are
+    summed."""
+    import torch
+    i = torch.arange(n, device="cuda", dtype=torch.int32)
+    col = torch.stack([torch.where(i == 0, 1, i - 1), torch.where(i == n - 1, n - 2, i + 1)], 1)
+    col[0] = torch.tensor([1, n - 1])
+    col[n - 1] = torch.tensor([0, n - 2])
+    rp = 2 * torch.arange(n + 1, device="cuda", dtype=torch.int64)
+    got = lne.graph_stats(ctx, rp, col.reshape(-1).contiguous(), seed=3, wedges=100, iters=1)
+    del i, col, rp
+    X = lne.gaussian(ctx, n, 16, 3, torch.float64)
+    Y = X.roll(1, 0)
+    Y += X.roll(-1, 0)
+    Y.mul_(0.5).add_(X).mul_(0.5)
+    S2 = torch.linalg.eigvalsh(Y.T @ Y)[-2].sqrt().item()
+    assert abs((2.0 - got[7]) / 2.0 - S2) <= 1e-9 * S2
+    assert got[6] == 0.0
+    del X, Y
+    torch.cuda.empty_cache()
