@@ -75,3 +75,21 @@ def test_spectral_step_of_a_graph_of_many_vertices(lne, ctx, n):
     assert got[6] == 0.0
     del X, Y
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("name", ["edges12", "k88", "cycle12"])
+def test_a_block_that_loses_rank_is_seen_after_two_steps(lne, name):
+    """The operator has fewer than 16 directions that do not vanish: the steps
+    by CholeskyQR are left after the second, whatever their number."""
+    g = {"edges12": gs.from_edges(24, [(2 * i, 2 * i + 1) for i in range(12)]),
+         "k88": gs.from_edges(16, [(i, 8 + j) for i in range(8) for j in range(8)]),
+         "cycle12": gs.cycle(12)}[name]
+    rp, col = to_dev(g)
+    c = lne.Context()
+    c.prof_enable()
+    for iters in (2, 3, 40):
+        c.prof_reset()
+        got = lne.graph_stats(c, rp, col, seed=7, wedges=10, iters=iters)
+        assert c.prof_get("chol_inv")[1] == min(iters - 1, 2)
+        assert abs(got[7] - (1.0 - gst.spectral_lambda2(g, 7, iters))) <= 1e-9
+    c.close()
