@@ -301,8 +301,8 @@ lne_status lne_eigsvd(lne_ctx *ctx, const void *Y, int64_t n, int32_t k, int64_t
  * lambda_2 = 2 S_2 - 1 after `iters` steps X <- U of [U, S] = eigSVD((X + D^-1/2
  * A D^-1/2 X) / 2), from X = the lne_gaussian block of n x min(16, n) under
  * key seed (isolated vertices: zero rows of D^-1/2 A D^-1/2); steps before the
- * last may take another orthonormal basis of the same span, on which alone S_2
- * depends.  g: unweighted,
+ * last may take another basis of the same span, orthonormal to rounding where
+ * the last product is formed (S_2 is the same for all of these).  g: unweighted,
  * with at least one edge.  out: host, 8 doubles.  Synchronous.
  * Errors: EINVAL (wedges < 1, iters < 1, invalid graph), EUNSUPPORTED
  * (weighted graph), ENOMEM, EHIP. */

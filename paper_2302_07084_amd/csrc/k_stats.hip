@@ -312,11 +312,12 @@ lne_status graph_stats_impl(lne_ctx *ctx, const Graph *g, uint64_t seed, int32_t
     }
     out[6] = (double)closed / (double)wedges;
     // spectral gap: subspace iteration on (I + S A S) / 2 from X = Omega; S_2
-    // is the second singular value of the last product.  It depends on the
-    // block before that product only through its span, so the steps before
-    // the last orthonormalise by one CholeskyQR pass (8 us of factorisation
-    // at b = 16 against 122 us of eigen-solve, 8.9 ms against 36 ms in all at n =
-    // 30,000 and 200 steps).  A breakdown (a block that is rank deficient to
+    // is the second singular value of the last product, the same for any
+    // orthonormal basis of the span of the block before it.  So the steps
+    // before the last orthonormalise by one CholeskyQR pass (8 us of
+    // factorisation at b = 16 against 122 us of eigen-solve, 8.8 ms against 36 ms
+    // in all at n = 30,000 and 200 steps), which keeps the span, and the block
+    // before the last product takes a second: one pass is off by about cond^2 u.  A breakdown (a block that is rank deficient to
     // rounding, as on graphs of few vertices) repeats the steps with eigSVD,
     // which drops the directions that vanish.  It is looked for after the
     // second step, before the others are spent (11.4 ms in all for twelve
@@ -361,11 +362,13 @@ lne_status graph_stats_impl(lne_ctx *ctx, const Graph *g, uint64_t seed, int32_t
                 LNE_TRY(lne_eigsvd(ctx, y, n, b, b, LNE_F64, x, b, nullptr, nullptr));
             } else {
                 int32_t *f = fl.as<int32_t>();
-                LNE_TRY(gram(ctx, y, LNE_F64, n, b, b, G.as<double>(), nullptr));
-                LNE_TRY(chol_inv(ctx, G.as<double>(), b, W.as<double>(), f, f + 1, n, nullptr,
-                                 nullptr));
-                LNE_TRY(project(ctx, y, LNE_F64, b, n, b, W.as<double>(), b, y, LNE_F64, b,
-                                nullptr, 1, 0, 0, 0, nullptr, true));
+                for (int pass = it + 2 == iters ? 2 : 1; pass > 0; --pass) {
+                    LNE_TRY(gram(ctx, y, LNE_F64, n, b, b, G.as<double>(), nullptr));
+                    LNE_TRY(chol_inv(ctx, G.as<double>(), b, W.as<double>(), f, f + 1, n, nullptr,
+                                     nullptr));
+                    LNE_TRY(project(ctx, y, LNE_F64, b, n, b, W.as<double>(), b, y, LNE_F64, b,
+                                    nullptr, 1, 0, 0, 0, nullptr, true));
+                }
                 std::swap(x, y);
                 if (it == 1) {
                     LNE_HIP(ctx, hipMemcpyAsync(hf, fl.p, sizeof(hf), hipMemcpyDeviceToHost,

@@ -90,6 +90,19 @@ def test_a_block_that_loses_rank_is_seen_after_two_steps(lne, name):
     for iters in (2, 3, 40):
         c.prof_reset()
         got = lne.graph_stats(c, rp, col, seed=7, wedges=10, iters=iters)
-        assert c.prof_get("chol_inv")[1] == min(iters - 1, 2)
+        # (a second pass where the next product is the last)
+        assert c.prof_get("chol_inv")[1] == (2 if iters != 3 else 3)
         assert abs(got[7] - (1.0 - gst.spectral_lambda2(g, 7, iters))) <= 1e-9
     c.close()
+
+
+@pytest.mark.parametrize("seed", [37904, 43290, 21102])
+def test_spectral_gap_from_an_ill_conditioned_start(lne, ctx, seed):
+    """A 16 x 16 Gaussian start whose condition number is 3 10^5 to 9 10^5,
+    found by search over seeds: one Cholesky pass (and one eigSVD) leaves it
+    orthonormal to 10^-5 only.  On the complete graph every direction but one
+    has the eigenvalue -1/15, so two steps give the gap 1 + 1/15 itself; bar:
+    1,000 roundings."""
+    rp, col = to_dev(gs.complete(16))
+    got = lne.graph_stats(ctx, rp, col, seed=seed, wedges=10, iters=2)
+    assert abs(got[7] - (1.0 + 1.0 / 15.0)) <= 1000 * 2.0 ** -53
