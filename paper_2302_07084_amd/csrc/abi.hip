@@ -261,8 +261,10 @@ struct Sampler {
 static lne_status sampler_edges(lne_ctx *ctx, const Graph *g, Sampler &S) {
     LNE_TRY(build_edges(ctx, g, S.eu, S.ev, S.m, g->weight ? &S.ea : nullptr));
     if (!g->weight) {
-        LNE_TRY(row_records(ctx, g, S.rows));
-        S.pl.rows = S.rows.as<uint4>();
+        if (records_pay(g->n, g->n_arcs)) {
+            LNE_TRY(row_records(ctx, g, S.rows));
+            S.pl.rows = S.rows.as<uint4>();
+        }
         return LNE_OK;
     }
     uint64_t vol = 0;

@@ -141,7 +141,8 @@ struct SamplePlan {
     int32_t upper;        // emit one entry per sample, (min, max) of its two
                           // endpoints (the upper triangle; no row filter, no
                           // channels), instead of both orientations
-    const uint4 *rows;    // a walk step's record of each vertex (row_records, weight_guide)
+    const uint4 *rows;    // a walk step's record of each vertex (row_records, weight_guide),
+                          // null on an unweighted graph where records_pay says no
     // weighted graphs (all null on an unweighted one)
     const uint32_t *wt;   // arc weights A
     const uint32_t *ea;   // weight of edge e (u < v arcs in CSR order)
@@ -164,6 +165,22 @@ lne_status weight_info(lne_ctx *ctx, const Graph *g, Buf &cw, uint64_t *vol);
 // Records of the unweighted walk step, 16 bytes per vertex: (offset of the first
 // arc, low and high word, degree d, floor((2^32 - 1) / d)).
 lne_status row_records(lne_ctx *ctx, const Graph *g, Buf &rows);
+// Whether they pay: a step saves three multiplications and a load but the table
+// is twice the offsets', so it has to stay small beside the caches, the smaller
+// the fewer the arcs that lead to a vertex' line again.  Emit pass with records
+// and with offsets, walks of 1..10 edges, power-law / planted graphs of n
+// vertices with e edges each, ms:
+//      n     e   power-law      planted
+//    4,000  10  0.149  0.167   0.166  0.172
+//   10,000   8  0.310  0.321   0.380  0.358
+//   10,000  33  1.199  1.380   1.205  1.456
+//   15,000  33  2.41   2.48    2.38   2.49
+//   20,000  30  2.79   2.70    2.74   2.68
+//  100,000  20  6.91   5.92    7.47   6.14
+//     10^7  20  144    141     229    223
+inline bool records_pay(int64_t n, int64_t arcs) {
+    return n <= 4096 || (n <= 16384 && arcs >= 32 * n);
+}
 // Records of the weighted walk step, 16 bytes each, so that a step reads three
 // cache lines and not eight.  arcs: (end of the arc's slice of the row's
 // cumulative weights, weight, column, guide entry); rows: (offset of the first

@@ -93,9 +93,7 @@ __device__ __forceinline__ uint4 slot_block(const SamplePlan &pl, int64_t e, uin
 
 // z mod d with inv = floor((2^32 - 1) / d): the quotient's high word is at most
 // one short, as z inv / 2^32 > z / d - 1.  Two multiplications; the compiler's
-// remainder takes five and a reciprocal.  With the offset, degree and inv in one
-// record the emit pass of 6.6 10^7 slots of 3.3 10^5 edges, whose tables the
-// caches hold, took 1.22 ms instead of 1.38.
+// remainder takes five and a reciprocal (records_pay has the times of both).
 __device__ __forceinline__ uint32_t mod_by(uint32_t z, uint32_t d, uint32_t inv) {
     const uint32_t r = z - __umulhi(z, inv) * d;
     return r >= d ? r - d : r;
@@ -386,8 +384,9 @@ k_fold_stats(const unsigned long long *__restrict__ att_part,
 
 // Emit pass: every wave writes its entries contiguously from the scanned
 // per-wave count; the order inside a wave is (slot, lane, orientation).
-// Keys are ((row - row_lo) << colbits) | col.
-template <bool W>
+// Keys are ((row - row_lo) << colbits) | col.  REC: an unweighted walk's steps
+// read the vertices' records (pl.rows), else the row offsets.
+template <bool W, bool REC>
 __global__ void __launch_bounds__(kBlock)
 k_sample_emit(SamplePlan pl, const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
               const int32_t *__restrict__ eu, const int32_t *__restrict__ ev, int64_t m,
@@ -438,8 +437,8 @@ k_sample_emit(SamplePlan pl, const int64_t *__restrict__ rp, const int32_t *__re
     };
     if constexpr (!W) {
         // kWalkQ slots at a time: their walks advance together, so each lane
-        // has kWalkQ chains of dependent loads (the vertex' record, then the
-        // column) in flight instead of one; the entries still go out in slot order.
+        // has kWalkQ chains of dependent loads (the vertex' record or row offsets,
+        // then the column) in flight instead of one; the entries still go out in slot order.
         // A slot without a step to take loads from u (cached) and keeps its
         // vertex, so the loads carry no branch.
         for (int64_t jj = 0; jj < pl.J; jj += kWalkQ) {
@@ -490,18 +489,34 @@ k_sample_emit(SamplePlan pl, const int64_t *__restrict__ rp, const int32_t *__re
                     }
                     cur[q] = act[q] ? (i < split[q] ? x[q] : y[q]) : u;
                 }
-                uint4 row[kWalkQ];
-#pragma unroll
-                for (int q = 0; q < kWalkQ; ++q) row[q] = pl.rows[cur[q]];
-                int32_t nb[kWalkQ];
+                int64_t at[kWalkQ];
                 uint32_t deg[kWalkQ];
+                if constexpr (REC) {
+                    uint4 row[kWalkQ];
 #pragma unroll
-                for (int q = 0; q < kWalkQ; ++q) {
-                    deg[q] = row[q].z;
-                    const int64_t at = (int64_t)(((uint64_t)row[q].y << 32) | row[q].x) +
-                                       (int64_t)mod_by(z[q], deg[q], row[q].w);
-                    nb[q] = col[min(at, 2 * m - 1)];
+                    for (int q = 0; q < kWalkQ; ++q) row[q] = pl.rows[cur[q]];
+#pragma unroll
+                    for (int q = 0; q < kWalkQ; ++q) {
+                        deg[q] = row[q].z;
+                        at[q] = (int64_t)(((uint64_t)row[q].y << 32) | row[q].x) +
+                                (int64_t)mod_by(z[q], deg[q], row[q].w);
+                    }
+                } else {
+                    int64_t beg[kWalkQ], end[kWalkQ];
+#pragma unroll
+                    for (int q = 0; q < kWalkQ; ++q) {
+                        beg[q] = rp[cur[q]];
+                        end[q] = rp[cur[q] + 1];
+                    }
+#pragma unroll
+                    for (int q = 0; q < kWalkQ; ++q) {
+                        deg[q] = (uint32_t)(end[q] - beg[q]);
+                        at[q] = beg[q] + (int64_t)(deg[q] ? z[q] % deg[q] : 0u);
+                    }
                 }
+                int32_t nb[kWalkQ];
+#pragma unroll
+                for (int q = 0; q < kWalkQ; ++q) nb[q] = col[min(at[q], 2 * m - 1)];
 #pragma unroll
                 for (int q = 0; q < kWalkQ; ++q) {
                     // a sink (asymmetric input) holds
@@ -970,12 +985,13 @@ lne_status launch_sample_emit(lne_ctx *ctx, const Graph *g, const SamplePlan &pl
     const int64_t threads = sample_threads(pl, m);
     {
         Launch L(ctx, "sample_emit");
-        if (pl.wt)
-            k_sample_emit<true><<<(unsigned)(threads / kBlock), kBlock, 0, ctx->stream>>>(
-                pl, g->row_ptr, g->col, eu, ev, m, row_lo, row_hi, wave_off, keys, vals);
-        else
-            k_sample_emit<false><<<(unsigned)(threads / kBlock), kBlock, 0, ctx->stream>>>(
-                pl, g->row_ptr, g->col, eu, ev, m, row_lo, row_hi, wave_off, keys, vals);
+#define LNE_EMIT(WW, REC)                                                                  \
+    k_sample_emit<WW, REC><<<(unsigned)(threads / kBlock), kBlock, 0, ctx->stream>>>(      \
+        pl, g->row_ptr, g->col, eu, ev, m, row_lo, row_hi, wave_off, keys, vals)
+        if (pl.wt) LNE_EMIT(true, true);
+        else if (pl.rows) LNE_EMIT(false, true);
+        else LNE_EMIT(false, false);
+#undef LNE_EMIT
     }
     return check_launch(ctx, "sample_emit");
 }

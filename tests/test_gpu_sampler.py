@@ -83,6 +83,26 @@ def test_count_csr_degrees_around_powers_of_two(lne, ctx, leaves):
     _count_parity(lne, ctx, g, p)
 
 
+@pytest.mark.parametrize("n,per_vertex,records", [
+    (4096, 4, True), (4097, 4, False), (16384, 17, True), (16384, 15, False), (16385, 17, False)])
+def test_count_csr_with_and_without_vertex_records(lne, n, per_vertex, records):
+    """Emit pass by vertex records on both sides of the sizes from which the
+    row offsets are read instead; the records are built only where they are
+    used."""
+    rng = np.random.default_rng(n + per_vertex)
+    d = np.repeat(np.arange(1, per_vertex + 1), n)
+    a = np.tile(np.arange(n), per_vertex)
+    b = (a + d * d) % n          # distinct pairs: d^2 < n / 2
+    g = gs.from_edges(n, rng.permutation(np.stack([a, b], 1)).tolist())
+    assert g.n_arcs == 2 * n * per_vertex and per_vertex ** 2 < n / 2
+    p = gs.params(T=4, s=[0.1, 0.2, 0.3, 0.4], M_per_m=4, C=math.log(n), m=g.m, seed=n)
+    c = lne.Context()
+    c.prof_enable()
+    _count_parity(lne, c, g, p)
+    assert c.prof_get("row_records")[1] == (1 if records else 0)
+    c.close()
+
+
 def test_count_csr_fewer_samples_than_edges(lne, ctx):
     g = sbm([40, 40], 0.3, 0.05, seed=3)
     p = gs.params(T=3, s=[0.5, 0.25, 0.25], M_per_m=1, C=math.log(g.n), m=g.m, seed=2)
