@@ -146,7 +146,11 @@ __host__ __device__ constexpr int mlp_pad(int h) { return (h + 16 * kMlpU - 1) /
 __host__ __device__ constexpr int mlp_stride(int HP) { return HP + 4; }
 // A1, gelu'(Z1), dZ2 (16 x hidden each, padded)
 inline size_t mlp_lds(int HP) { return sizeof(float) * 3 * kMlpRows * (size_t)mlp_stride(HP); }
-inline bool mlp_fits(int h) { return h <= kMlpMaxH; }
+// A launch has fewer than 2^32 threads: batches past that many rows' blocks take
+// the launches per layer (a thread per output) too.
+inline bool mlp_fits(int h, int64_t B) {
+    return h <= kMlpMaxH && ceil_div(B, kMlpRows) < ((int64_t)1 << 32) / kMlpThreads;
+}
 static_assert(kMlpMaxH <= 16 * kMlpWaves * kMlpTiles, "accumulators of the widest layer");
 
 // Bounds-checked loads (zero outside the buffer's `bytes` bytes): a guard as a
@@ -830,10 +834,10 @@ lne_status lne_mlp_forward(lne_ctx *ctx, int32_t in_dim, int32_t hidden, const f
     if (!ctx) return LNE_EINVAL;
     LNE_TRY(mlp_validate(ctx, in_dim, hidden, batch));
     if (!params || !X || !y) return fail(ctx, LNE_EINVAL, "mlp_forward: NULL argument");
-    if (mlp_fits(hidden))
+    if (mlp_fits(hidden, batch))
         return mlp_rows<false>(ctx, in_dim, hidden, params, X, nullptr, batch, y, nullptr, nullptr,
                                nullptr, nullptr, nullptr);
-    // wider networks than the fused kernel's LDS tile holds: a launch per layer
+    // networks or batches past the fused kernel's: a launch per layer
     Buf act(ctx);
     LNE_TRY(alloc(ctx, act, sizeof(float) * (size_t)(2 * batch * hidden)));
     float *A1 = act.as<float>(), *A2 = A1 + batch * hidden;
@@ -849,7 +853,7 @@ lne_status lne_mlp_grad(lne_ctx *ctx, int32_t in_dim, int32_t hidden, const floa
     const MlpLayout Ly(in_dim, hidden);
     const int64_t Bh = batch * hidden;
     Buf ws(ctx);
-    if (mlp_fits(hidden)) {
+    if (mlp_fits(hidden, batch)) {
         const int64_t nblk = ceil_div(batch, kMlpRows);
         LNE_TRY(alloc(ctx, ws, sizeof(float) * (size_t)(3 * Bh + nblk * (3 * hidden + 2))));
         float *A1 = ws.as<float>(), *dZ2 = A1 + Bh, *dZ1 = dZ2 + Bh;

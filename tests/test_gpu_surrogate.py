@@ -71,6 +71,28 @@ def test_network_at_the_edges_of_its_tiles(lne, ctx, n_in, h, B):
     assert np.linalg.norm(g.cpu().numpy() - g0) <= 1e-4 * np.linalg.norm(g0)
 
 
+@pytest.mark.parametrize("B", [(1 << 26) - 16, (1 << 26) - 15, (1 << 26) + 1])
+def test_forward_of_batches_around_a_launch_of_threads(lne, ctx, B):
+    """64 threads a row fill a launch (2^32 threads) at 2^26 rows; more go
+    through the launches per layer.  The network is a sum of two GELUs, summed
+    by torch in double precision; u = 2^-24, a dozen operations."""
+    import torch
+    p = torch.tensor([1.0, -0.5, 0.1, 0.2, 0.7, 0.3, -0.4, 0.9, 0.0, 0.1, 1.5, -0.8, 0.25],
+                     device="cuda")
+    assert p.numel() == lne.mlp_param_count(1, 2)
+    X = torch.linspace(-3, 3, B, device="cuda").unsqueeze(1)
+    y = lne.mlp_forward(ctx, 1, 2, p, X)
+    gelu = torch.nn.functional.gelu
+    q = p.double()
+    for rows in (slice(0, 1 << 16), slice(B // 2, B // 2 + 4096), slice(B - 4096, B)):
+        h = gelu(X[rows].double() @ q[0:2].view(1, 2) + q[2:4])
+        h = gelu(h @ q[4:8].view(2, 2) + q[8:10])
+        ref = h @ q[10:12] + q[12]
+        assert (y[rows].double() - ref).abs().max() <= 64 * 2.0 ** -24
+    del X, y
+    torch.cuda.empty_cache()
+
+
 def test_adam_step_matches_oracle(lne, ctx):
     import torch
     p = lne.mlp_init(ctx, IN, H, seed=9)
