@@ -5,8 +5,9 @@
 //
 // MLP: in -> hidden -> hidden -> 1, GELU, FP32, mean squared error, Adam.
 // Parameters are one flat array: W1 (in x h), b1 (h), W2 (h x h), b2 (h),
-// W3 (h), b3 (1).  Every reduction is a fixed-order loop in one thread, so
-// results do not depend on scheduling.
+// W3 (h), b3 (1).  Every sum has a fixed order (one thread's loop, matrix
+// instructions over a fixed split of the terms, lane shuffles, waves in turn),
+// so results do not depend on scheduling.
 //
 // Scorer: one-vs-rest L2-regularised logistic regression on the embedding
 // (standardised features, full-batch Adam), then each test vertex predicts its
@@ -152,6 +153,37 @@ inline bool mlp_fits(int h, int64_t B) {
     return h <= kMlpMaxH && ceil_div(B, kMlpRows) < ((int64_t)1 << 32) / kMlpThreads;
 }
 static_assert(kMlpMaxH <= 16 * kMlpWaves * kMlpTiles, "accumulators of the widest layer");
+// Where the fused kernel is the faster.  A block of it takes as long for a
+// narrow network as for one of 64 (4 us and 0.116 us an input, a block per CU at
+// a time: 4,096 rows), while a thread per output pays by the output and
+// starts at some 14 us.  Forward pass, fused and per layer, us, by inputs x
+// hidden and rows:
+//                 16          4,096        32,768       10^6
+//    21 x   8    7   14      8    15      49    14    1306   117
+//    21 x  48    7   17      8    22      49    52    1337  1666
+//    21 x  64    7   18      9    26      50    71    1330  2629
+//    64 x   8   13   14     15    16      93    16    2748   271
+//   128 x   8   20   15     22    17     153    22    4605   509
+//   128 x  48   20   25     22    33     155   109    4693  3652
+//   128 x  64   22   31     23    36     155   146    4696  5217
+//  1000 x  64  118  106    126   164     956   933       -     -
+//  4096 x 320  508 1053    517  3084    4175 20208       -     -
+// The gradient per layer also sums over the rows thread by thread (some 0.5 us
+// a row), so the fused one is ahead but for few rows of many inputs: 16 and
+// 64 rows of 1000 x 16 126 and 127 against 102 and 128 us, of 4096 x 128 482
+// and 485 against 450 and 484; 16 rows of 1000 x 128 130 against 159, 1,024
+// rows of 21 x 8 20 against 475.
+inline bool mlp_fused_forward(int I, int h, int64_t B) {
+    if (!mlp_fits(h, B)) return false;
+    if (h > 128) return true;
+    if (I > 512) return h >= 64 && B > 512;
+    if (h >= 64) return true;
+    if (B <= 4096) return I <= 64 || h >= 32;
+    return I <= 32 && (B <= 8192 || h >= 48);
+}
+inline bool mlp_fused_grad(int I, int h, int64_t B) {
+    return mlp_fits(h, B) && 18 * (B + h) >= I;
+}
 
 // Bounds-checked loads (zero outside the buffer's `bytes` bytes): a guard as a
 // condition became a branch and a wait per load.  out_if: bits that move an
@@ -834,10 +866,10 @@ lne_status lne_mlp_forward(lne_ctx *ctx, int32_t in_dim, int32_t hidden, const f
     if (!ctx) return LNE_EINVAL;
     LNE_TRY(mlp_validate(ctx, in_dim, hidden, batch));
     if (!params || !X || !y) return fail(ctx, LNE_EINVAL, "mlp_forward: NULL argument");
-    if (mlp_fits(hidden, batch))
+    if (mlp_fused_forward(in_dim, hidden, batch))
         return mlp_rows<false>(ctx, in_dim, hidden, params, X, nullptr, batch, y, nullptr, nullptr,
                                nullptr, nullptr, nullptr);
-    // networks or batches past the fused kernel's: a launch per layer
+    // a launch per layer
     Buf act(ctx);
     LNE_TRY(alloc(ctx, act, sizeof(float) * (size_t)(2 * batch * hidden)));
     float *A1 = act.as<float>(), *A2 = A1 + batch * hidden;
@@ -853,7 +885,7 @@ lne_status lne_mlp_grad(lne_ctx *ctx, int32_t in_dim, int32_t hidden, const floa
     const MlpLayout Ly(in_dim, hidden);
     const int64_t Bh = batch * hidden;
     Buf ws(ctx);
-    if (mlp_fits(hidden, batch)) {
+    if (mlp_fused_grad(in_dim, hidden, batch)) {
         const int64_t nblk = ceil_div(batch, kMlpRows);
         LNE_TRY(alloc(ctx, ws, sizeof(float) * (size_t)(3 * Bh + nblk * (3 * hidden + 2))));
         float *A1 = ws.as<float>(), *dZ2 = A1 + Bh, *dZ1 = dZ2 + Bh;

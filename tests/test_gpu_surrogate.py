@@ -71,6 +71,35 @@ def test_network_at_the_edges_of_its_tiles(lne, ctx, n_in, h, B):
     assert np.linalg.norm(g.cpu().numpy() - g0) <= 1e-4 * np.linalg.norm(g0)
 
 
+@pytest.mark.parametrize("n_in,h,B,fused", [
+    (21, 8, 8192, "fg"), (21, 8, 8193, "g"), (32, 48, 8193, "fg"), (33, 16, 4097, "g"),
+    (64, 31, 4096, "fg"), (65, 31, 4096, "g"), (65, 32, 4096, "fg"), (600, 63, 65, "g"),
+    (600, 16, 17, ""), (600, 17, 17, "g"), (600, 128, 512, "g"), (600, 64, 513, "fg"), (600, 129, 16, "fg")])
+def test_network_on_both_sides_of_the_fused_kernel(lne, n_in, h, B, fused):
+    """Forward pass (f) and gradient (g) by the fused kernel and by launches per
+    layer, each where its rule has it; bars as in the test above."""
+    import torch
+    c = lne.Context()
+    c.prof_enable()
+    rng = np.random.default_rng(h)
+    p = lne.mlp_init(c, n_in, h, seed=h)
+    X = rng.standard_normal((B, n_in)).astype(np.float32)
+    t = rng.standard_normal(B).astype(np.float32)
+    pn = p.cpu().numpy().astype(np.float64)
+    Xd, td = torch.from_numpy(X).cuda(), torch.from_numpy(t).cuda()
+    y0, _ = S.forward(pn, X.astype(np.float64), n_in, h)
+    y = lne.mlp_forward(c, n_in, h, p, Xd).cpu().numpy()
+    assert c.prof_get("mlp_rows")[1] == int("f" in fused)
+    np.testing.assert_allclose(y, y0, rtol=1e-4, atol=1e-5)
+    c.prof_reset()
+    g, loss = lne.mlp_grad(c, n_in, h, p, Xd, td)
+    assert c.prof_get("mlp_wgrad")[1] == int("g" in fused)
+    l0, g0 = S.loss_and_grad(pn, X.astype(np.float64), t.astype(np.float64), n_in, h)
+    assert abs(loss.item() - l0) <= 1e-4 * max(l0, 1e-3)
+    assert np.linalg.norm(g.cpu().numpy() - g0) <= 1e-4 * np.linalg.norm(g0)
+    c.close()
+
+
 @pytest.mark.parametrize("B", [(1 << 26) - 16, (1 << 26) - 15, (1 << 26) + 1])
 def test_forward_of_batches_around_a_launch_of_threads(lne, ctx, B):
     """64 threads a row fill a launch (2^32 threads) at 2^26 rows; more go
