@@ -14,6 +14,7 @@
 // one launch per step (batched Gram, Cholesky, eigen-solves and projections,
 // one channel SpMM over every (trial, row) pair, one graph SpMM per
 // propagation step with per-trial epilogue coefficients).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -475,6 +476,23 @@ lne_status chan_segments(lne_ctx *ctx, const lne_csr *ext, int nseg, uint32_t *s
     return check_launch(ctx, "chan_segments");
 }
 
+// Whether tb trials of one operand (n rows of k floats) share its gather.  A wave
+// then takes a row for all of them, which leaves too few waves on few rows, and a
+// small operand is in the caches for a gather each.  Shared and not, us, by
+// rows x columns (some 1,500 entries a row):
+//                  2 trials       4 trials        8 trials
+//    2,000 x 144    227   155     (5: 538  298)    591   448
+//    4,000 x  48    236   177      320   286       527   505
+//    6,000 x  48    321   279      457   464       760   843
+//    8,000 x  48    401   370      617   655     1,000 1,208
+//    4,000 x 144    291   279      427   500       757   904
+//    6,000 x 144    419   477      658   830     1,181 1,501
+//    8,000 x 144    539   647      871 1,163     1,543 2,194
+//   16,000 x 144  1,083 1,502    1,696 2,786     3,144 5,279
+static bool chan_shared_pays(int64_t n, int k, int tb) {
+    return n >= 4096 && n * k * tb * (int64_t)sizeof(float) >= 3 << 21;
+}
+
 lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int nseg, bool shared,
                      int ntr, const double *coef, const float *X, int64_t ldx, int64_t xs,
                      float *Y, int64_t ldy, int64_t ys, int k, int variant) {
@@ -490,31 +508,44 @@ lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int 
     const int64_t n = ext->n_rows;
     if (n == 0 || ntr == 0) return LNE_OK;
     if (!seg) nseg = 1;
-    const int tb = !shared || ntr == 1 ? 1 : ntr <= 2 ? 2 : ntr <= 4 ? 4 : 8;
-    for (int s = 0; s < nseg; ++s) {
-        Launch L(ctx, "spmm_chan");
-#define LNE_CS(TB, VW, U, TM)                                                               \
-    k_chan_seg<TB, VW, U, TM><<<grid_of(n * ceil_div(ntr, TB), 4), 256, 0, ctx->stream>>>(  \
-        ext->row_ptr, seg, nseg, s, ext->col, (const double *)ext->val, n, ntr, coef, X, ldx, xs, \
-        Y, ldy, ys, k, s == 0 ? 1 : 0)
-#define LNE_CV(VW)                                                                          \
-    do {                                                                                    \
-        if (tb == 2) LNE_CS(2, VW, 4, true);                                                \
-        else if (tb == 4) LNE_CS(4, VW, 4, true);                                           \
-        else if (tb == 8) LNE_CS(8, VW, 4, true);                                           \
-        else if (seg || variant == 0) LNE_CS(1, VW, 4, true);                               \
-        else if (variant == 1) LNE_CS(1, VW, 2, true);                                      \
-        else if (variant == 2) LNE_CS(1, VW, 8, true);                                      \
-        else if (variant == 3) LNE_CS(1, VW, 4, false);                                     \
-        else if (variant == 4) LNE_CS(1, VW, 2, false);                                     \
-        else LNE_CS(1, VW, 8, false);                                                       \
-    } while (0)
-        if (k <= 64) LNE_CV(1);
-        else if (k <= 128) LNE_CV(2);
-        else if (k <= 192 && k % 3 == 0) LNE_CV(3);
-        else LNE_CV(4);
+    for (int t0 = 0; t0 < ntr;) {
+        // groups of eight, four and two trials, then a single one.  An incomplete
+        // group costs what a full one does: at 8,000 x 144 five trials in a group
+        // of eight took 1,545 us, as four and one 1,219, but three as two and one
+        // 887 against 852 in a group of four, and six as four and two 1,410
+        const int left = ntr - t0;
+        const int group = left >= 7 ? 8 : left >= 3 ? 4 : left;
+        const int tb = shared && chan_shared_pays(n, k, group) ? group : 1;
+        const int nt = tb == 1 ? left : left >= 8 ? left / 8 * 8 : std::min(tb, left);
+        const double *cf = coef + 16 * t0;
+        const float *Xt = X + t0 * xs;
+        float *Yt = Y + t0 * ys;
+        for (int s = 0; s < nseg; ++s) {
+            Launch L(ctx, "spmm_chan");
+#define LNE_CS(TB, VW, U, TM)                                                                  \
+        k_chan_seg<TB, VW, U, TM><<<grid_of(n * ceil_div(nt, TB), 4), 256, 0, ctx->stream>>>(  \
+            ext->row_ptr, seg, nseg, s, ext->col, (const double *)ext->val, n, nt, cf, Xt, ldx, \
+            xs, Yt, ldy, ys, k, s == 0 ? 1 : 0)
+#define LNE_CV(VW)                                                                             \
+        do {                                                                                   \
+            if (tb == 2) LNE_CS(2, VW, 4, true);                                               \
+            else if (tb == 4) LNE_CS(4, VW, 4, true);                                          \
+            else if (tb == 8) LNE_CS(8, VW, 4, true);                                          \
+            else if (seg || variant == 0) LNE_CS(1, VW, 4, true);                              \
+            else if (variant == 1) LNE_CS(1, VW, 2, true);                                     \
+            else if (variant == 2) LNE_CS(1, VW, 8, true);                                     \
+            else if (variant == 3) LNE_CS(1, VW, 4, false);                                    \
+            else if (variant == 4) LNE_CS(1, VW, 2, false);                                    \
+            else LNE_CS(1, VW, 8, false);                                                      \
+        } while (0)
+            if (k <= 64) LNE_CV(1);
+            else if (k <= 128) LNE_CV(2);
+            else if (k <= 192 && k % 3 == 0) LNE_CV(3);
+            else LNE_CV(4);
 #undef LNE_CV
 #undef LNE_CS
+        }
+        t0 += nt;
     }
     return check_launch(ctx, "spmm_chan");
 }

@@ -147,6 +147,25 @@ def test_batch_spmm_by_column_ranges(lne, ctx, ntr):
     B.close()
 
 
+@pytest.mark.parametrize("n", [600, 6000])
+def test_batch_spmm_groups_of_a_shared_operand(lne, ctx, n):
+    """Every number of trials up to two groups of eight and one: one operand for
+    all of them gives the bits of the same operand copied for each (too few
+    rows to share the gather, and enough)."""
+    import torch
+    g = sbm([n // 20] * 20, 180.0 / n, 0.0008, seed=8)
+    p = gs.params(T=4, M_per_m=20, C=math.log(g.n), m=g.m, seed=3, d=62, oversample=10,
+                  precision="f32")
+    rp, col = to_dev(g)
+    B = lne.Batch(ctx, rp, col, p, max_trials=17)
+    trials = trial_vectors(17, seed=4, T=4)
+    X = torch.from_numpy(np.random.default_rng(0).standard_normal((n, 72)).astype("f")).cuda()
+    own = B.spmm(trials, X.expand(17, n, 72))
+    for ntr in range(1, 18):
+        assert torch.equal(B.spmm(trials[:ntr], X), own[:ntr]), ntr
+    B.close()
+
+
 def _single_trial_reference(lne, ctx, rp, col, p, ch, tr):
     M = lne.trial_matrix(ctx, rp, col, p, ch, tr)
     pt = dict(p, s=tr["s"], cheb_k=tr["k"], theta=tr["theta"], mu=tr["mu"])
