@@ -165,37 +165,53 @@ __global__ void k_inv_sqrt_deg(const int64_t *__restrict__ rp, int64_t n, double
 }
 
 // Y = (X + S A S X) / 2 for n x b row-major blocks (b <= kWalkB), S =
-// diag(s).  A wave takes a row: its lanes read 64 neighbours and their s at
-// once, then four groups of kWalkB lanes gather every fourth neighbour's row
-// of X, lane c of a group summing column c.  Bound by latency (a row is three
-// dependent reads): with kWalkB lanes a row, one neighbour at a time, it took
-// 29 us at n = 30,000 and 9 10^5 arcs, with eight in flight 25, with a
+// diag(s).  G groups of kWalkB lanes take a row: they read a neighbour and its s
+// a lane, then each group gathers every G-th neighbour's row of X, lane c of it
+// summing column c.  Bound by latency (a row is three dependent reads), on many
+// rows by the gathered lines: with kWalkB lanes a row, one neighbour at a time,
+// it took 29 us at n = 30,000 and 9 10^5 arcs, with eight in flight 25, with a
 // wave a row 18 us.
-constexpr int kWalkG = 64 / kWalkB;
 constexpr int kWalkU = 4;
-constexpr int64_t kWalkBlocks = 1 << 22;   // a launch has fewer than 2^32 threads: more rows than
-                                           // waves are taken in turn
+constexpr int64_t kWalkBlocks = 1 << 22;   // a launch has fewer than 2^32 threads: more rows are
+                                           // taken in turn
+// The groups of a row: a wave's four where a hub's row would outlast the others,
+// two of them where there are rows enough to cover that, one on short rows of
+// like length.  A step of graph_stats, us, by G:
+//                          1      2      4
+//     30,000 cycle        29.8   35.1   39.5      (2 arcs a row)
+//     30,000 planted      36.9   37.7   39.6      (16)    64.4   62.8   62.4 (100)
+//  3,000,000 cycle         761  1,029  1,585
+//  3,000,000 planted     2,047  2,023  2,058      (16)
+//     30,000 power-law    96.6   66.4   50.9      (16)
+//    300,000 power-law     199    132    146      (4)      378    233    185 (16)
+//  3,000,000 power-law   1,231  1,157  1,624      (4)    3,117  2,542  2,800 (24)
+inline int half_walk_groups(int64_t n, double mean, uint64_t max_deg) {
+    if (max_deg <= 64) return mean <= 16.0 ? 1 : 4;
+    return n >= 1 << 20 && mean <= 32.0 ? 2 : 4;
+}
+template <int G>
 __global__ void __launch_bounds__(kStatThreads)
 k_half_walk(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             const double *__restrict__ s, const double *__restrict__ X, double *__restrict__ Y,
             int64_t n, int b) {
-    const int lane = threadIdx.x & 63, grp = lane / kWalkB, c = lane % kWalkB;
+    constexpr int L = kWalkB * G;
+    const int lane = threadIdx.x % L, grp = lane / kWalkB, c = lane % kWalkB;
     const double *xc = X + (c < b ? c : 0);   // idle lanes read column 0
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < n;
-         i += (int64_t)gridDim.x * blockDim.x >> 6) {
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L; i < n;
+         i += (int64_t)gridDim.x * blockDim.x / L) {
         double acc = 0.0;
         const int64_t end = rp[i + 1];
-        for (int64_t e0 = rp[i]; e0 < end; e0 += 64) {
-            const int cnt = (int)min((int64_t)64, end - e0);
+        for (int64_t e0 = rp[i]; e0 < end; e0 += L) {
+            const int cnt = (int)min((int64_t)L, end - e0);
             const int32_t j = col[e0 + min(lane, cnt - 1)];
             const double sj = lane < cnt ? s[j] : 0.0;
-            for (int t0 = 0; t0 < cnt; t0 += kWalkG * kWalkU) {
+            for (int t0 = 0; t0 < cnt; t0 += G * kWalkU) {
                 double x[kWalkU], f[kWalkU];
 #pragma unroll
                 for (int u = 0; u < kWalkU; ++u) {
-                    const int t = t0 + kWalkG * u + grp;   // past cnt: the last one, weight 0
-                    const int32_t jt = __shfl(j, min(t, 63), 64);
-                    f[u] = t < 64 ? __shfl(sj, min(t, 63), 64) : 0.0;
+                    const int t = t0 + G * u + grp;   // past cnt: the last one, weight 0
+                    const int32_t jt = __shfl(j, min(t, L - 1), L);
+                    f[u] = t < L ? __shfl(sj, min(t, L - 1), L) : 0.0;
                     x[u] = xc[(int64_t)jt * b];
                 }
 #pragma unroll
@@ -203,7 +219,7 @@ k_half_walk(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             }
         }
 #pragma unroll
-        for (int o = kWalkB; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+        for (int o = kWalkB; o < L; o <<= 1) acc += __shfl_xor(acc, o, 64);
         if (grp == 0 && c < b) Y[i * b + c] = 0.5 * (X[i * b + c] + s[i] * acc);
     }
 }
@@ -341,6 +357,7 @@ lne_status graph_stats_impl(lne_ctx *ctx, const Graph *g, uint64_t seed, int32_t
             rp, n, s.as<double>());
     }
     LNE_TRY(check_launch(ctx, "graph_stats"));
+    const int wide = half_walk_groups(n, mean, maxd);
     double sv[2] = {0.0, 0.0};
     int32_t hf[kFlagStride];
     for (const bool eig : {false, true}) {
@@ -350,10 +367,14 @@ lne_status graph_stats_impl(lne_ctx *ctx, const Graph *g, uint64_t seed, int32_t
         for (int it = 0; it < iters; ++it) {
             {
                 Launch L(ctx, "graph_stats");
-                k_half_walk<<<(unsigned)std::min<int64_t>(ceil_div(n * 64, kStatThreads),
-                                                          kWalkBlocks),
-                              kStatThreads, 0, ctx->stream>>>(rp, g->col, s.as<double>(), x, y, n,
-                                                              b);
+                const unsigned grid = (unsigned)std::min<int64_t>(
+                    ceil_div(n * kWalkB * wide, kStatThreads), kWalkBlocks);
+#define LNE_HW(G)                                                                          \
+    k_half_walk<G><<<grid, kStatThreads, 0, ctx->stream>>>(rp, g->col, s.as<double>(), x, y, n, b)
+                if (wide == 1) LNE_HW(1);
+                else if (wide == 2) LNE_HW(2);
+                else LNE_HW(4);
+#undef LNE_HW
             }
             LNE_TRY(check_launch(ctx, "graph_stats"));
             if (it + 1 == iters) {

@@ -51,6 +51,19 @@ def test_graph_stats_rejects_bad_input(lne, ctx):
         lne.graph_stats(ctx, empty_rp, empty_col)
 
 
+@pytest.mark.parametrize("n", [5000, (1 << 20) + 7])
+@pytest.mark.parametrize("hub", [65, 64])
+def test_spectral_step_with_and_without_a_hub(lne, ctx, n, hub):
+    """A star of `hub` leaves beside a path: rows taken by one, two or four groups
+    of lanes, as the largest degree and the number of rows have it."""
+    e = np.stack([np.arange(hub + 1, n - 1), np.arange(hub + 2, n)], 1)
+    star = np.stack([np.zeros(hub, int), np.arange(1, hub + 1)], 1)
+    g = gs.from_edges(n, np.concatenate([star, e]).tolist())
+    rp, col = to_dev(g)
+    got = lne.graph_stats(ctx, rp, col, seed=7, wedges=100, iters=3)
+    assert abs(got[7] - (1.0 - gst.spectral_lambda2(g, 7, 3))) <= 1e-9
+
+
 @pytest.mark.parametrize("n", [(1 << 24) + 1, (1 << 26) + 5])
 def test_spectral_step_of_a_graph_of_many_vertices(lne, ctx, n):
     """One step on a cycle whose rows outnumber the waves of a launch (and, the
