@@ -454,8 +454,9 @@ lne_status lne_batch_run(lne_batch *b, const lne_trial *trials, int32_t n_trials
 lne_status lne_batch_spmm(lne_batch *b, const lne_trial *trials, int32_t n_trials,
                           const float *X, int64_t ldx, int64_t xs, float *Y, int64_t ldy,
                           int64_t ys, int32_t k);
-/* Launch shapes chosen by the tuner (0-based variant ids), nnz of the channel
- * CSR and the number of graph captures so far; any pointer may be NULL.
+/* Launch shapes chosen by the tuner (0-based variant ids; *spmm_variant is 0
+ * where the channel SpMM goes by column ranges, which have one shape), nnz of the
+ * channel CSR and the number of graph captures so far; any pointer may be NULL.
  * Host only.  Errors: EINVAL (b NULL). */
 lne_status lne_batch_info(const lne_batch *b, int32_t *spmm_variant, int32_t *gspmm_variant,
                           int64_t *channel_nnz, int32_t *captures);

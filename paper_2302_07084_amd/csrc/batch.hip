@@ -309,10 +309,13 @@ lne_status tune(lne_batch *b) {
                                 hipMemcpyHostToDevice, ctx->stream));
     LNE_HIP(ctx, hipMemcpyAsync(b->pc(), pc.data(), sizeof(float) * pc.size(),
                                 hipMemcpyHostToDevice, ctx->stream));
-    LNE_TRY(pick_variant(ctx, tune_key("spmm_chan", b, b->dp), kSpmmChanVariants, [&](int var) {
-        return spmm_chan(ctx, &b->ext, nullptr, 1, false, nt, b->chan(), b->om.as<float>(), b->dp,
-                         0, b->B.as<float>(), b->dp, ys, b->dp, var);
-    }, &b->spmm_v));
+    // the product of a power step, which the shape is for: whole rows, an
+    // operand a trial (zeros here).  Products by column ranges have one shape.
+    if (b->nseg == 1)
+        LNE_TRY(pick_variant(ctx, tune_key("spmm_chan", b, b->dp), kSpmmChanVariants, [&](int var) {
+            return spmm_chan(ctx, &b->ext, nullptr, 1, false, nt, b->chan(), b->A.as<float>(),
+                             b->dp, ys, b->B.as<float>(), b->dp, ys, b->dp, var);
+        }, &b->spmm_v));
     LNE_TRY(pick_variant(ctx, tune_key("graph_spmm_batch", b, b->d8), kGspmmBatchVariants,
                          [&](int var) {
         return gspmm_batch(ctx, &b->g, nt, b->d8, b->d8, xs, b->X0.as<float>(), b->P0.as<float>(),

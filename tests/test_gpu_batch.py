@@ -319,3 +319,23 @@ def test_tuner_cache_round_trip(lne, ctx, tmp_path, monkeypatch):
     assert B2.info()["spmm_variant"] == i1["spmm_variant"]
     assert len(path.read_text().splitlines()) == 2          # read, not re-tuned
     B2.close()
+
+
+def test_tuner_times_only_what_is_used(lne, tmp_path, monkeypatch):
+    """A batch whose channel SpMM goes by column ranges (6,000 rows of 144
+    floats, as above) has no whole-row shape to choose: the channel kernel does
+    not run while the batch is created."""
+    path = tmp_path / "tune.jsonl"
+    monkeypatch.setenv("LNE_TUNE_CACHE", str(path))
+    g = sbm([300] * 20, 0.03, 0.0008, seed=8)
+    p = gs.params(T=4, M_per_m=60, C=math.log(g.n), m=g.m, seed=3, d=134, oversample=10,
+                  precision="f32")
+    rp, col = to_dev(g)
+    c = lne.Context()
+    c.prof_enable()
+    B = lne.Batch(c, rp, col, p, max_trials=2)
+    assert B.info()["channel_nnz"] >= 2 * 32 * g.n
+    assert c.prof_get("spmm_chan")[1] == 0 and B.info()["spmm_variant"] == 0
+    assert {json.loads(x)["op"] for x in path.read_text().splitlines()} == {"graph_spmm_batch"}
+    B.close()
+    c.close()
