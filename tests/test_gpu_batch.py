@@ -339,3 +339,28 @@ def test_tuner_times_only_what_is_used(lne, tmp_path, monkeypatch):
     assert {json.loads(x)["op"] for x in path.read_text().splitlines()} == {"graph_spmm_batch"}
     B.close()
     c.close()
+
+
+@pytest.mark.parametrize("ldx", [8, (1 << 31) - 4, 1 << 31, 1 << 32])
+def test_batch_spmm_rows_far_apart(lne, ctx, ldx):
+    """Operand rows up to 2^32 floats apart (52 GB, of which four rows are
+    touched) give the bits of rows side by side."""
+    import ctypes
+
+    import torch
+    g = gs.complete(4)
+    p = gs.params(T=2, M_per_m=200, C=None, m=g.m, seed=3, d=2, oversample=2, precision="f32")
+    rp, col = to_dev(g)
+    B = lne.Batch(ctx, rp, col, p, max_trials=1)
+    trials = trial_vectors(1, seed=4, T=2)
+    X = torch.randn(4, 8, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    far = torch.empty(3 * ldx + 8, device="cuda").as_strided((4, 8), (ldx, 1))
+    far.copy_(X)
+    Y = torch.empty(4, 8, device="cuda")
+    ctx.check(ctx.L.lne_batch_spmm(B.h, lne._trial_array(trials), 1, far.data_ptr(),
+                                   ctypes.c_int64(ldx), ctypes.c_int64(0), Y.data_ptr(),
+                                   ctypes.c_int64(8), ctypes.c_int64(32), 8), "batch_spmm")
+    assert bool(Y.any()) and torch.equal(Y, B.spmm(trials, X)[0])
+    B.close()
+    del far
+    torch.cuda.empty_cache()
