@@ -162,12 +162,17 @@ void drop_graph(lne_batch *b) {
 }
 
 // The table of column ranges of the channel CSR, for operands of the batch's
-// own row stride.
+// own row stride.  Made after the batch's other buffers; where there is no
+// memory for it, the products take whole rows.
 lne_status make_segments(lne_batch *b) {
     b->seg.release();
     b->nseg = chan_ranges(b->n, b->ext.nnz, b->dp);
     if (b->nseg == 1) return LNE_OK;
-    LNE_TRY(alloc(b->ctx, b->seg, sizeof(uint32_t) * (size_t)b->n * (b->nseg + 1)));
+    if (alloc(b->ctx, b->seg, sizeof(uint32_t) * (size_t)b->n * (b->nseg + 1)) != LNE_OK) {
+        (void)hipGetLastError();
+        b->nseg = 1;
+        return LNE_OK;
+    }
     return chan_segments(b->ctx, &b->ext, b->nseg, b->seg.as<uint32_t>());
 }
 
@@ -463,7 +468,6 @@ lne_status lne_batch_create(lne_ctx *ctx, const lne_graph *gin, const lne_params
     LNE_TRY(channels_pass(ctx, g, p, &b->ext, st));
     if (st) st->nnz_counts = (uint64_t)b->ext.nnz;
     LNE_TRY(norm_channels(ctx, &b->ext, g, b->scale));
-    LNE_TRY(make_segments(b));
 
     const int64_t n = b->n, mt = max_trials;
     LNE_TRY(alloc(ctx, b->om, sizeof(float) * (size_t)n * b->dp));
@@ -487,6 +491,7 @@ lne_status lne_batch_create(lne_ctx *ctx, const lne_graph *gin, const lne_params
     // the shared test matrix of Algorithm "Fast Randomized SVD" (same seed and
     // values as the single-trial path)
     LNE_TRY(launch_gaussian(ctx, n, kp, b->dp, p->seed, LNE_F32, b->om.p));
+    LNE_TRY(make_segments(b));
     LNE_TRY(tune(b));
     LNE_HIP(ctx, hipStreamSynchronize(ctx->stream));
     guard.b = nullptr;

@@ -364,3 +364,43 @@ def test_batch_spmm_rows_far_apart(lne, ctx, ldx):
     B.close()
     del far
     torch.cuda.empty_cache()
+
+
+def test_batch_without_memory_for_the_column_ranges(lne, ctx):
+    """An allocator that refuses the table of column ranges (and nothing else):
+    the batch is made all the same, its products go by whole rows and give the
+    same bits, before and after a new channel pass."""
+    import ctypes
+
+    import torch
+    g = sbm([300] * 20, 0.03, 0.0008, seed=8)
+    p = gs.params(T=4, M_per_m=60, C=math.log(g.n), m=g.m, seed=3, d=134, oversample=10,
+                  precision="f32")
+    rp, col = to_dev(g)
+    trials = trial_vectors(2, seed=4, T=4)
+    X = torch.from_numpy(np.random.default_rng(0).standard_normal((2, g.n, 144)).astype("f")).cuda()
+    B = lne.Batch(ctx, rp, col, p, max_trials=2)
+    refs = [B.spmm(trials, X)]
+    B.resample([4, 3, 2, 1])
+    refs.append(B.spmm(trials, X))
+    B.close()
+    c = lne.Context()
+    table, refused = 4 * g.n * 3, []
+
+    def alloc(size, user):
+        if size == table:
+            refused.append(size)
+            return None
+        return give(size, user)
+
+    give, c._refusing = c._alloc, lne._ALLOC_T(alloc)
+    c.close()
+    c.h = ctypes.c_void_p()
+    assert c.L.lne_ctx_create(ctypes.byref(c.h), ctypes.c_void_p(c.stream.cuda_stream),
+                              c._refusing, c._free, None) == 0
+    B = lne.Batch(c, rp, col, p, max_trials=2)
+    assert len(refused) == 1 and torch.equal(B.spmm(trials, X), refs[0])
+    B.resample([4, 3, 2, 1])
+    assert len(refused) == 2 and torch.equal(B.spmm(trials, X), refs[1])
+    B.close()
+    c.close()
