@@ -2149,20 +2149,23 @@ __global__ void k_eig_weights(const double *__restrict__ V, const double *__rest
 
 // ---------------------------------------------------------------- host side
 // Lets `fn` use `bytes` of dynamic LDS (above the default 64 KB), once per
-// kernel; fails when the device offers less.
+// kernel and device (the attribute belongs to the current device's copy of the
+// kernel); fails when the device offers less.
 static lne_status lds_opt_in(lne_ctx *ctx, const void *fn, size_t bytes) {
+    if (bytes <= 64 * 1024) return LNE_OK;
+    int dev = 0;
+    LNE_HIP(ctx, hipGetDevice(&dev));
     static std::mutex mu;
-    static std::map<const void *, size_t> done;
+    static std::map<std::pair<int, const void *>, size_t> done;
     std::lock_guard<std::mutex> lock(mu);
-    auto it = done.find(fn);
-    if (it != done.end() && it->second >= bytes) return LNE_OK;
-    if (bytes > 64 * 1024 &&
-        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) !=
-            hipSuccess) {
+    size_t &have = done[{dev, fn}];
+    if (have >= bytes) return LNE_OK;
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) !=
+        hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, LNE_EUNSUPPORTED, "%zu bytes of LDS per block are not available", bytes);
     }
-    done[fn] = bytes;
+    have = bytes;
     return LNE_OK;
 }
 
