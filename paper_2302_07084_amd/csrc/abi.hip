@@ -235,14 +235,16 @@ double bessel_i(int n, double x) {
 }
 
 // ------------------------------------------------------------------- stages
-// Pair-buffer budget in bytes: LNE_HBM_BUDGET_GB if set, else 70% of HBM.
-static double pair_budget(lne_ctx *ctx) {
+// Pair-buffer budget in bytes: LNE_HBM_BUDGET_GB if set, else 70% of HBM less
+// `tables`, what the sampler's records hold beside them beyond the 12 bytes an
+// arc of a weighted graph that the share leaves room for.
+static double pair_budget(lne_ctx *ctx, double tables) {
     const char *env = getenv("LNE_HBM_BUDGET_GB");
     if (env && *env) return atof(env) * 1e9;
     size_t fr = 0, tot = 0;
     if (hipMemGetInfo(&fr, &tot) != hipSuccess || tot == 0) return 64e9;
     (void)ctx;
-    return 0.7 * (double)tot;
+    return 0.7 * (double)tot - tables;
 }
 
 // Device bytes one row range needs while it is aggregated: two (key, weight)
@@ -442,7 +444,8 @@ static lne_status sparsify_impl(lne_ctx *ctx, const Graph *g, const lne_params *
         st->nnz_counts = 0;
         st->entries = total;
     }
-    const double budget = pair_budget(ctx);
+    const double budget =
+        pair_budget(ctx, (double)S.rows.bytes + (double)S.arcs.bytes * (4.0 / 16.0));
     // the upper-triangle pass needs about as much memory as the two-orientation
     // one for half the entries
     if (sym && total > 0 && range_bytes(2 * total) <= budget) {
