@@ -237,6 +237,57 @@ def test_orthonormalize_wider_than_one_tile_group(lne, ctx, n, k, dtype):
     assert err <= 16 * 4 * math.sqrt(k) * u
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("n,k", [(9_001, 145), (7_003, 209), (20_003, 257), (30_011, 266)])
+def test_orthonormalize_at_the_widths_of_the_largest_kernels(lne, ctx, n, k, dtype):
+    """Widths that take the largest variants of the factorisation and, in BF16,
+    of the projection (266: the precision configuration's), as in the test
+    above.  BF16, u = 2^-8: the last product's weights have diagonals near one,
+    rounded by u / 2, and Q's entries are rounded by u / 2, so Q^T Q is off by
+    2 u; the first product's rounding (u / 2 of each column, which QR turns
+    into sqrt 2 of that) adds to the distance from the QR factor of Y.  Both
+    bars allow 4 u."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(k)
+    Y = torch.randn(n, (k + 7) // 8 * 8, generator=g, device="cuda", dtype=torch.float64)[:, :k]
+    Y *= 1.0 + torch.linspace(0, 1, k, device="cuda")
+    tdt = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    Yd = torch.empty(n, (k + 7) // 8 * 8, dtype=tdt, device="cuda")[:, :k]
+    Yd.copy_(Y)
+    q, r = np.linalg.qr(Yd.double().cpu().numpy())
+    q = q * np.sign(np.diag(r))
+    lne.orthonormalize(ctx, Yd)
+    Q = Yd.double().cpu().numpy()
+    err = np.linalg.norm(Q - q) / np.linalg.norm(q)
+    if dtype == "bf16":
+        assert err <= 4 * UBF
+        assert np.max(np.abs(Q.T @ Q - np.eye(k))) <= 4 * UBF
+    else:
+        assert err <= 16 * 4 * math.sqrt(k) * (U64 if dtype == "f64" else U32)
+
+
+@pytest.mark.parametrize("late", [False, True])
+@pytest.mark.parametrize("k", [138, 200, 266, 288])
+def test_orthonormalize_takes_the_shift_in_a_later_panel(lne, ctx, k, late):
+    """A column that depends on the ones before it to 1e-9, in the middle panels
+    or the last but two column: its pivot fails the 1e-14 test after several
+    panels have been written, and the factorisation starts again with the
+    shift.  The shift leaves a condition number of about 1e6 to the second pass
+    (orthonormal to 1e-4 then), the third is orthonormal to rounding."""
+    import torch
+    n, j = 4000, (k - 3 if late else 88)
+    rng = np.random.default_rng(k)
+    Y = rng.standard_normal((n, k))
+    Y[:, j] = Y[:, :j] @ rng.standard_normal(j) / math.sqrt(j) + 1e-9 * rng.standard_normal(n)
+    d = np.abs(np.diag(np.linalg.qr(Y, mode="r"))) / np.linalg.norm(Y, axis=0)
+    assert d[j] ** 2 < 1e-15 and np.all(np.delete(d, j) > 0.5)
+    Yd = torch.from_numpy(Y).cuda()
+    lne.orthonormalize(ctx, Yd)
+    Q = Yd.cpu().numpy()
+    assert np.max(np.abs(Q.T @ Q - np.eye(k))) < 1e-12
+    assert np.linalg.norm(Y - Q @ (Q.T @ Y)) < 1e-12 * np.linalg.norm(Y)
+
+
 def test_orthonormalize_ill_conditioned_takes_shift(lne, ctx):
     import torch
     n, k = 4000, 40
