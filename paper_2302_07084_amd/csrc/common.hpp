@@ -401,7 +401,8 @@ lne_status norm_channels(lne_ctx *ctx, lne_csr *ext, const Graph *g, double scal
 // `ext` with coef[16 t + r - 1] = s_t[r] / pi_r; k <= 256, k % 4 == 0, X's columns
 // up to k zero-padded, ldx < 2^32.  seg: its nseg column ranges
 // (chan_segments), taken one after the other, or NULL for whole rows.
-// shared: gather an operand's row once for several trials (xs = 0).
+// shared: gather an operand's row once for several trials (xs = 0) where that
+// pays, by whole rows.
 // variant: launch shape 0..5 of whole rows with an operand each; the result
 // is the same in every way of these.
 lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int nseg, bool shared,
@@ -410,10 +411,17 @@ lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int 
 constexpr int kSpmmChanVariants = 6;
 // Column ranges of that product: chan_ranges(n, nnz, ldx) of them for an
 // operand of n rows of ldx floats, as many as bring a range's rows of X down
-// to kChanRangeBytes (of an XCD's 4 MB of L2: 1.5, 2.5, 3 and 4 MB measured
-// 69, 65, 65 and 79 ms at 2 10^8 entries, n = 10^5, eight trials) -- or 1 when
-// rows have fewer than kChanMinRun entries a range on average, so that a range
-// would not fill half a wave's step.
+// to kChanRangeBytes (of an XCD's 4 MB of L2; 1.5, 2.5, 3, 3.5 and 4 MB take
+// 52.5, 50.9, 50.6, 50.7 and 51.1 ms at 2 10^8 entries, n = 10^5, k = 144, eight
+// trials' own operands) -- or 1 when rows have fewer than kChanMinRun entries
+// a range on average, so that a range would not fill half a wave's step.
+// Eight trials' products by ranges and by whole rows, ms, by entries a row and
+// range: n = 10^5, k = 144 (22 ranges) 4.7: 8.9 and 6.4, 10: 11.2 and 14.0, 26:
+// 17.7 and 35.4, 99: 52.7 and 135; k = 48 (8 ranges) 19: 3.7 and 3.4, 37: 5.3 and
+// 6.5; n = 30,000, k = 144 (7 ranges) 15: 1.19 and 1.45, 42: 2.2 and 4.5; n =
+// 10,000 (3 ranges) 34: 0.34 and 0.32, 188: 1.28 and 1.37.  Trials that share
+// an operand gather an eighth of the rows and take whole rows throughout: n =
+// 10^5, k = 144 26: 9.9 and 6.5, 99: 25.8 and 24.6, 192: 46.7 and 47.8.
 constexpr int64_t kChanRangeBytes = 5ll << 19;
 constexpr int64_t kChanMinRun = 32;
 int chan_ranges(int64_t n, int64_t nnz, int64_t ldx);

@@ -131,8 +131,8 @@ __global__ void k_norm_chan(const int64_t *__restrict__ rp, const int32_t *__res
 // change the result.
 //   TB = 1: wave (trial, row), trial-major (TM: consecutive waves share a
 //   trial's operand) or row-major (they share a row's entries).
-//   TB > 1: wave = row, TB trials of one shared operand: an X row is gathered
-//   once for all of them (a trial that drops the entry adds nothing).
+//   TB > 1: wave = row, TB trials of one shared operand, by whole rows: an X row
+//   is gathered once for all of them (a trial that drops the entry adds nothing).
 // 2 10^8 entries, n = 10^5, 144 columns, eight trials: each trial's own operand
 // 132 ms by whole rows with four columns a lane (bound by memory-side lines),
 // 50 by ranges of 2.5 MB; one operand for all 70 ms with a gather each, 24
@@ -507,7 +507,6 @@ lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int 
                     variant);
     const int64_t n = ext->n_rows;
     if (n == 0 || ntr == 0) return LNE_OK;
-    if (!seg) nseg = 1;
     for (int t0 = 0; t0 < ntr;) {
         // groups of eight, four and two trials, then a single one.  An incomplete
         // group costs what a full one does: at 8,000 x 144 five trials in a group
@@ -517,21 +516,23 @@ lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int 
         const int group = left >= 7 ? 8 : left >= 3 ? 4 : left;
         const int tb = shared && chan_shared_pays(n, k, group) ? group : 1;
         const int nt = tb == 1 ? left : left >= 8 ? left / 8 * 8 : std::min(tb, left);
+        // a shared gather by whole rows (chan_ranges has the times of both)
+        const uint32_t *sg = tb == 1 ? seg : nullptr;
         const double *cf = coef + 16 * t0;
         const float *Xt = X + t0 * xs;
         float *Yt = Y + t0 * ys;
-        for (int s = 0; s < nseg; ++s) {
+        for (int s = 0; s < (sg ? nseg : 1); ++s) {
             Launch L(ctx, "spmm_chan");
 #define LNE_CS(TB, VW, U, TM)                                                                  \
         k_chan_seg<TB, VW, U, TM><<<grid_of(n * ceil_div(nt, TB), 4), 256, 0, ctx->stream>>>(  \
-            ext->row_ptr, seg, nseg, s, ext->col, (const double *)ext->val, n, nt, cf, Xt, ldx, \
+            ext->row_ptr, sg, nseg, s, ext->col, (const double *)ext->val, n, nt, cf, Xt, ldx, \
             xs, Yt, ldy, ys, k, s == 0 ? 1 : 0)
 #define LNE_CV(VW)                                                                             \
         do {                                                                                   \
             if (tb == 2) LNE_CS(2, VW, 4, true);                                               \
             else if (tb == 4) LNE_CS(4, VW, 4, true);                                          \
             else if (tb == 8) LNE_CS(8, VW, 4, true);                                          \
-            else if (seg || variant == 0) LNE_CS(1, VW, 4, true);                              \
+            else if (sg || variant == 0) LNE_CS(1, VW, 4, true);                              \
             else if (variant == 1) LNE_CS(1, VW, 2, true);                                     \
             else if (variant == 2) LNE_CS(1, VW, 8, true);                                     \
             else if (variant == 3) LNE_CS(1, VW, 4, false);                                    \
