@@ -1006,14 +1006,17 @@ k_chol_inv(double *Gb, int k, double *Wb, int32_t *__restrict__ status,
 }
 
 // ---------------------------------------------------------------- eigen-solver
-// Symmetric eigen-decomposition of a k x k matrix, in three phases, the first
-// two by one workgroup each (Householder reduction to tridiagonal form, the
-// tridiagonal eigen-problem, the reflectors applied to its eigenvectors):
-//  1. k - 2 Householder steps.  Step j reflects the entries of column j below
-//     the subdiagonal to zero: with x = A[j+1.., j], beta = -sign(x0) |x|,
-//     v = (1, x1 / (x0 - beta), ...), tau = (beta - x0) / beta, the trailing
-//     block becomes A - v w^T - w v^T with p = tau A v, w = p - (tau/2)(p.v) v.
-//     v is written into row j (which later steps never touch).
+// Symmetric eigen-decomposition of a k x k matrix, in three phases: Householder
+// reduction to tridiagonal form and the tridiagonal eigen-problem, by one
+// workgroup each, and the reflectors applied to its eigenvectors, by a wave for
+// each 16 of these:
+//  1. k - 2 Householder steps on the matrix scaled to unit size.  Step j
+//     reflects the entries of column j below the subdiagonal to zero by H = I -
+//     tau v v^T: with x = A[j+1.., j] and beta = -sign(x0) |x|, v = (1, x1 / (x0 -
+//     beta), ...) and tau = (beta - x0) / beta.  The trailing block becomes A -
+//     v w^T - w v^T with p = tau A v, w = p - (tau/2)(p.v) v (k_tridiag works
+//     with u = (x0 - beta) v instead).  v is left in row j (which later steps
+//     never touch).
 //  2. The tridiagonal matrix (d, e): implicit QL sweeps (Wilkinson's shift)
 //     chase the shifted bulge from the bottom of an unreduced block to its
 //     top with plane rotations.  One wave computes a sweep's rotations while
@@ -1664,13 +1667,13 @@ __device__ __forceinline__ void tridiag_eig(int k, const EigWs &out) {
         // ---- merge: eigenvalues and eigenvectors of D + rho z z^T, D the
         // eigenvalues of T1 and T2, z the rows h-1 / h of their eigenvectors.
         // Deflation (a negligible weight, or two poles whose rotation
-        // leaves a negligible coupling), then per root a bisection of the
-        // secular equation 1 + rho sum z_i^2 / (d_i - lambda) = 0 in its
-        // interval between poles (its distance to the nearer pole kept as
-        // (origin, tau) so that differences stay accurate), and weights
-        // recomputed from the roots (Gu and Eisenstat) so that the
-        // eigenvectors z_i / (d_i - lambda_j) come out orthogonal (column j
-        // of U; k_eig_back multiplies).
+        // leaves a negligible coupling), then each root of the secular
+        // equation 1 + rho sum z_i^2 / (d_i - lambda) = 0 in its interval
+        // between poles, by a bracketed iteration (its distance to the nearer
+        // pole kept as (origin, tau) so that differences stay accurate), and
+        // weights recomputed from the roots (Gu and Eisenstat) so that the
+        // eigenvectors z_i / (d_i - lambda_j) come out orthogonal (column j of
+        // U; k_eig_back multiplies).
         int *ord = idx, *kept = idx + MK;
         double *dk = buf, *zk = buf + MK, *tau = buf + 2 * MK, *zh = buf + 3 * MK;
         for (int i = tid; i < k; i += NT)
@@ -2102,8 +2105,8 @@ k_eig_back(double *__restrict__ A, int k, double *__restrict__ ws, double *__res
 }
 
 // All three phases in one launch for matrices that are not torn, whose phases
-// are as short as a launch (k = 3: 23 us in three launches, 16 in one; k = 16:
-// 103 and 93).
+// are as short as a launch (k = 3: 23 us in three launches, 16 in one, before the
+// scaling; k = 16: 103 and 93).
 __global__ void __launch_bounds__(kTriDiagThreads)
 k_sym_eig_small(double *__restrict__ A, int k, double *__restrict__ ws, double *__restrict__ V,
                 double *__restrict__ lam) {
