@@ -1308,13 +1308,25 @@ __device__ __forceinline__ void tridiag(double *__restrict__ A, int k, const Eig
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const __amdgpu_buffer_rsrc_t ab = square_buf(A, k);
     auto held = [&](int q) { return 2 * (w + W * (q / 2)) + q % 2; };   // row of a[q]
+    // (the largest entry from a read of its own: with the matrix already held,
+    // its registers spill)
+    double amax = 0.0;
+    for (int i = tid; i < k * k; i += 8 * 64 * W)
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            amax = fmax(amax, fabs(buf_d(ab, 8 * (i + 64 * W * u))));   // past the end: zeros
+    part[w][lane] = wave_max(amax);
+    lds_barrier();
+#pragma unroll
+    for (int v = 0; v < W; ++v) amax = fmax(amax, part[v][lane]);
+    const double unit = readlane_d(unit_scale(amax), 0), back = readlane_d(1.0 / unit, 0);
     double a[Q][C];
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int i = held(q), l = lane + 64 * c;
-            a[q][c] = buf_d(ab, 8 * (i * k + l) | out_if(i, k) | out_if(l, k));
+            a[q][c] = unit * buf_d(ab, 8 * (i * k + l) | out_if(i, k) | out_if(l, k));
         }
     // row j to LDS by the wave that holds it
     auto publish = [&](int j) {
@@ -1325,20 +1337,6 @@ __device__ __forceinline__ void tridiag(double *__restrict__ A, int k, const Eig
 #pragma unroll
                 for (int c = 0; c < C; ++c) row[lane + 64 * c] = a[q][c];
     };
-    double amax = 0.0;
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-#pragma unroll
-        for (int c = 0; c < C; ++c) amax = fmax(amax, fabs(a[q][c]));
-    part[w][lane] = wave_max(amax);
-    lds_barrier();
-#pragma unroll
-    for (int v = 0; v < W; ++v) amax = fmax(amax, part[v][lane]);
-    const double unit = unit_scale(wave_max(amax)), back = 1.0 / unit;
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-#pragma unroll
-        for (int c = 0; c < C; ++c) a[q][c] *= unit;
     publish(0);
     lds_barrier();
     for (int j = 0; j + 2 < k; ++j) {
@@ -1463,14 +1461,24 @@ k_tridiag_wide(double *__restrict__ A, int k, double *__restrict__ ws) {
     const int tid = threadIdx.x, lane = tid & 63;
     constexpr int P = kSolveThreads / MK < 4 ? kSolveThreads / MK : 4;   // parts per row sum
     constexpr int G = kSolveThreads / MK;                                 // row groups
+    // (eight reads at a time; past the end: zeros, and no stores)
+    const __amdgpu_buffer_rsrc_t ab = square_buf(A, k);
     double amax = 0.0;
-    for (int i = tid; i < k * k; i += kSolveThreads) amax = fmax(amax, fabs(A[i]));
+    for (int i = tid; i < k * k; i += 8 * kSolveThreads)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) amax = fmax(amax, fabs(buf_d(ab, 8 * (i + kSolveThreads * u))));
     amax = wave_max(amax);
     if (lane == 0) pq[tid >> 6] = amax;
     __syncthreads();
     for (int v = 0; v < kSolveThreads / 64; ++v) amax = fmax(amax, pq[v]);
     const double unit = unit_scale(amax), back = 1.0 / unit;
-    for (int i = tid; i < k * k; i += kSolveThreads) A[i] *= unit;
+    for (int i = tid; i < k * k; i += 8 * kSolveThreads) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = buf_d(ab, 8 * (i + kSolveThreads * u));
+#pragma unroll
+        for (int u = 0; u < 8; ++u) buf_store(ab, 8 * (i + kSolveThreads * u), unit * x[u]);
+    }
     __syncthreads();
     for (int j = 0; j + 2 < k; ++j) {
         const int m = k - j - 1;   // trailing indices j+1 .. k-1
