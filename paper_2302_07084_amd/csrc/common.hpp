@@ -402,7 +402,7 @@ lne_status norm_channels(lne_ctx *ctx, lne_csr *ext, const Graph *g, double scal
 // up to k zero-padded, ldx < 2^32.  seg: its nseg column ranges
 // (chan_segments), taken one after the other, or NULL for whole rows.
 // shared: gather an operand's row once for several trials (xs = 0) where that
-// pays, by whole rows.
+// pays.
 // variant: launch shape 0..5 of whole rows with an operand each; the result
 // is the same in every way of these.
 lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int nseg, bool shared,
@@ -419,11 +419,14 @@ constexpr int kSpmmChanVariants = 6;
 // range: n = 10^5, k = 144 (22 ranges) 4.7: 8.9 and 6.4, 10: 11.2 and 14.0, 26:
 // 17.7 and 35.4, 99: 52.7 and 135; k = 48 (8 ranges) 19: 3.7 and 3.4, 37: 5.3 and
 // 6.5; n = 30,000, k = 144 (7 ranges) 15: 1.19 and 1.45, 42: 2.2 and 4.5; n =
-// 10,000 (3 ranges) 34: 0.34 and 0.32, 188: 1.28 and 1.37.  Trials that share
-// an operand gather an eighth of the rows and take whole rows throughout: n =
-// 10^5, k = 144 26: 9.9 and 6.5, 99: 25.8 and 24.6, 192: 46.7 and 47.8.
+// 10,000 (3 ranges) 34: 0.34 and 0.32, 188: 1.28 and 1.37.  Eight trials of one
+// operand gather an eighth of the rows and take whole rows below kChanSharedRun
+// entries a row and range: n = 10^5, k = 144 51: 15.0 and 12.7, 99: 25.8 and 24.6,
+// 192: 46.6 and 47.5; n = 30,000 42: 1.30 and 1.14, 310: 7.3 and 7.7; four trials
+// 99: 13.0 and 16.8, 42: 0.70 and 0.64, two 99: 8.0 and 17.7, 42: 0.46 and 0.58.
 constexpr int64_t kChanRangeBytes = 5ll << 19;
 constexpr int64_t kChanMinRun = 32;
+constexpr int64_t kChanSharedRun = 128;
 int chan_ranges(int64_t n, int64_t nnz, int64_t ldx);
 lne_status chan_segments(lne_ctx *ctx, const lne_csr *ext, int nseg, uint32_t *seg);
 // Propagation step for ntr trials (blocks zs apart, rows ld apart, k columns):

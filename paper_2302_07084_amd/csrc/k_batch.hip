@@ -131,8 +131,8 @@ __global__ void k_norm_chan(const int64_t *__restrict__ rp, const int32_t *__res
 // change the result.
 //   TB = 1: wave (trial, row), trial-major (TM: consecutive waves share a
 //   trial's operand) or row-major (they share a row's entries).
-//   TB > 1: wave = row, TB trials of one shared operand, by whole rows: an X row
-//   is gathered once for all of them (a trial that drops the entry adds nothing).
+//   TB > 1: wave = row, TB trials of one shared operand: an X row is gathered
+//   once for all of them (a trial that drops the entry adds nothing).
 // 2 10^8 entries, n = 10^5, 144 columns, eight trials: each trial's own operand
 // 132 ms by whole rows with four columns a lane (bound by memory-side lines),
 // 50 by ranges of 2.5 MB; one operand for all 70 ms with a gather each, 24
@@ -516,8 +516,9 @@ lne_status spmm_chan(lne_ctx *ctx, const lne_csr *ext, const uint32_t *seg, int 
         const int group = left >= 7 ? 8 : left >= 3 ? 4 : left;
         const int tb = shared && chan_shared_pays(n, k, group) ? group : 1;
         const int nt = tb == 1 ? left : left >= 8 ? left / 8 * 8 : std::min(tb, left);
-        // a shared gather by whole rows (chan_ranges has the times of both)
-        const uint32_t *sg = tb == 1 ? seg : nullptr;
+        // a gather for eight by whole rows, where ranges are short (chan_ranges
+        // has the times of both)
+        const uint32_t *sg = tb == 8 && ext->nnz < kChanSharedRun * n * nseg ? nullptr : seg;
         const double *cf = coef + 16 * t0;
         const float *Xt = X + t0 * xs;
         float *Yt = Y + t0 * ys;

@@ -166,6 +166,26 @@ def test_batch_spmm_groups_of_a_shared_operand(lne, ctx, n):
     B.close()
 
 
+@pytest.mark.parametrize("M_per_m,long", [(15, False), (60, True)])
+def test_batch_spmm_shared_operand_by_ranges_and_whole_rows(lne, ctx, M_per_m, long):
+    """Two column ranges (6,000 rows of 144 floats): groups of two and four trials
+    of one operand go by ranges, groups of eight by ranges on long rows only;
+    the bits are those of the operand copied for each trial."""
+    import torch
+    g = sbm([300] * 20, 0.03, 0.0008, seed=8)
+    p = gs.params(T=4, M_per_m=M_per_m, C=math.log(g.n), m=g.m, seed=3, d=134, oversample=10,
+                  precision="f32")
+    rp, col = to_dev(g)
+    B = lne.Batch(ctx, rp, col, p, max_trials=14)
+    assert (B.info()["channel_nnz"] >= 128 * 2 * g.n) == long
+    trials = trial_vectors(14, seed=4, T=4)
+    X = torch.from_numpy(np.random.default_rng(0).standard_normal((g.n, 144)).astype("f")).cuda()
+    own = B.spmm(trials, X.expand(14, g.n, 144))
+    for ntr in (2, 4, 8, 14):
+        assert torch.equal(B.spmm(trials[:ntr], X), own[:ntr]), ntr
+    B.close()
+
+
 def _single_trial_reference(lne, ctx, rp, col, p, ch, tr):
     M = lne.trial_matrix(ctx, rp, col, p, ch, tr)
     pt = dict(p, s=tr["s"], cheb_k=tr["k"], theta=tr["theta"], mu=tr["mu"])
