@@ -176,8 +176,10 @@ constexpr int64_t kWalkBlocks = 1 << 22;   // a launch has fewer than 2^32 threa
                                            // taken in turn
 // The groups of a row: a wave's four where a hub's row would outlast the others,
 // two of them where there are rows enough to cover that, one on short rows of
-// like length.  A step of graph_stats, us, by G:
+// like length (all four on few rows, where only latency counts).  A step of
+// graph_stats, us, by G:
 //                          1      2      4
+//      2,000 planted      21.9   21.8   21.5      (12)
 //     30,000 cycle        29.8   35.1   39.5      (2 arcs a row)
 //     30,000 planted      36.9   37.7   39.6      (16)    64.4   62.8   62.4 (100)
 //  3,000,000 cycle         761  1,029  1,585
@@ -186,6 +188,7 @@ constexpr int64_t kWalkBlocks = 1 << 22;   // a launch has fewer than 2^32 threa
 //    300,000 power-law     199    132    146      (4)      378    233    185 (16)
 //  3,000,000 power-law   1,231  1,157  1,624      (4)    3,117  2,542  2,800 (24)
 inline int half_walk_groups(int64_t n, double mean, uint64_t max_deg) {
+    if (n < 8192) return 4;
     if (max_deg <= 64) return mean <= 16.0 ? 1 : 4;
     return n >= 1 << 20 && mean <= 32.0 ? 2 : 4;
 }
